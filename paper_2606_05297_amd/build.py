@@ -33,6 +33,7 @@ SOURCES = [
     "kernels_gate_dd.hip",
     "kernels_gate_de.hip",
     "kernels_gate_df.hip",
+    "small_eval.hip",
     "gate_half.hip",
     "gate_real.hip", "gate_real_fuse.hip",
     "sector.hip",
@@ -75,7 +76,7 @@ def _compile(src: str) -> str:
 
 # Sources with matrix-core (MFMA) instructions; their device assembly is checked
 # after compilation (see check_mfma_operands).
-MFMA_SOURCES = ["dense_gate.hip", "mlp_kernels.hip"]
+MFMA_SOURCES = ["dense_gate.hip", "mlp_kernels.hip", "small_eval.hip"]
 
 _MFMA_RE = re.compile(r"v_mfma_\w+\s+([av])\[(\d+):(\d+)\],[^\n]*,\s*([av])\[(\d+):(\d+)\]\s*$", re.M)
 

@@ -236,6 +236,7 @@ int stage_gates(Ctx &c, const fock_op_t *ops, const double *theta, int n, const 
       r.type = ops[k].type;
       r.u_off = k * stride;
       r.nblk = nblk && nblk[k] > 0 ? nblk[k] : is_single_mode(ops[k].type) ? Gd : gate_blocks_count(c.g, ops[k].i);
+      r.modes = gate_modes(ops[k]);
     }
     return launch_gate_build_args(ga, c.T, (float2 *)(c.ws + c.L.utab), (double *)(c.ws + c.L.theta),
                                   (GateRec *)(c.ws + c.L.recs), c.s);
@@ -253,7 +254,7 @@ int stage_gates(Ctx &c, const fock_op_t *ops, const double *theta, int n, const 
     rec[k].type = ops[k].type;
     rec[k].u_off = k * stride;
     rec[k].nblk = nblk && nblk[k] > 0 ? nblk[k] : is_single_mode(ops[k].type) ? Gd : gate_blocks_count(c.g, ops[k].i);
-    rec[k].pad = 0;
+    rec[k].modes = gate_modes(ops[k]);
   }
   (void)bt;
   FOCK_HIP(hipMemcpyAsync(c.ws + c.L.theta, hp + c.L.theta, c.L.recs + br - c.L.theta, hipMemcpyHostToDevice, c.s));
@@ -737,18 +738,74 @@ static int reverse_real(Ctx &c, const fock_op_t *ops, int n, const std::vector<R
   return launch_reduce_rows(part, c.L.rs, (const GateRec *)(c.ws + c.L.recs), n, res, c.s);
 }
 
+// ---------------------------------------------------------------- small states
+// Small states are evaluated by one workgroup in one launch (small_eval.hip):
+// whenever both states of the reverse sweep fit its LDS (about 9,500
+// amplitudes), unless the caller asks for a particular gate path (dense gates,
+// fused runs, kept forward states).  Measured per call, against gate by gate:
+// 21 gates on 64 amplitudes 64 against 159 us, 30 gates on 4,096 amplitudes 172
+// against 387 us, 35 gates on 7,776 amplitudes (the largest of d = 6) 286
+// against 347 us.
+static bool small_used(const Ctx &c, int n) {
+  return !c.g.half && !c.store && gate_variant() == FOCK_GATE_BLOCK && g_fuse.load() == FOCK_FUSE_OFF &&
+         small_eval_ok(c.g.L, c.g.d, c.g.n_amp, n);
+}
+
+SmallItem small_item(const HamArgs &h, uint32_t namp, int n, bool grad) {
+  SmallItem it;
+  memset(&it, 0, sizeof(it));
+  it.n = n;
+  it.grad = grad;
+  it.point = -1;
+  it.L = h.L;
+  it.d = h.d;
+  it.N = (int)namp;
+  it.wrap = h.periodic_wrap;
+  it.ustride = gate_stride(h.d);
+  it.chunk = small_chunk(h.d, namp, n);
+  it.J = h.J;
+  it.Delta = h.Delta;
+  it.c2 = h.c2;
+  it.mu = h.mu;
+  return it;
+}
+
+// Tables and the whole evaluation; res (device or host-visible) receives
+// <H>, <1> and, with grad, the raw gate sums.
+static int enqueue_small(Ctx &c, const fock_op_t *ops, const double *theta, int n, const void *psi0, float2 *phi,
+                         float2 *lam, bool grad, double *res) {
+  if (n > c.L.nmax) return set_error(FOCK_ERR_SIZE, "circuit of %d gates exceeds the workspace's %d", n, c.L.nmax);
+  int rc = n > 0 ? stage_gates(c, ops, theta, n, nullptr) : FOCK_OK;
+  if (rc) return rc;
+  SmallItem it = small_item(c.h, c.g.n_amp, n, grad);
+  it.psi0 = (const float2 *)psi0;
+  it.phi = phi;
+  it.lam = lam;
+  it.U = (const float2 *)(c.ws + c.L.utab);
+  it.recs = (const GateRec *)(c.ws + c.L.recs);
+  it.res = res;
+  ProfScope ps(grad ? FOCK_K_ADJ : FOCK_K_GATE, c.s, ((grad ? 48.0 : 16.0) * n + 16.0) * c.g.n_amp);
+  return launch_small_eval(it, nullptr, 0, small_lds_bytes(it), small_waves(it), c.T, nullptr, c.s);
+}
+
 // State of a circuit, its energy and the pool gradients there, with the
 // scoring fused where possible; g receives the raw 2 Re <H psi|A_k psi>.
 int run_score(Ctx &c, const fock_op_t *ops, const double *theta, int n, const void *psi0, float2 *phi,
               float2 *lam, const fock_op_t *pool, int P, double *E, double *norm2, double *g) {
   std::vector<GateGroup> groups;
   std::vector<RealRun> runs;
-  const bool real = real_eval(c, ops, n);
-  int rc = real ? stage_real(c, ops, theta, n, &runs) : stage_circuit(c, ops, theta, n, &groups);
-  if (rc) return rc;
-  if ((rc = real ? forward_real(c, ops, n, runs, phi) : forward_circuit(c, ops, n, groups, psi0, phi))) return rc;
   double *res = (double *)(c.ws + c.L.result);
-  if ((rc = score_dev(c, pool, P, phi, lam, res))) return rc;
+  int rc;
+  if (small_used(c, n)) {  // leaves phi and H phi, and the energy and norm in res
+    if ((rc = enqueue_small(c, ops, theta, n, psi0, phi, lam, false, res))) return rc;
+    if ((rc = pool_dev(c, pool, P, phi, lam, res + 2))) return rc;
+  } else {
+    const bool real = real_eval(c, ops, n);
+    rc = real ? stage_real(c, ops, theta, n, &runs) : stage_circuit(c, ops, theta, n, &groups);
+    if (rc) return rc;
+    if ((rc = real ? forward_real(c, ops, n, runs, phi) : forward_circuit(c, ops, n, groups, psi0, phi))) return rc;
+    if ((rc = score_dev(c, pool, P, phi, lam, res))) return rc;
+  }
   std::vector<double> host(2 + P);
   if ((rc = fetch_results(c, 2 + P, host.data()))) return rc;
   const double nrm = host[1];
@@ -760,9 +817,30 @@ int run_score(Ctx &c, const fock_op_t *ops, const double *theta, int n, const vo
   return FOCK_OK;
 }
 
+// Rayleigh energy, norm and dE/dtheta from an evaluation's raw sums
+// (<H>, <1>, Re<lam|A_k phi>).
+static int finish_eval(const double *res, int n, bool grad, double *E, double *norm2, double *dE) {
+  const double nrm = res[1];
+  if (!std::isfinite(res[0]) || !std::isfinite(nrm) || nrm <= 0.0)
+    return set_error(FOCK_ERR_NONFINITE, "non-finite energy or zero norm (E=%g, norm2=%g)", res[0], nrm);
+  *E = res[0] / nrm;
+  if (norm2) *norm2 = nrm;
+  if (grad && dE)
+    for (int k = 0; k < n; ++k) dE[k] = 2.0 * res[2 + k] / nrm;
+  return FOCK_OK;
+}
+
 // Energy and (optionally) all dE/dtheta of a circuit; see fock_energy_grad_adjoint.
 int run_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int n, const void *psi0, float2 *phi,
                        float2 *lam, bool grad, double *E, double *norm2, double *dE) {
+  if (small_used(c, n)) {
+    int rc = tl_res.reserve(2 + (size_t)n);
+    if (rc) return rc;
+    if ((rc = enqueue_small(c, ops, theta, n, psi0, phi, lam, grad, tl_res.p))) return rc;
+    FOCK_HIP(hipStreamSynchronize(c.s));
+    prof_harvest();
+    return finish_eval(tl_res.p, n, grad, E, norm2, dE);
+  }
   std::vector<GateGroup> groups;
   std::vector<RealRun> runs;
   const bool real = real_eval(c, ops, n);
@@ -781,14 +859,7 @@ int run_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int n, const 
       if ((rc = reverse_real(c, ops, n, runs, tl_res.p, Ge))) return rc;
       FOCK_HIP(hipStreamSynchronize(c.s));
       prof_harvest();
-      const double nrm = tl_res.p[1];
-      if (!std::isfinite(tl_res.p[0]) || !std::isfinite(nrm) || nrm <= 0.0)
-        return set_error(FOCK_ERR_NONFINITE, "non-finite energy or zero norm (E=%g, norm2=%g)", tl_res.p[0], nrm);
-      *E = tl_res.p[0] / nrm;
-      if (norm2) *norm2 = nrm;
-      if (dE)
-        for (int k = 0; k < n; ++k) dE[k] = 2.0 * tl_res.p[2 + k] / nrm;
-      return FOCK_OK;
+      return finish_eval(tl_res.p, n, true, E, norm2, dE);
     } else {
       if (rh) {
         if ((rc = apply_h_real(c, res))) return rc;
@@ -819,14 +890,7 @@ int run_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int n, const 
   std::vector<double> host(cnt);
   rc = fetch_results(c, cnt, host.data());
   if (rc) return rc;
-  const double nrm = host[1];
-  if (!std::isfinite(host[0]) || !std::isfinite(nrm) || nrm <= 0.0)
-    return set_error(FOCK_ERR_NONFINITE, "non-finite energy or zero norm (E=%g, norm2=%g)", host[0], nrm);
-  *E = host[0] / nrm;
-  if (norm2) *norm2 = nrm;
-  if (grad && dE)
-    for (int k = 0; k < n; ++k) dE[k] = 2.0 * host[2 + k] / nrm;
-  return FOCK_OK;
+  return finish_eval(host.data(), n, grad, E, norm2, dE);
 }
 
 // All dE/dtheta by the reverse sweep alone, from phi = psi_n and lam = H psi_n

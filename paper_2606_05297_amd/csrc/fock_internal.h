@@ -97,8 +97,11 @@ enum GateKind { KIND_SUM = 0, KIND_DIFF = 1 };
 // One gate of a circuit as seen by the device-side gate build.
 struct GateRec {
   int type, u_off;  // generator type, complex offset of its table in the U buffer
-  int nblk, pad;    // workgroups of its reverse-step kernel (partials to reduce)
+  int nblk;         // workgroups of its reverse-step kernel (partials to reduce)
+  int modes;        // i in bits 0-7, j in bits 8-15 (0xff: none)
 };
+
+inline int gate_modes(const fock_op_t &op) { return (op.i & 0xff) | ((op.j & 0xff) << 8); }
 
 // Per-(d) gate eigendata on the device: for each two-mode type t < 5, the
 // packed blocks of V (complex double, b x b row-major per block, column m is

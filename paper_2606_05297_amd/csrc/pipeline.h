@@ -2,6 +2,7 @@
 #pragma once
 
 #include "fock_internal.h"
+#include "small_eval.h"
 
 namespace fock {
 
@@ -53,6 +54,8 @@ int make_ctx(const fock_ham_t &ham, uint32_t namp, int P, int n, void *ws, size_
 // room; *owner receives the allocation to free (nullptr: no store).
 int attach_state_store(Ctx &c, int nmax, void **owner);
 int stage_gates(Ctx &c, const fock_op_t *ops, const double *theta, int n, const int *nblk);
+// An evaluation's item with the lattice filled in (small_eval.h).
+SmallItem small_item(const HamArgs &h, uint32_t namp, int n, bool grad);
 // psi <- O_k src (src == psi: in place)
 int forward_gate(Ctx &c, const fock_op_t &op, int k, bool dag, const float2 *src, float2 *psi);
 int apply_h_dev(Ctx &c, const float2 *psi, float2 *hpsi, double *res2);

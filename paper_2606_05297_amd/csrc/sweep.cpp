@@ -25,6 +25,8 @@ using namespace fock;
 
 namespace {
 
+constexpr int kSideStreams = 3;
+
 size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct SPoint {
@@ -73,6 +75,9 @@ struct fock_sweep {
   std::vector<DGroup> groups;
   fock_adapt_opts_t opt;
   hipStream_t s = nullptr;  // private non-blocking stream (graph capture needs one)
+  // side streams of an evaluation round (forked from s and joined to it)
+  hipStream_t side[kSideStreams] = {};
+  hipEvent_t fork = nullptr, join[kSideStreams] = {};
   void *dbuf = nullptr;
   int *active_d = nullptr;
   double *res_d = nullptr;
@@ -108,8 +113,13 @@ double *pin_res(fock_sweep *sw) {
 struct Lists {
   std::vector<std::vector<std::vector<SweepItem>>> fwd, rev;  // [k][2 * group + item class]
   std::vector<std::vector<SweepHItem>> h;                     // [group]
+  std::vector<std::vector<SmallItem>> small;                  // points evaluated by one workgroup each, per launch
   std::vector<SweepRItem> red;
 };
+
+// Whether a point's circuit is evaluated whole by one workgroup (the rule of
+// the single-point path).
+bool point_small(const SPoint &P) { return small_eval_ok(P.g.L, P.g.d, P.g.n_amp, (int)P.ops.size()); }
 
 // A point's gate groups: [k0, k1) runs of phase gates (diag_run_end) or single gates.
 void point_groups(const std::vector<fock_op_t> &ops, std::vector<std::pair<int, int>> *gr) {
@@ -133,6 +143,7 @@ int build_lists(fock_sweep *sw, const std::vector<char> &sel, bool grad, Lists *
   int maxn = 0;
   for (size_t p = 0; p < npt; ++p) {
     const SPoint &P = sw->pts[p];
+    if (point_small(P)) continue;
     point_groups(P.ops, &groups[p]);
     run_base[p] = runs.size();
     for (auto &g : groups[p])
@@ -152,6 +163,7 @@ int build_lists(fock_sweep *sw, const std::vector<char> &sel, bool grad, Lists *
   Ls->fwd.assign(maxn, std::vector<std::vector<SweepItem>>(2 * NG));
   Ls->rev.assign(maxn, std::vector<std::vector<SweepItem>>(2 * NG));
   Ls->h.assign(NG, {});
+  Ls->small.clear();
   Ls->red.clear();
   for (size_t pi = 0; pi < npt; ++pi) {
     if (!sel[pi]) continue;
@@ -159,6 +171,22 @@ int build_lists(fock_sweep *sw, const std::vector<char> &sel, bool grad, Lists *
     const DGroup &G = sw->groups[P.group];
     const int stride = gate_stride(P.g.d);
     const int n = (int)P.ops.size();
+    if (point_small(P)) {
+      SmallItem it = small_item(P.h, P.g.n_amp, n, grad);
+      it.point = (int)pi;
+      it.psi0 = P.psi0;
+      it.phi = P.phi;
+      it.lam = P.lam;
+      it.U = G.utab + (size_t)P.gate_base * stride;
+      it.recs = G.recs + P.gate_base;
+      it.res = P.res;
+      // one launch per cutoff and workgroup size
+      auto same = [&](const std::vector<SmallItem> &v) { return v[0].d == it.d && small_waves(v[0]) == small_waves(it); };
+      auto at = std::find_if(Ls->small.begin(), Ls->small.end(), same);
+      if (at == Ls->small.end()) Ls->small.push_back({it});
+      else at->push_back(it);
+      continue;
+    }
     size_t ri = run_base[pi];
     for (size_t l = 0; l < groups[pi].size(); ++l) {
       const int k = groups[pi][l].first, k1 = groups[pi][l].second;
@@ -246,7 +274,10 @@ int upload_recs(fock_sweep *sw) {
     for (int k = 0; k < G.ngates; ++k) recs[k] = GateRec{FOCK_ROT, k * stride, 0, 0};
     for (int pi : G.pts) {
       const SPoint &P = sw->pts[pi];
-      for (size_t k = 0; k < P.ops.size(); ++k) recs[P.gate_base + k].type = P.ops[k].type;
+      for (size_t k = 0; k < P.ops.size(); ++k) {
+        recs[P.gate_base + k].type = P.ops[k].type;
+        recs[P.gate_base + k].modes = gate_modes(P.ops[k]);
+      }
     }
     FOCK_HIP(hipMemcpy(G.recs, recs.data(), sizeof(GateRec) * recs.size(), hipMemcpyHostToDevice));
   }
@@ -268,6 +299,21 @@ int enqueue_eval(fock_sweep *sw, const Lists &Ls, const std::vector<size_t> &off
     }
   }
   const int NG = (int)sw->groups.size();
+  // Whole evaluations of small points run on side streams beside the layers of
+  // the others: they keep one workgroup each busy for as long as many layers.
+  const int nside = Ls.fwd.empty() ? 0 : (int)std::min<size_t>(Ls.small.size(), kSideStreams);
+  if (nside > 0) FOCK_HIP(hipEventRecord(sw->fork, s));
+  for (int b = 0; b < nside; ++b) FOCK_HIP(hipStreamWaitEvent(sw->side[b], sw->fork, 0));
+  for (size_t b = 0; b < Ls.small.size(); ++b) {
+    const auto &v = Ls.small[b];
+    size_t lds = 0;
+    for (const SmallItem &it : v) lds = std::max(lds, small_lds_bytes(it));
+    const DGroup &G = sw->groups[sw->pts[v[0].point].group];
+    int rc = launch_small_eval(v[0], (const SmallItem *)(base + offs[oi++]), (int)v.size(), lds, small_waves(v[0]),
+                               G.T, sw->active_d, nside > 0 ? sw->side[b % nside] : s);
+    if (rc) return rc;
+  }
+  for (int b = 0; b < nside; ++b) FOCK_HIP(hipEventRecord(sw->join[b], sw->side[b]));
   for (size_t k = 0; k < Ls.fwd.size(); ++k)
     for (int li = 0; li < 2 * NG; ++li) {
       const auto &v = Ls.fwd[k][li];
@@ -281,7 +327,7 @@ int enqueue_eval(fock_sweep *sw, const Lists &Ls, const std::vector<size_t> &off
                             (const HamArgs *)(base + offs.back()), sw->active_d, sw->grid, s);
     if (rc) return rc;
   }
-  // energy / norm of every point
+  // energy / norm of every point evaluated gate by gate
   {
     const size_t off = offs[oi++];
     const int nr = (int)(offs[oi++]);
@@ -302,23 +348,26 @@ int enqueue_eval(fock_sweep *sw, const Lists &Ls, const std::vector<size_t> &off
                                  s);
     if (rc) return rc;
   }
+  for (int b = 0; b < nside; ++b) FOCK_HIP(hipStreamWaitEvent(s, sw->join[b], 0));
   FOCK_HIP(hipMemcpyAsync(pin_res(sw), sw->res_d, sizeof(double) * sw->n_res, hipMemcpyDeviceToHost, s));
   return FOCK_OK;
 }
 
-// Lay out all item lists in one device blob; offs lists, in order: forward
-// [k][2 g + class], H [g], E/norm reduce (offset, count), reverse
+// Lay out all item lists in one device blob; offs lists, in order: launches of
+// small points, forward [k][2 g + class], H [g], E/norm reduce (offset, count), reverse
 // [k][2 g + class], grad reduce,
 // and finally the per-point HamArgs array.
 int stage_lists(fock_sweep *sw, const Lists &Ls, bool grad, std::vector<size_t> *offs) {
   std::vector<char> blob;
   offs->clear();
+  for (auto &v : Ls.small) offs->push_back(push_items(blob, v));
   for (auto &lk : Ls.fwd)
     for (auto &v : lk) offs->push_back(push_items(blob, v));
   for (auto &v : Ls.h) offs->push_back(push_items(blob, v));
   std::vector<SweepRItem> en;
   for (size_t pi = 0; pi < sw->pts.size(); ++pi) {
     const SPoint &P = sw->pts[pi];
+    if (point_small(P)) continue;
     en.push_back(SweepRItem{(int)pi, 0, P.GH, 2, 0, 0, P.partial, P.res + 0});
     en.push_back(SweepRItem{(int)pi, 0, P.GH, 2, 1, 0, P.partial, P.res + 1});
   }
@@ -572,7 +621,7 @@ int score_phase(fock_sweep *sw, const std::vector<char> &sel, std::vector<std::v
     SPoint &P = sw->pts[pi];
     pargs.push_back(P.pa);
     if (!sel[pi]) continue;
-    const float2 *st = P.ops.empty() ? P.psi0 : P.phi;
+    const float2 *st = P.ops.empty() && !point_small(P) ? P.psi0 : P.phi;
     for (int vb = 0; vb < P.GH; ++vb) pitems[P.group].push_back(SweepHItem{(int)pi, vb, st, P.lam, P.partial});
     for (int k = 0; k < P.P; ++k) red.push_back(SweepRItem{(int)pi, 0, P.GH, P.P, k, 0, P.partial, P.res + 2 + k});
   }
@@ -653,8 +702,13 @@ int fock_sweep_create(const fock_sweep_point_t *pts, int npts, const fock_adapt_
   if (hipStreamSynchronize((hipStream_t)stream) != hipSuccess) return set_error(FOCK_ERR_HIP, "caller stream error");
   fock_sweep *sw = new fock_sweep();
   sw->opt = *opts;
-  if (hipStreamCreateWithFlags(&sw->s, hipStreamNonBlocking) != hipSuccess) {
-    delete sw;
+  bool ok = hipStreamCreateWithFlags(&sw->s, hipStreamNonBlocking) == hipSuccess &&
+            hipEventCreateWithFlags(&sw->fork, hipEventDisableTiming) == hipSuccess;
+  for (int b = 0; b < kSideStreams && ok; ++b)
+    ok = hipStreamCreateWithFlags(&sw->side[b], hipStreamNonBlocking) == hipSuccess &&
+         hipEventCreateWithFlags(&sw->join[b], hipEventDisableTiming) == hipSuccess;
+  if (!ok) {
+    fock_sweep_destroy(sw);
     return set_error(FOCK_ERR_HIP, "stream creation failed");
   }
   sw->pts.resize(npts);
@@ -1083,7 +1137,13 @@ int fock_sweep_autotune(fock_sweep_t *sw, const char *cache_path, int *best_grid
 
 int fock_sweep_destroy(fock_sweep_t *sw) {
   if (!sw) return FOCK_OK;
-  (void)hipStreamSynchronize(sw->s);
+  if (sw->s) (void)hipStreamSynchronize(sw->s);
+  for (int b = 0; b < kSideStreams; ++b) {
+    if (sw->side[b]) (void)hipStreamSynchronize(sw->side[b]);
+    if (sw->side[b]) (void)hipStreamDestroy(sw->side[b]);
+    if (sw->join[b]) (void)hipEventDestroy(sw->join[b]);
+  }
+  if (sw->fork) (void)hipEventDestroy(sw->fork);
   destroy_graph(sw);
   if (sw->items_d) (void)hipFree(sw->items_d);
   if (sw->runs_d) (void)hipFree(sw->runs_d);
