@@ -443,16 +443,20 @@ int fock_get_gate_variant(void);
 
 /* ------------------------------------------------------------------ gate fusion */
 
-/* Circuits evaluated by fock_energy_grad_adjoint and adapt_step run runs of
- * consecutive gates whose modes (with mode 0) fit one tile of d^s <= 4096
- * amplitudes as one pass: the tile is staged in LDS and the gates are applied
- * there one after another (forward), or the tiles of phi and lambda are staged
- * and the reverse steps of the run are taken there (adjoint sweep).  Same
- * operations as the per-gate kernels (same block arithmetic); gradient partials
- * are summed over other tiles, so results agree to FP32/FP64 rounding, not
- * bitwise.  d in {2, 4, 6, 8}; process-wide mode: FOCK_FUSE_OFF (the
- * default), FOCK_FUSE_FORWARD (forward circuit only) or FOCK_FUSE_ALL (forward
- * and adjoint sweep).  The batched sweep does not fuse. */
+/* Circuits on complex64 states (fock_energy_grad_adjoint, fock_adjoint_sweep,
+ * the ADAPT, HVA and sweep drivers) run in passes the library plans.  Small
+ * states (d <= 8, both states of the reverse sweep in the LDS of one workgroup:
+ * up to about 9,500 amplitudes; at most 256 gates) are evaluated whole in one
+ * launch.  On larger ones at d <= 8, gates whose modes fit one tile (mode 0 and
+ * two to twelve others, at most 8192 amplitudes) run as one pass: the tile is
+ * staged in LDS and the gates, or their reverse steps, are applied there one
+ * after another; a gate may move past others on disjoint modes, with which it
+ * commutes.  The rest runs gate by gate.  The paths agree to FP32/FP64 rounding,
+ * not bitwise.  Process-wide mode: FOCK_FUSE_OFF (the default): as above;
+ * FOCK_FUSE_FORWARD: no whole evaluations, fused runs in the forward circuit
+ * only; FOCK_FUSE_ALL: no whole evaluations, fused runs both ways (phi_work and
+ * lam_work then end as after fock_adjoint_sweep).  With the dense gate variant or
+ * a forward-state store the gates run one by one. */
 enum { FOCK_FUSE_OFF = 0, FOCK_FUSE_FORWARD = 1, FOCK_FUSE_ALL = 2 };
 int fock_set_gate_fusion(int mode);
 int fock_get_gate_fusion(void);
@@ -560,13 +564,15 @@ int fock_get_real_states(void);
  * with their gradient terms (Sec. IV.B), are applied there in order.  States
  * are the same bit for bit as gate by gate; gradient partials are summed per
  * tile, so gradients agree to FP32/FP64 rounding.  At most 8 gates per run.
+ * Fused or not, an evaluation first moves gates up to join a run where they
+ * commute with every gate they pass (disjoint modes).
  * Process-wide: FOCK_RFUSE_ON (default) or FOCK_RFUSE_OFF (gate by gate). */
 enum { FOCK_RFUSE_OFF = 0, FOCK_RFUSE_ON = 1 };
 int fock_set_real_fusion(int mode);
 int fock_get_real_fusion(void);
 
-/* The runs that an evaluation of ops[0..n) on real states would launch under
- * the current fusion mode (host only: no device work).  run_k0[r] is the first
+/* The runs of ops[0..n) on real states, in the given order, under the current
+ * fusion mode (host only: no device work).  run_k0[r] is the first
  * gate of run r (runs are consecutive and cover the circuit in order), run_a[r]
  * the lowest of its three tile modes, or -1 for a gate taken by the per-gate
  * kernels; *nruns receives the count.  ham->layout selects the geometry (full

@@ -41,10 +41,11 @@ SOURCES = [
     "sweep.cpp",
     "host_common.cpp",
     "api.cpp",
+    "gate_plan.cpp",
     "adapt.cpp",
     "hva.cpp",
     "bfgs.cpp",
-    "fuse_kernels.hip",
+    "tile_runs.hip",
     "gate1_kernels.hip",
     "f64_kernels.hip",
     "adapt64.cpp",
@@ -76,7 +77,7 @@ def _compile(src: str) -> str:
 
 # Sources with matrix-core (MFMA) instructions; their device assembly is checked
 # after compilation (see check_mfma_operands).
-MFMA_SOURCES = ["dense_gate.hip", "mlp_kernels.hip", "small_eval.hip"]
+MFMA_SOURCES = ["dense_gate.hip", "mlp_kernels.hip", "small_eval.hip", "tile_runs.hip"]
 
 _MFMA_RE = re.compile(r"v_mfma_\w+\s+([av])\[(\d+):(\d+)\],[^\n]*,\s*([av])\[(\d+):(\d+)\]\s*$", re.M)
 

@@ -160,6 +160,9 @@ Layout make_layout(uint32_t namp, int Lm, int d, int P, int n, int half) {
     Geometry g{Lm, d, namp};
     g.half = half;
     L.rs = std::max(L.G, gate_blocks_max(g));
+    int T = 1;  // tiles of a fused run
+    for (int r = fuse_modes(g); r > 0; --r) T *= d;
+    if (T > 1) L.rs = std::max(L.rs, (int)(namp / (uint32_t)T));
   }
   L.nmax = std::max(n, 1);
   L.pmax = std::min(std::max(P, 1), kMaxSlots);
@@ -341,109 +344,6 @@ int fetch_results(Ctx &c, int count, double *host) {
 // ---------------------------------------------------------------- gate fusion
 static std::atomic<int> g_fuse{FOCK_FUSE_OFF};
 
-bool fuse_supported(int d) { return d == 2 || d == 4 || d == 6 || d == 8; }
-
-int fuse_max_modes(int L, int d) {
-  int s = 0;
-  for (long t = d; t <= 4096 && s < kMaxFuseModes && s < L; t *= d) ++s;
-  return s;
-}
-
-// Greedy grouping: a group grows while the union of its gates' modes and mode
-// 0 fits smax modes; its tile is that union filled up with the lowest other
-// modes.  Kept when it has at least two gates and its tile holds mode 1 (rows
-// of d^2 contiguous amplitudes) or at least three gates; groups whose tile
-// count exceeds the partial-row stride are not fused.
-static void plan_gate_groups(const Ctx &c, const fock_op_t *ops, int n, std::vector<GateGroup> *out) {
-  out->clear();
-  const int L = c.g.L, d = c.g.d, smax = fuse_max_modes(L, d);
-  const bool on = !c.g.half && g_fuse.load() != FOCK_FUSE_OFF && fuse_supported(d) && smax >= 2;
-  int k = 0;
-  while (k < n) {
-    GateGroup gr;
-    gr.k0 = k;
-    gr.k1 = k + 1;
-    gr.s = 0;
-    // consecutive single-mode phase gates commute: one diagonal pass
-    const int k1 = diag_run_end(ops, n, k);
-    if (k1 > k) {
-      gr.k1 = k1;
-      gr.diag = true;
-      out->push_back(gr);
-      k = k1;
-      continue;
-    }
-    if (on) {
-      unsigned mask = 1u;  // modes in the union (mode 0 always)
-      auto modes = [&](const fock_op_t &o) { return is_single_mode(o.type) ? (1u << o.i) : ((1u << o.i) | (1u << o.j)); };
-      mask |= modes(ops[k]);
-      int k1 = k + 1;
-      // squeezer gates are not fused: they run alone on the per-gate kernels
-      while (!is_squeeze(ops[k].type) && k1 < n && k1 - k < kMaxFuseGates && !is_squeeze(ops[k1].type)) {
-        const unsigned nm = mask | modes(ops[k1]);
-        if (__builtin_popcount(nm) > smax) break;
-        mask = nm;
-        ++k1;
-      }
-      for (int r = 0; r < L && __builtin_popcount(mask) < smax; ++r) mask |= 1u << r;
-      const int size = k1 - k;
-      const int s = __builtin_popcount(mask);
-      long ntile = 1;
-      for (int r = 0; r < L - s; ++r) ntile *= d;
-      if (size >= 2 && ((mask & 2u) || size >= 3) && ntile <= c.L.rs) {
-        gr.k1 = k1;
-        gr.s = 0;
-        for (int r = 0; r < L; ++r)
-          if (mask & (1u << r)) gr.m[gr.s++] = r;
-      }
-    }
-    out->push_back(gr);
-    k = gr.k1;
-  }
-}
-
-static FuseArgs make_fuse_args(const Ctx &c, const GateGroup &gr, const fock_op_t *ops) {
-  FuseArgs a;
-  memset(&a, 0, sizeof(a));
-  const int L = c.g.L, d = c.g.d;
-  std::vector<uint32_t> pw(L, 1);
-  for (int r = 1; r < L; ++r) pw[r] = pw[r - 1] * (uint32_t)d;
-  a.s = gr.s;
-  int pos[kMaxL];
-  for (int r = 0; r < L; ++r) pos[r] = -1;
-  for (int k = 0; k < gr.s; ++k) {
-    a.tstride[k] = pw[gr.m[k]];
-    pos[gr.m[k]] = k;
-  }
-  a.nc = 0;
-  a.ntile = 1;
-  for (int r = 0; r < L; ++r)
-    if (pos[r] < 0) {
-      a.cstride[a.nc++] = pw[r];
-      a.ntile *= d;
-    }
-  int off = 0;
-  for (int sb = 0; sb <= 2 * d - 2; ++sb) {
-    a.boff[sb] = off;
-    const int b = blk_hi(KIND_SUM, d, sb) - blk_lo(KIND_SUM, d, sb) + 1;
-    off += b * b;
-  }
-  for (int t = 0; t < kTwoModeTypes; ++t) a.A[t] = c.T.A[t];
-  a.ng = gr.k1 - gr.k0;
-  for (int q = 0; q < a.ng; ++q) {
-    const int k = gr.k0 + q;
-    const fock_op_t &o = ops[k];
-    FuseGate &g = a.g[q];
-    g.type = o.type;
-    g.kind = is_single_mode(o.type) ? 0 : gate_kind(o.type);
-    g.ki = pos[o.i];
-    g.kj = is_single_mode(o.type) ? -1 : pos[o.j];
-    g.u_off = k * gate_stride(d);
-    g.k = k;
-  }
-  return a;
-}
-
 // Stage the gate tables of a circuit (with the per-gate partial counts of the
 // reverse step, which depend on how the gates are grouped) and plan its groups.
 // Gates the parity-halved layout runs: two-mode HR..PI generators (they keep
@@ -453,6 +353,12 @@ bool half_layout_op_ok(const fock_op_t &op, int L) {
   return op.j < L - 1 || op.i == L - 2;
 }
 
+// Fused runs are on unless the caller asks for a path that works gate by gate
+// (dense gates, kept forward states); FOCK_FUSE_FORWARD keeps the reverse sweep
+// gate by gate.
+static bool fused_runs(const Ctx &c) { return !c.store && gate_variant() == FOCK_GATE_BLOCK; }
+static bool reverse_fused() { return g_fuse.load() != FOCK_FUSE_FORWARD; }
+
 static int stage_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int n, std::vector<GateGroup> *groups) {
   if (n > c.L.nmax) return set_error(FOCK_ERR_SIZE, "circuit of %d gates exceeds the workspace's %d", n, c.L.nmax);
   if (c.g.half)
@@ -460,16 +366,13 @@ static int stage_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int 
       if (!half_layout_op_ok(ops[k], c.g.L))
         return set_error(FOCK_ERR_UNSUPPORTED, "gate %d (type %d on (%d,%d)) in the parity-halved layout", k,
                          ops[k].type, ops[k].i, ops[k].j);
-  plan_gate_groups(c, ops, n, groups);
+  *groups = plan_gate_groups(c.g, ops, n, fused_runs(c));
   if (n == 0) return FOCK_OK;
-  const bool fuse_rev = g_fuse.load() == FOCK_FUSE_ALL;
   std::vector<int> nblk(n, 0);
-  for (const GateGroup &gr : *groups)
-    if (gr.s > 0 && fuse_rev) {
-      int nt = 1;
-      for (int r = 0; r < c.g.L - gr.s; ++r) nt *= c.g.d;
-      for (int k = gr.k0; k < gr.k1; ++k) nblk[k] = nt;
-    }
+  if (reverse_fused())
+    for (const GateGroup &gr : *groups)
+      if (gr.s > 0)
+        for (int k : gr.k) nblk[k] = fuse_tiles(c.g, gr);
   return stage_gates(c, ops, theta, n, nblk.data());
 }
 
@@ -515,7 +418,6 @@ static int reverse_sweep(Ctx &c, const fock_op_t *ops, int n, const std::vector<
                          float2 *lam, double *res) {
   if (n == 0) return FOCK_OK;
   int rc = FOCK_OK;
-  const bool fuse_rev = g_fuse.load() == FOCK_FUSE_ALL;
   const float2 *utab = (const float2 *)(c.ws + c.L.utab);
   double *part = (double *)(c.ws + c.L.partial);
   const int stride = gate_stride(c.g.d);
@@ -523,18 +425,20 @@ static int reverse_sweep(Ctx &c, const fock_op_t *ops, int n, const std::vector<
     const GateGroup &gr = groups[gi];
     if (gr.diag) {
       ProfScope ps(FOCK_K_DIAG, c.s, 32.0 * c.g.n_amp);
-      rc = launch_diag_run_adj(c.g, diag_run_params(c.g, ops, gr.k0, gr.k1), utab + (size_t)gr.k0 * stride, phi, lam,
-                               part + (size_t)gr.k0 * c.L.rs, c.L.rs, c.s);
+      rc = launch_diag_run_adj(c.g, diag_run_params(c.g, ops, gr.k.front(), gr.k.back() + 1),
+                               utab + (size_t)gr.k.front() * stride, phi, lam, part + (size_t)gr.k.front() * c.L.rs,
+                               c.L.rs, c.s);
       if (rc) return rc;
       continue;
     }
-    if (gr.s > 0 && fuse_rev) {
+    if (gr.s > 0 && reverse_fused()) {
       ProfScope ps(FOCK_K_ADJ, c.s, 32.0 * c.g.n_amp);
-      rc = launch_fuse_adj(c.g.d, make_fuse_args(c, gr, ops), phi, lam, utab, part, c.L.rs, c.s);
+      rc = launch_fuse_adj(make_fuse_args(c.g, c.T, gr, ops), phi, lam, utab, part, c.L.rs, c.s);
       if (rc) return rc;
       continue;
     }
-    for (int k = gr.k1 - 1; k >= gr.k0; --k) {
+    for (auto it = gr.k.rbegin(); it != gr.k.rend(); ++it) {
+      const int k = *it;
       const fock_op_t &op = ops[k];
       const float2 *U = utab + (size_t)k * stride;
       double *pk = part + (size_t)k * c.L.rs;
@@ -567,17 +471,17 @@ static int forward_circuit(Ctx &c, const fock_op_t *ops, int n, const std::vecto
   if (n == 0)
     FOCK_HIP(hipMemcpyAsync(phi, psi0, sizeof(float2) * (size_t)c.g.n_amp, hipMemcpyDeviceToDevice, c.s));
   for (const GateGroup &gr : groups) {
-    const float2 *src = gr.k0 == 0 ? (const float2 *)psi0 : phi;
+    const float2 *src = &gr == &groups.front() ? (const float2 *)psi0 : phi;
     int rc;
     if (gr.diag) {
       ProfScope ps(FOCK_K_DIAG, c.s, 16.0 * c.g.n_amp);
-      rc = launch_diag_run(c.g, diag_run_params(c.g, ops, gr.k0, gr.k1), false,
-                           utab + (size_t)gr.k0 * gate_stride(c.g.d), src, phi, c.s);
+      rc = launch_diag_run(c.g, diag_run_params(c.g, ops, gr.k.front(), gr.k.back() + 1), false,
+                           utab + (size_t)gr.k.front() * gate_stride(c.g.d), src, phi, c.s);
     } else if (gr.s == 0) {
-      rc = forward_gate(c, ops[gr.k0], gr.k0, false, src, phi);
+      rc = forward_gate(c, ops[gr.k.front()], gr.k.front(), false, src, phi);
     } else {
       ProfScope ps(FOCK_K_GATE, c.s, 16.0 * c.g.n_amp);
-      rc = launch_fuse_fwd(c.g.d, make_fuse_args(c, gr, ops), src, phi, utab, c.s);
+      rc = launch_fuse_fwd(make_fuse_args(c.g, c.T, gr, ops), src, phi, utab, c.s);
     }
     if (rc) return rc;
   }

@@ -1,0 +1,133 @@
+// How a circuit on complex64 states is cut into passes: runs of single-mode
+// phase gates (one diagonal pass), fused runs of gates inside one tile
+// (tile_runs.hip) and single gates on their own kernels.  Host only; the
+// single-point drivers and the batched sweep plan with this one function.
+#include <algorithm>
+#include <cstring>
+
+#include "fuse_internal.h"
+
+namespace fock {
+
+namespace {
+
+// A gate, or a run of single-mode phase gates, to be placed as a whole.
+struct Item {
+  int k0, k1;
+  unsigned modes;
+  bool fusable;
+};
+
+unsigned mode_mask(const fock_op_t &o) { return (1u << o.i) | (o.j >= 0 ? 1u << o.j : 0u); }
+
+}  // namespace
+
+// Modes of a fused run's tile: as many as the LDS of one workgroup holds (both
+// states of the reverse sweep, kTileMaxAmps each) while 128 tiles are left to
+// keep the chip busy; a state too small for that takes up to four modes while 32
+// tiles are left.  Measured, an evaluation in us: 8^6, 4 modes (64 tiles) 308, 3
+// (512) 318; 6^6, 4 modes (36) 267, 3 (216) 281; 4^8, 4 modes (256) 237, 5 (64)
+// 224, 6 (16) 299; 5^8, 4 modes (625) 247, 5 (125) 338.
+int fuse_modes(const Geometry &g) {
+  const int Lf = g.half ? g.L - 1 : g.L;
+  int s128 = 0, s32 = 0, s = 1;
+  for (long T = g.d; s <= Lf && s <= kMaxFuseModes && T <= kTileMaxAmps; T *= g.d, ++s) {
+    if ((long)g.n_amp / T >= 128) s128 = s;
+    if ((long)g.n_amp / T >= 32 && s <= 4) s32 = s;
+  }
+  return std::max(s128, s32);
+}
+
+std::vector<GateGroup> plan_gate_groups(const Geometry &g, const fock_op_t *ops, int n, bool fuse) {
+  const int Lf = g.half ? g.L - 1 : g.L, smax = fuse_modes(g);
+  const bool on = fuse && fuse_supported(g.d) && smax >= 3;
+  std::vector<Item> items;
+  for (int k = 0; k < n;) {
+    Item it{k, std::max(diag_run_end(ops, n, k), k + 1), 0u, false};
+    for (int q = it.k0; q < it.k1; ++q) it.modes |= mode_mask(ops[q]);
+    it.fusable = on && it.k1 == it.k0 + 1 && !is_squeeze(ops[k].type) && !(it.modes >> Lf);
+    items.push_back(it);
+    k = it.k1;
+  }
+  std::vector<GateGroup> out;
+  std::vector<char> done(items.size(), 0);
+  for (size_t a = 0; a < items.size(); ++a) {
+    if (done[a]) continue;
+    GateGroup gr;
+    std::vector<size_t> take{a};
+    unsigned mask = 1u | items[a].modes;  // mode 0 always, so that rows stay contiguous
+    if (items[a].fusable && __builtin_popcount(mask) <= smax) {
+      // Later gates join while the union of modes fits the tile; one whose modes
+      // meet no gate left behind commutes with all of them and may move up.
+      unsigned behind = 0u;
+      for (size_t b = a + 1; b < items.size() && take.size() < kMaxFuseGates && ~behind & ((1u << g.L) - 1); ++b) {
+        if (done[b]) continue;
+        const unsigned u = mask | items[b].modes;
+        if (items[b].fusable && !(items[b].modes & behind) && __builtin_popcount(u) <= smax) {
+          mask = u;
+          take.push_back(b);
+        } else {
+          behind |= items[b].modes;
+        }
+      }
+      if (take.size() > 1)  // the tile's other modes: the lowest
+        for (int r = 0; r < Lf && __builtin_popcount(mask) < smax; ++r) mask |= 1u << r;
+    }
+    for (size_t b : take) {
+      done[b] = 1;
+      for (int k = items[b].k0; k < items[b].k1; ++k) gr.k.push_back(k);
+    }
+    gr.diag = take.size() == 1 && gr.k.size() > 1;
+    if (take.size() > 1)
+      for (int r = 0; r < Lf; ++r)
+        if (mask & (1u << r)) gr.m[gr.s++] = r;
+    out.push_back(gr);
+  }
+  return out;
+}
+
+int fuse_tiles(const Geometry &g, const GateGroup &gr) {
+  int T = 1;
+  for (int r = 0; r < gr.s; ++r) T *= g.d;
+  return (int)(g.n_amp / (uint32_t)T);
+}
+
+FuseArgs make_fuse_args(const Geometry &g, const EigTables &T, const GateGroup &gr, const fock_op_t *ops) {
+  FuseArgs a;
+  memset(&a, 0, sizeof(a));
+  const int L = g.L, d = g.d;
+  std::vector<uint32_t> pw(L, 1);
+  for (int r = 1; r < L; ++r) pw[r] = pw[r - 1] * (uint32_t)d;
+  a.d = d;
+  a.dd = make_fastdiv((uint32_t)d);
+  a.s = gr.s;
+  a.T = 1;
+  std::vector<int> pos(L, -1);
+  for (int k = 0; k < gr.s; ++k) {
+    a.tstride[k] = pw[gr.m[k]];
+    pos[gr.m[k]] = k;
+    a.T *= d;
+  }
+  a.ntile = fuse_tiles(g, gr);
+  for (int r = 0; r < L; ++r)
+    if (pos[r] < 0) a.cstride[a.nc++] = pw[r];
+  for (int t = 0; t < kTwoModeTypes; ++t) a.A[t] = T.A[t];
+  a.ng = (int)gr.k.size();
+  for (int q = 0; q < a.ng; ++q) {
+    const int k = gr.k[q];
+    const fock_op_t &o = ops[k];
+    FuseGate &f = a.g[q];
+    f.type = o.type;
+    f.ki = pos[o.i];
+    f.kj = o.j < 0 ? -1 : pos[o.j];
+    f.u_off = k * gate_stride(d);
+    f.k = k;
+    int si = 1, sj = 1;
+    for (int e = 0; e < f.ki; ++e) si *= d;
+    for (int e = 0; e < (f.kj < 0 ? f.ki + 1 : f.kj); ++e) sj *= d;
+    f.p = tile_pair(si, sj, d);
+  }
+  return a;
+}
+
+}  // namespace fock

@@ -28,8 +28,6 @@ namespace fock {
 
 namespace {
 
-constexpr int kFlush = 32;  // gates between two flushes of the per-wave sums
-
 // A gate's description, decoded once per launch (p.sj = 0: single mode).
 struct SGate {
   int type;
@@ -37,7 +35,7 @@ struct SGate {
 };
 
 struct SmallShared {
-  double part[kFlush][kTileWaves];
+  double part[kTileSums][kTileWaves];
   double en[2][kTileWaves];
   float4 w[64];
   SGate gate[kSmallGates];
@@ -235,8 +233,8 @@ __global__ __launch_bounds__(64 * kTileWaves) void k_small_eval(SmallItem one, c
     const float2 *U = tab + (k - k0) * us;
     if (pair > 0) {
       if (busy)
-        tile_gate<P2>(phi, g.p, tl, tile_step<P2>(g.p, tl, gate_kind_dev(type), nfib, d), tile_mat<false>(U, tl), nfib,
-                      d);
+        tile_gate<P2>(phi, tl, tile_step<P2>(g.p, tl, gate_kind_dev(type)), tile_mat<false>(tile_raw<false>(U, tl), tl), nfib,
+                      [&](int f) { return 8 * tile_pos<P2>(tile_fibre(f, g.p, d)); });
     } else if (gate_is_phase(type)) {
       small_phase<false, P2>(phi, lam, U, g, N, d);
     } else {
@@ -265,7 +263,8 @@ __global__ __launch_bounds__(64 * kTileWaves) void k_small_eval(SmallItem one, c
     }
     return;
   }
-  // reverse; the per-wave sums of up to kFlush gates are added up together
+  // reverse; the sums of up to kTileSums gates are added up together
+  f64x4 sums = {0.0, 0.0, 0.0, 0.0};
   int done = 0;
   for (int k = n - 1; k >= 0; --k) {
     const SGate g = sh.gate[k];
@@ -275,26 +274,28 @@ __global__ __launch_bounds__(64 * kTileWaves) void k_small_eval(SmallItem one, c
     float acc = 0.f;
     if (pair > 0) {
       if (busy)
-        acc = tile_gate_adj<P2>(phi, lam, g.p, tl, tile_step<P2>(g.p, tl, gate_kind_dev(type), nfib, d),
-                                tile_mat<true>(U, tl), tile_mat<false>(gen + table_slot(type) * us, tl), nfib, d);
+        acc = tile_gate_adj<P2>(phi, lam, tl, tile_step<P2>(g.p, tl, gate_kind_dev(type)), tile_mat<true>(tile_raw<true>(U, tl), tl),
+                                tile_gen_raw(gen + table_slot(type) * us, tl, tile_gen_kind(type)), tile_gen_kind(type), nfib,
+                                [&](int f) { return 8 * tile_pos<P2>(tile_fibre(f, g.p, d)); });
     } else if (gate_is_phase(type)) {
       acc = small_phase<true, P2>(phi, lam, U, g, N, d);
     } else {
       acc = small_squeeze<true, P2>(phi, lam, U, T.A1[type == FOCK_SR ? 0 : 1], g, N, d);
     }
-    const double sw = busy || pair == 0 ? wave_total_d((double)acc) : 0.0;
-    if (lane == 63) sh.part[done][wave] = sw;
+    if (busy || pair == 0) tile_sums_add(sums, done, acc);
     ++done;
-    __syncthreads();
-    if (done == kFlush || k == 0) {
+    if (done == kTileSums || k == 0) {  // a full accumulator
+      tile_sums_flush(sums, sh.part);
+      sums = f64x4{0.0, 0.0, 0.0, 0.0};
+      __syncthreads();
       if ((int)threadIdx.x < done) {
         double s = 0.0;
         for (int w = 0; w < nw; ++w) s += sh.part[threadIdx.x][w];
         it.res[2 + k + done - 1 - threadIdx.x] = s;
       }
       done = 0;
-      __syncthreads();
     }
+    __syncthreads();
   }
 }
 

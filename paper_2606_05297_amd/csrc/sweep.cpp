@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "bfgs.h"
+#include "fuse_internal.h"
 #include "pipeline.h"
 #include "sweep_internal.h"
 
@@ -110,45 +111,56 @@ double *pin_res(fock_sweep *sw) {
 }
 
 // ---------------------------------------------------------------- item lists
+// A list that goes to the device with the others in one blob, at offset off.
+template <class T>
+struct DevList {
+  std::vector<T> v;
+  size_t off = 0;
+};
+
+// Fused runs of one layer in one launch (runs of one workgroup size).
+struct RunBatch {
+  int waves = 0;
+  DevList<SweepRun> runs;
+  DevList<int2> tiles;  // (run, tile) of every workgroup
+};
+
+// The passes of the points of one cutoff, in order: layers forward (items of two
+// classes and fused runs), H psi, energy sums, layers in reverse, gradient sums.
+// A layer holds one pass of every point.
+struct GroupLists {
+  struct Layer {
+    DevList<SweepItem> fwd[2], rev[2];  // by item class
+    std::vector<RunBatch> runs;
+  };
+  std::vector<Layer> layers;
+  DevList<SweepHItem> h;
+  DevList<SweepRItem> en, red;
+};
+
 struct Lists {
-  std::vector<std::vector<std::vector<SweepItem>>> fwd, rev;  // [k][2 * group + item class]
-  std::vector<std::vector<SweepHItem>> h;                     // [group]
-  std::vector<std::vector<SmallItem>> small;                  // points evaluated by one workgroup each, per launch
-  std::vector<SweepRItem> red;
+  std::vector<GroupLists> g;                // [group]
+  std::vector<DevList<SmallItem>> small;    // points evaluated by one workgroup each, per launch
+  DevList<HamArgs> hams;                    // [point]
 };
 
 // Whether a point's circuit is evaluated whole by one workgroup (the rule of
 // the single-point path).
 bool point_small(const SPoint &P) { return small_eval_ok(P.g.L, P.g.d, P.g.n_amp, (int)P.ops.size()); }
 
-// A point's gate groups: [k0, k1) runs of phase gates (diag_run_end) or single gates.
-void point_groups(const std::vector<fock_op_t> &ops, std::vector<std::pair<int, int>> *gr) {
-  gr->clear();
-  const int n = (int)ops.size();
-  for (int k = 0; k < n;) {
-    const int e = diag_run_end(ops.data(), n, k);
-    const int k1 = e > k ? e : k + 1;
-    gr->push_back({k, k1});
-    k = k1;
-  }
-}
-
-// Gate layers are the points' gate groups: layer l holds group l of every
-// point, so a run of phase gates takes one layer and one pass.
+// The passes of a point are those of the single-point driver (plan_gate_groups).
 int build_lists(fock_sweep *sw, const std::vector<char> &sel, bool grad, Lists *Ls) {
   const size_t npt = sw->pts.size();
-  std::vector<std::vector<std::pair<int, int>>> groups(npt);
+  std::vector<std::vector<GateGroup>> groups(npt);
   std::vector<DiagRun> runs;
   std::vector<size_t> run_base(npt, 0);
-  int maxn = 0;
   for (size_t p = 0; p < npt; ++p) {
     const SPoint &P = sw->pts[p];
     if (point_small(P)) continue;
-    point_groups(P.ops, &groups[p]);
+    groups[p] = plan_gate_groups(P.g, P.ops.data(), (int)P.ops.size(), true);
     run_base[p] = runs.size();
     for (auto &g : groups[p])
-      if (g.second - g.first > 1) runs.push_back(diag_run_params(P.g, P.ops.data(), g.first, g.second));
-    if (sel[p]) maxn = std::max(maxn, (int)groups[p].size());
+      if (g.diag) runs.push_back(diag_run_params(P.g, P.ops.data(), g.k.front(), g.k.back() + 1));
   }
   if (runs.size() > sw->runs_cap) {
     if (sw->runs_d) FOCK_HIP(hipFree(sw->runs_d));
@@ -159,16 +171,14 @@ int build_lists(fock_sweep *sw, const std::vector<char> &sel, bool grad, Lists *
   }
   if (!runs.empty())
     FOCK_HIP(hipMemcpy(sw->runs_d, runs.data(), sizeof(DiagRun) * runs.size(), hipMemcpyHostToDevice));
-  const int NG = (int)sw->groups.size();
-  Ls->fwd.assign(maxn, std::vector<std::vector<SweepItem>>(2 * NG));
-  Ls->rev.assign(maxn, std::vector<std::vector<SweepItem>>(2 * NG));
-  Ls->h.assign(NG, {});
-  Ls->small.clear();
-  Ls->red.clear();
+  *Ls = Lists();
+  Ls->g.resize(sw->groups.size());
+  for (auto &P : sw->pts) Ls->hams.v.push_back(P.h);
   for (size_t pi = 0; pi < npt; ++pi) {
     if (!sel[pi]) continue;
     SPoint &P = sw->pts[pi];
     const DGroup &G = sw->groups[P.group];
+    GroupLists &GL = Ls->g[P.group];
     const int stride = gate_stride(P.g.d);
     const int n = (int)P.ops.size();
     if (point_small(P)) {
@@ -181,22 +191,50 @@ int build_lists(fock_sweep *sw, const std::vector<char> &sel, bool grad, Lists *
       it.recs = G.recs + P.gate_base;
       it.res = P.res;
       // one launch per cutoff and workgroup size
-      auto same = [&](const std::vector<SmallItem> &v) { return v[0].d == it.d && small_waves(v[0]) == small_waves(it); };
+      auto same = [&](const DevList<SmallItem> &l) {
+        return l.v[0].d == it.d && small_waves(l.v[0]) == small_waves(it);
+      };
       auto at = std::find_if(Ls->small.begin(), Ls->small.end(), same);
-      if (at == Ls->small.end()) Ls->small.push_back({it});
-      else at->push_back(it);
+      if (at == Ls->small.end()) at = Ls->small.insert(at, DevList<SmallItem>());
+      at->v.push_back(it);
       continue;
     }
+    const float2 *utab = G.utab + (size_t)P.gate_base * stride;
+    std::vector<int> nblk(n, 0);  // partials of each gate's reverse step
     size_t ri = run_base[pi];
+    if (GL.layers.size() < groups[pi].size()) GL.layers.resize(groups[pi].size());
     for (size_t l = 0; l < groups[pi].size(); ++l) {
-      const int k = groups[pi][l].first, k1 = groups[pi][l].second;
+      const GateGroup &gr = groups[pi][l];
+      GroupLists::Layer &Ly = GL.layers[l];
+      const int k = gr.k.front();
       const fock_op_t &op = P.ops[k];
+      if (gr.s > 0) {
+        SweepRun r;
+        r.a = make_fuse_args(P.g, G.T, gr, P.ops.data());
+        r.p = (int)pi;
+        r.rs = P.rs;
+        r.src = l == 0 ? P.psi0 : P.phi;
+        r.phi = P.phi;
+        r.lam = P.lam;
+        r.utab = utab;
+        r.partial = P.partial;
+        for (int q : gr.k) nblk[q] = r.a.ntile;
+        const int waves = fuse_waves(r.a.d, r.a.T);
+        auto at = std::find_if(Ly.runs.begin(), Ly.runs.end(), [&](const RunBatch &b) { return b.waves == waves; });
+        if (at == Ly.runs.end()) {
+          at = Ly.runs.insert(at, RunBatch());
+          at->waves = waves;
+        }
+        for (int t = 0; t < r.a.ntile; ++t) at->tiles.v.push_back(make_int2((int)at->runs.v.size(), t));
+        at->runs.v.push_back(r);
+        continue;
+      }
       SweepItem it;
       memset(&it, 0, sizeof(it));
       it.p = (int)pi;
-      it.U = G.utab + (size_t)(P.gate_base + k) * stride;
+      it.U = utab + (size_t)k * stride;
       int nb;
-      if (k1 - k > 1) {
+      if (gr.diag) {
         it.variant = 3;
         it.kind = 0;
         it.rs = P.rs;
@@ -214,35 +252,32 @@ int build_lists(fock_sweep *sw, const std::vector<char> &sel, bool grad, Lists *
         it.A = G.T.A[table_slot(op.type)];
         nb = sweep_gate_blocks(P.g.d, (int)P.g.n_amp, op.i);
       }
+      for (int q : gr.k) nblk[q] = nb;
       const bool m0 = it.variant == 1 || it.variant == 4;
-      const int li = 2 * P.group + (m0 && sweep_split_classes(P.g.d) ? 1 : 0);  // item class list
+      const int cls = m0 && sweep_split_classes(P.g.d) ? 1 : 0;
       for (int vb = 0; vb < nb; ++vb) {
         SweepItem f = it;
         f.vb = vb;
-        f.src = k == 0 ? P.psi0 : P.phi;
+        f.src = l == 0 ? P.psi0 : P.phi;
         f.dst = P.phi;
-        Ls->fwd[l][li].push_back(f);
+        Ly.fwd[cls].v.push_back(f);
         if (grad) {
           SweepItem r = it;
           r.vb = vb;
           r.dst = P.phi;
           r.lam = P.lam;
           r.partial = P.partial + (size_t)k * P.rs;
-          Ls->rev[l][li].push_back(r);
+          Ly.rev[cls].v.push_back(r);
         }
       }
     }
     if (grad)
-      for (int k = 0; k < n; ++k) {
-        const fock_op_t &op = P.ops[k];
-        const int nb = is_single_mode(op.type) ? diag_blocks_count(P.g)
-                                               : sweep_gate_blocks(P.g.d, (int)P.g.n_amp, op.i);
-        Ls->red.push_back(SweepRItem{(int)pi, 1, nb, 0, k, P.rs, P.partial, P.res + 2 + k});
-      }
+      for (int k = 0; k < n; ++k)
+        GL.red.v.push_back(SweepRItem{(int)pi, 1, nblk[k], 0, k, P.rs, P.partial, P.res + 2 + k});
     const float2 *st = n > 0 ? P.phi : P.psi0;
-    for (int vb = 0; vb < P.GH; ++vb) Ls->h[P.group].push_back(SweepHItem{(int)pi, vb, st, P.lam, P.partial});
+    for (int vb = 0; vb < P.GH; ++vb) GL.h.v.push_back(SweepHItem{(int)pi, vb, st, P.lam, P.partial});
+    for (int c = 0; c < 2; ++c) GL.en.v.push_back(SweepRItem{(int)pi, 0, P.GH, 2, c, 0, P.partial, P.res + c});
   }
-  // energy / norm reductions run before the reverse sweep reuses the partials
   return FOCK_OK;
 }
 
@@ -285,11 +320,12 @@ int upload_recs(fock_sweep *sw) {
 }
 
 // Enqueue one evaluation round (forward, H psi, optional reverse sweep,
-// reductions) of the points in the current lists.
-int enqueue_eval(fock_sweep *sw, const Lists &Ls, const std::vector<size_t> &offs, bool grad, bool upload) {
+// reductions) of the points in the current lists.  The points of each cutoff
+// and each launch of small points are chains of their own; they run side by
+// side on streams forked from s and joined to it.
+int enqueue_eval(fock_sweep *sw, const Lists &Ls, bool grad, bool upload) {
   hipStream_t s = sw->s;
   char *base = (char *)sw->items_d;
-  size_t oi = 0;
   if (upload) {
     FOCK_HIP(hipMemcpyAsync(sw->up_d, pin_up(sw), sizeof(double) * sw->n_up, hipMemcpyHostToDevice, s));
     FOCK_HIP(hipMemcpyAsync(sw->active_d, pin_active(sw), sizeof(int) * sw->pts.size(), hipMemcpyHostToDevice, s));
@@ -298,89 +334,90 @@ int enqueue_eval(fock_sweep *sw, const Lists &Ls, const std::vector<size_t> &off
       if (rc) return rc;
     }
   }
-  const int NG = (int)sw->groups.size();
-  // Whole evaluations of small points run on side streams beside the layers of
-  // the others: they keep one workgroup each busy for as long as many layers.
-  const int nside = Ls.fwd.empty() ? 0 : (int)std::min<size_t>(Ls.small.size(), kSideStreams);
+  int chains = (int)Ls.small.size();
+  for (const GroupLists &GL : Ls.g) chains += !GL.h.v.empty();
+  const int nside = chains > 1 ? std::min(chains - 1, kSideStreams) : 0;  // the first chain stays on s
   if (nside > 0) FOCK_HIP(hipEventRecord(sw->fork, s));
   for (int b = 0; b < nside; ++b) FOCK_HIP(hipStreamWaitEvent(sw->side[b], sw->fork, 0));
-  for (size_t b = 0; b < Ls.small.size(); ++b) {
-    const auto &v = Ls.small[b];
+  int chain = 0;
+  auto next_stream = [&]() {
+    const int c = chain++ % (nside + 1);
+    return c == 0 ? s : sw->side[c - 1];
+  };
+  for (size_t gi = 0; gi < Ls.g.size(); ++gi) {
+    const GroupLists &GL = Ls.g[gi];
+    if (GL.h.v.empty()) continue;
+    const int d = sw->groups[gi].d;
+    hipStream_t cs = next_stream();
+    int rc;
+    auto layer = [&](const GroupLists::Layer &Ly, bool rev) -> int {
+      int r = FOCK_OK;
+      for (int c = 0; c < 2 && !r; ++c) {
+        const DevList<SweepItem> &l = rev ? Ly.rev[c] : Ly.fwd[c];
+        const SweepItem *it = (const SweepItem *)(base + l.off);
+        r = rev ? sweep_launch_adj(d, c, it, (int)l.v.size(), sw->active_d, sw->grid, cs)
+                : sweep_launch_gate(d, c, it, (int)l.v.size(), sw->active_d, sw->grid, cs);
+      }
+      for (size_t b = 0; b < Ly.runs.size() && !r; ++b) {
+        const RunBatch &rb = Ly.runs[b];
+        size_t lds = 0;
+        for (const SweepRun &x : rb.runs.v) lds = std::max(lds, fuse_lds(x.a, rev));
+        r = sweep_launch_runs(d, rev, (const SweepRun *)(base + rb.runs.off), (const int2 *)(base + rb.tiles.off),
+                              (int)rb.tiles.v.size(), rb.waves, lds, sw->active_d, cs);
+      }
+      return r;
+    };
+    for (const auto &Ly : GL.layers)
+      if ((rc = layer(Ly, false))) return rc;
+    if ((rc = sweep_launch_h(d, (const SweepHItem *)(base + GL.h.off), (int)GL.h.v.size(),
+                             (const HamArgs *)(base + Ls.hams.off), sw->active_d, sw->grid, cs)))
+      return rc;
+    // energy and norm, before the reverse sweep reuses the partials
+    if ((rc = sweep_launch_reduce((const SweepRItem *)(base + GL.en.off), (int)GL.en.v.size(), sw->active_d, sw->grid,
+                                  cs)))
+      return rc;
+    if (!grad) continue;
+    for (auto it = GL.layers.rbegin(); it != GL.layers.rend(); ++it)
+      if ((rc = layer(*it, true))) return rc;
+    if ((rc = sweep_launch_reduce((const SweepRItem *)(base + GL.red.off), (int)GL.red.v.size(), sw->active_d,
+                                  sw->grid, cs)))
+      return rc;
+  }
+  for (const DevList<SmallItem> &l : Ls.small) {
     size_t lds = 0;
-    for (const SmallItem &it : v) lds = std::max(lds, small_lds_bytes(it));
-    const DGroup &G = sw->groups[sw->pts[v[0].point].group];
-    int rc = launch_small_eval(v[0], (const SmallItem *)(base + offs[oi++]), (int)v.size(), lds, small_waves(v[0]),
-                               G.T, sw->active_d, nside > 0 ? sw->side[b % nside] : s);
+    for (const SmallItem &it : l.v) lds = std::max(lds, small_lds_bytes(it));
+    const DGroup &G = sw->groups[sw->pts[l.v[0].point].group];
+    int rc = launch_small_eval(l.v[0], (const SmallItem *)(base + l.off), (int)l.v.size(), lds, small_waves(l.v[0]),
+                               G.T, sw->active_d, next_stream());
     if (rc) return rc;
   }
   for (int b = 0; b < nside; ++b) FOCK_HIP(hipEventRecord(sw->join[b], sw->side[b]));
-  for (size_t k = 0; k < Ls.fwd.size(); ++k)
-    for (int li = 0; li < 2 * NG; ++li) {
-      const auto &v = Ls.fwd[k][li];
-      int rc = sweep_launch_gate(sw->groups[li / 2].d, li % 2, (const SweepItem *)(base + offs[oi++]), (int)v.size(),
-                                 sw->active_d, sw->grid, s);
-      if (rc) return rc;
-    }
-  for (int gi = 0; gi < NG; ++gi) {
-    const auto &v = Ls.h[gi];
-    int rc = sweep_launch_h(sw->groups[gi].d, (const SweepHItem *)(base + offs[oi++]), (int)v.size(),
-                            (const HamArgs *)(base + offs.back()), sw->active_d, sw->grid, s);
-    if (rc) return rc;
-  }
-  // energy / norm of every point evaluated gate by gate
-  {
-    const size_t off = offs[oi++];
-    const int nr = (int)(offs[oi++]);
-    int rc = sweep_launch_reduce((const SweepRItem *)(base + off), nr, sw->active_d, sw->grid, s);
-    if (rc) return rc;
-  }
-  if (grad) {
-    for (int k = (int)Ls.rev.size() - 1; k >= 0; --k)
-      for (int li = 0; li < 2 * NG; ++li) {
-        const auto &v = Ls.rev[k][li];
-        int rc = sweep_launch_adj(sw->groups[li / 2].d, li % 2,
-                                  (const SweepItem *)(base + offs[oi + (size_t)k * 2 * NG + li]), (int)v.size(),
-                                  sw->active_d, sw->grid, s);
-        if (rc) return rc;
-      }
-    oi += Ls.rev.size() * 2 * NG;
-    int rc = sweep_launch_reduce((const SweepRItem *)(base + offs[oi]), (int)Ls.red.size(), sw->active_d, sw->grid,
-                                 s);
-    if (rc) return rc;
-  }
   for (int b = 0; b < nside; ++b) FOCK_HIP(hipStreamWaitEvent(s, sw->join[b], 0));
   FOCK_HIP(hipMemcpyAsync(pin_res(sw), sw->res_d, sizeof(double) * sw->n_res, hipMemcpyDeviceToHost, s));
   return FOCK_OK;
 }
 
-// Lay out all item lists in one device blob; offs lists, in order: launches of
-// small points, forward [k][2 g + class], H [g], E/norm reduce (offset, count), reverse
-// [k][2 g + class], grad reduce,
-// and finally the per-point HamArgs array.
-int stage_lists(fock_sweep *sw, const Lists &Ls, bool grad, std::vector<size_t> *offs) {
+// Lay out all item lists in one device blob.
+int stage_lists(fock_sweep *sw, Lists &Ls, bool grad) {
   std::vector<char> blob;
-  offs->clear();
-  for (auto &v : Ls.small) offs->push_back(push_items(blob, v));
-  for (auto &lk : Ls.fwd)
-    for (auto &v : lk) offs->push_back(push_items(blob, v));
-  for (auto &v : Ls.h) offs->push_back(push_items(blob, v));
-  std::vector<SweepRItem> en;
-  for (size_t pi = 0; pi < sw->pts.size(); ++pi) {
-    const SPoint &P = sw->pts[pi];
-    if (point_small(P)) continue;
-    en.push_back(SweepRItem{(int)pi, 0, P.GH, 2, 0, 0, P.partial, P.res + 0});
-    en.push_back(SweepRItem{(int)pi, 0, P.GH, 2, 1, 0, P.partial, P.res + 1});
+  auto put = [&](auto &l) { l.off = push_items(blob, l.v); };
+  for (GroupLists &GL : Ls.g) {
+    for (auto &Ly : GL.layers) {
+      for (int c = 0; c < 2; ++c) {
+        put(Ly.fwd[c]);
+        if (grad) put(Ly.rev[c]);
+      }
+      for (RunBatch &rb : Ly.runs) {
+        put(rb.runs);
+        put(rb.tiles);
+      }
+    }
+    put(GL.h);
+    put(GL.en);
+    if (grad) put(GL.red);
   }
-  offs->push_back(push_items(blob, en));
-  offs->push_back(en.size());
-  if (grad) {
-    for (auto &lk : Ls.rev)
-      for (auto &v : lk) offs->push_back(push_items(blob, v));
-    offs->push_back(push_items(blob, Ls.red));
-  }
-  std::vector<HamArgs> hams;
-  for (auto &P : sw->pts) hams.push_back(P.h);
-  offs->push_back(push_items(blob, hams));
+  for (auto &l : Ls.small) put(l);
+  put(Ls.hams);
   return upload_blob(sw, blob);
 }
 
@@ -425,10 +462,9 @@ int eval_forward(fock_sweep *sw, const std::vector<char> &sel) {
     const int brc = build_lists(sw, sel, false, &Lf);
     if (brc) return brc;
   }
-  std::vector<size_t> offf;
   int rc = upload_recs(sw);
   if (rc) return rc;
-  rc = stage_lists(sw, Lf, false, &offf);
+  rc = stage_lists(sw, Lf, false);
   if (rc) return rc;
   for (size_t pi = 0; pi < sw->pts.size(); ++pi) {
     SPoint &P = sw->pts[pi];
@@ -436,7 +472,7 @@ int eval_forward(fock_sweep *sw, const std::vector<char> &sel) {
     pin_active(sw)[pi] = P.want ? 1 : 0;
   }
   pack_angles(sw);
-  rc = enqueue_eval(sw, Lf, offf, false, true);
+  rc = enqueue_eval(sw, Lf, false, true);
   if (rc) return rc;
   FOCK_HIP(hipStreamSynchronize(sw->s));
   unpack(sw, false);
@@ -455,13 +491,13 @@ int bfgs_phase(fock_sweep *sw, const std::vector<char> &sel, const std::vector<d
     if (brc) return brc;
   }
   std::vector<size_t> offs;
-  int rc = stage_lists(sw, Ls, true, &offs);
+  int rc = stage_lists(sw, Ls, true);
   if (rc) return rc;
   rc = upload_recs(sw);
   if (rc) return rc;
   destroy_graph(sw);
   FOCK_HIP(hipStreamBeginCapture(sw->s, hipStreamCaptureModeThreadLocal));
-  rc = enqueue_eval(sw, Ls, offs, true, true);
+  rc = enqueue_eval(sw, Ls, true, true);
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(sw->s, &g);
   if (rc) {
@@ -597,12 +633,11 @@ int score_phase(fock_sweep *sw, const std::vector<char> &sel, std::vector<std::v
     const int brc = build_lists(sw, sel, false, &Ls);
     if (brc) return brc;
   }
-  std::vector<size_t> offs;
   // pool items reuse the H tiles of every point
   std::vector<char> blob;
   int rc = upload_recs(sw);
   if (rc) return rc;
-  rc = stage_lists(sw, Ls, false, &offs);
+  rc = stage_lists(sw, Ls, false);
   if (rc) return rc;
   for (size_t pi = 0; pi < sw->pts.size(); ++pi) {
     SPoint &P = sw->pts[pi];
@@ -611,7 +646,7 @@ int score_phase(fock_sweep *sw, const std::vector<char> &sel, std::vector<std::v
     pin_active(sw)[pi] = P.want ? 1 : 0;
   }
   pack_angles(sw);
-  rc = enqueue_eval(sw, Ls, offs, false, true);
+  rc = enqueue_eval(sw, Ls, false, true);
   if (rc) return rc;
   // pool scoring: items per group, then per-slot reductions into res[2..]
   std::vector<std::vector<SweepHItem>> pitems(sw->groups.size());
@@ -1087,7 +1122,7 @@ int fock_sweep_autotune(fock_sweep_t *sw, const char *cache_path, int *best_grid
   std::vector<size_t> offs;
   int rc = upload_recs(sw);
   if (rc) return rc;
-  rc = stage_lists(sw, Ls, false, &offs);
+  rc = stage_lists(sw, Ls, false);
   if (rc) return rc;
   for (size_t pi = 0; pi < sw->pts.size(); ++pi) {
     SPoint &P = sw->pts[pi];
@@ -1108,7 +1143,7 @@ int fock_sweep_autotune(fock_sweep_t *sw, const char *cache_path, int *best_grid
     float t[3];
     for (int r = -1; r < 3; ++r) {
       FOCK_HIP(hipEventRecord(e0, sw->s));
-      rc = enqueue_eval(sw, Ls, offs, false, true);
+      rc = enqueue_eval(sw, Ls, false, true);
       if (rc) break;
       FOCK_HIP(hipEventRecord(e1, sw->s));
       FOCK_HIP(hipEventSynchronize(e1));

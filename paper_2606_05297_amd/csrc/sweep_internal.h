@@ -1,6 +1,7 @@
 // Work items and launchers of the batched sweep kernels.
 #pragma once
 
+#include "fuse_internal.h"
 #include "gate_kernels.h"
 #include "stencil_kernels.h"
 
@@ -52,6 +53,18 @@ struct SweepItem {
 };
 static_assert(sizeof(DiagRun) % 4 == 0, "run descriptors are copied word by word");
 
+// A fused run of point p's gates (tile_runs.hip): forward phi <- run(src);
+// reverse in place on phi and lam, partial sums into partial[k * rs + tile].
+struct SweepRun {
+  FuseArgs a;
+  int p, rs;
+  GPtr<const float2> src;
+  GPtr<float2> phi;
+  GPtr<float2> lam;
+  CPtr<const float2> utab;
+  GPtr<double> partial;
+};
+
 // One tile of H psi or of pool scoring for point p.
 struct SweepHItem {
   int p, vb;
@@ -84,6 +97,9 @@ bool sweep_m0_piped(int d, int namp, int i);
 bool sweep_split_classes(int d);
 int sweep_launch_gate(int d, int cls, const SweepItem *items, int n, const int *active, int grid, hipStream_t s);
 int sweep_launch_adj(int d, int cls, const SweepItem *items, int n, const int *active, int grid, hipStream_t s);
+// Workgroup b runs tile tiles[b].y of runs[tiles[b].x].
+int sweep_launch_runs(int d, bool rev, const SweepRun *runs, const int2 *tiles, int n, int waves, size_t lds,
+                      const int *active, hipStream_t s);
 int sweep_launch_h(int d, const SweepHItem *items, int n, const HamArgs *hams, const int *active, int grid,
                    hipStream_t s);
 int sweep_launch_pool(int d, const SweepHItem *items, int n, const SweepPoolArgs *pa, const int *active, int grid,

@@ -24,6 +24,7 @@
 #pragma once
 
 #include "gate_kernels.h"
+#include "tile_pair.h"
 
 namespace fock {
 
@@ -32,8 +33,8 @@ constexpr int kTileWaves = 16;  // wavefronts of a workgroup, at most
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Levels per group slot (2, 4 or 8) and units per gate.
-__host__ __device__ inline int tile_slots(int D) { return D <= 2 ? 2 : (D <= 4 ? 4 : 8); }
-__host__ __device__ inline int tile_units(int D) {
+__host__ __device__ constexpr int tile_slots(int D) { return D <= 2 ? 2 : (D <= 4 ? 4 : 8); }
+__host__ __device__ constexpr int tile_units(int D) {
   const int per = 8 / tile_slots(D);
   return (D + per - 1) / per;
 }
@@ -62,18 +63,17 @@ __device__ __forceinline__ int tile_at(int base, int off) { return P2 ? base ^ o
 // least 0.5 / d away from an integer, more than its rounding error.
 __device__ __forceinline__ int tile_div(int n, float r) { return (int)(((float)n + 0.5f) * r); }
 
-// What a lane does in every gate: its unit's two slots and, as a matrix row,
-// the dword offsets of its entries in the packed blocks.
-struct TileLane {
-  int unit, c0, cstep;     // unit of the wave, its first fibre chunk and the chunk stride
-  int ni[2], nj_s[2], nj_d[2];
-  bool ok[2];
-  int of[2], od[2];        // entry (row, slot), entry (slot, row): the part the row's (re or im) starts with
-  unsigned keep[2];        // 0: zero entry (row and slot in different blocks)
-  unsigned neg_f, neg_d;   // sign bits of the forward and the adjoint operand
+// What a lane does in every gate, by cutoff and unit: a compile-time table (its
+// divisions and block sums would cost a workgroup more than a gate).  Offsets
+// are dwords into a packed two-mode table (0xffff: none).
+struct TileLaneWord {
+  uint32_t fwd, dag;    // operand entry (row, slot) and (slot, row) of slots 2g, 2g + 1
+  uint32_t link, diag;  // generator entries: links (2g, 2g + 1), (2g + 1, 2g + 2); slots 2g, 2g + 1
+  uint32_t levels;      // 3-bit levels and flags, see tile_lane
 };
+constexpr int kTileMinD = 2, kTileMaxD = 8;
 
-__device__ __forceinline__ int tile_block_off(int s, int D) {  // packed offset of block s
+constexpr int tile_block_off(int s, int D) {  // packed offset (entries) of block s
   int off = 0;
   for (int t = 0; t < s; ++t) {
     const int b = t < D ? t + 1 : 2 * D - 1 - t;
@@ -81,167 +81,247 @@ __device__ __forceinline__ int tile_block_off(int s, int D) {  // packed offset 
   }
   return off;
 }
+// Packed entry (m + up, m) of group g, or -1: member m is n_i = m, in block g
+// (m <= g) or g + D.
+constexpr int tile_entry(int D, int g, int p, int q) {
+  if (g >= D || p >= D || q >= D || (p <= g) != (q <= g)) return -1;
+  const bool lo = p <= g;
+  const int b = lo ? g + 1 : D - 1 - g, o = lo ? 0 : g + 1;
+  return tile_block_off(lo ? g : g + D, D) + (p - o) * b + (q - o);
+}
+constexpr TileLaneWord tile_lane_word(int D, int unit, int lane) {
+  TileLaneWord w{0, 0, 0, 0, 0};
+  const int dp = tile_slots(D), per = 8 / dp, g = lane >> 4, row = lane & 15, im = row & 1;
+  const int pg = unit * per + (row >> 1) / dp, pm = (row >> 1) % dp;
+  uint32_t lv = im ? 1u << 31 : 0u;
+  for (int e = 0; e < 3; ++e) {  // slots 2g, 2g + 1 and, for the second link, 2g + 2
+    const int q = 2 * g + e, qg = unit * per + q / dp, qm = q % dp;
+    const bool ok = q < 8 && qg < D && qm < D;
+    const uint32_t ni = ok ? qm : 0, njs = ok ? (qg - qm + D) % D : 0, njd = ok ? (qm - qg - 1 + D) % D : 0;
+    lv |= ni << (3 * e) | njs << (9 + 3 * e) | njd << (18 + 3 * e);
+    if (e == 2) break;
+    if (ok) lv |= 1u << (27 + e);
+    const int f = ok && pg == qg ? tile_entry(D, qg, pm, qm) : -1, r = ok && pg == qg ? tile_entry(D, qg, qm, pm) : -1;
+    if (f >= 0) lv |= 1u << (29 + e);
+    w.fwd |= (uint32_t)(f >= 0 ? 2 * f + im : 0) << (16 * e);
+    w.dag |= (uint32_t)(r >= 0 ? 2 * r + im : 0) << (16 * e);
+    const int k = ok && (q + 1) / dp == q / dp ? tile_entry(D, qg, qm + 1, qm) : -1, d = ok ? tile_entry(D, qg, qm, qm) : -1;
+    w.link |= (uint32_t)(k >= 0 ? 2 * k : 0xffff) << (16 * e);
+    w.diag |= (uint32_t)(d >= 0 ? 2 * d : 0xffff) << (16 * e);
+  }
+  w.levels = lv;
+  return w;
+}
+struct TileLaneTable {
+  TileLaneWord w[kTileMaxD - kTileMinD + 1][8][64];
+  constexpr TileLaneTable() : w() {
+    for (int D = kTileMinD; D <= kTileMaxD; ++D)
+      for (int u = 0; u < tile_units(D); ++u)
+        for (int l = 0; l < 64; ++l) w[D - kTileMinD][u][l] = tile_lane_word(D, u, l);
+  }
+};
+static __device__ const TileLaneTable kTileLanes{};
 
+struct TileLane {
+  TileLaneWord w;
+  int c0, cstep;           // the wave's first fibre chunk and the chunk stride
+  bool ok0, ok1;           // slots 2g, 2g + 1 hold members
+  bool whole;              // every lane's do
+  unsigned keep0, keep1;   // 0: zero entry (row and slot in different blocks)
+  unsigned neg_f, neg_d;   // sign bits of the forward and the adjoint operand
+};
+// The wave's unit is wave % units and its chunks are wave / units, + cstep, ..;
+// nwaves / units whole rounds of waves work, the rest have no chunk.
 __device__ __forceinline__ TileLane tile_lane(int D, int nwaves) {
   TileLane t;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int units = tile_units(D), dp = tile_slots(D), per = 8 / dp;
-  t.unit = wave % units;
+  const int units = tile_units(D), round = wave / units;
   t.cstep = nwaves / units > 0 ? nwaves / units : 1;
-  t.c0 = wave / units < t.cstep ? wave / units : 1 << 20;  // waves beyond the last whole round rest
-  const int g = lane >> 4, row = lane & 15;
-  const int im = row & 1;
-  t.neg_f = im ? 0u : 0x80000000u;
-  t.neg_d = im ? 0x80000000u : 0u;
-  const int ps = row >> 1, pg = t.unit * per + ps / dp, pm = ps % dp;  // the row's group and member
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const int q = 2 * g + e, qg = t.unit * per + q / dp, qm = q % dp;
-    t.ok[e] = qg < D && qm < D;
-    t.ni[e] = t.ok[e] ? qm : 0;
-    t.nj_s[e] = t.ok[e] ? (qg - qm + D) % D : 0;
-    t.nj_d[e] = t.ok[e] ? (qm - qg - 1 + D) % D : 0;
-    t.of[e] = t.od[e] = 0;
-    t.keep[e] = 0u;
-    if (t.ok[e] && pg == qg && pm < D && (pm <= pg) == (qm <= pg)) {
-      const bool lo = pm <= pg;
-      const int s = lo ? pg : pg + D, b = lo ? pg + 1 : D - 1 - pg;
-      const int p0 = lo ? pm : pm - pg - 1, q0 = lo ? qm : qm - pg - 1;
-      const int off = tile_block_off(s, D);
-      t.of[e] = 2 * (off + p0 * b + q0) + im;
-      t.od[e] = 2 * (off + q0 * b + p0) + im;
-      t.keep[e] = ~0u;
-    }
-  }
+  t.c0 = round < t.cstep ? round : 1 << 20;
+  t.w = kTileLanes.w[D - kTileMinD][wave - round * units][lane];
+  t.ok0 = t.w.levels & (1u << 27);
+  t.ok1 = t.w.levels & (1u << 28);
+  t.whole = D == 8 || D == 4;  // slots = groups x members
+  t.keep0 = t.w.levels & (1u << 29) ? ~0u : 0u;
+  t.keep1 = t.w.levels & (1u << 30) ? ~0u : 0u;
+  t.neg_f = ~t.w.levels & 0x80000000u;
+  t.neg_d = t.w.levels & 0x80000000u;
   return t;
 }
 
 // A lane's matrix operand for the four reduction steps: row (re or im) times
-// (re, im) of its two slots.
+// (re, im) of its two slots.  Loaded as table entries (TileRaw, so that a load
+// can be in flight while another gate runs) and finished by tile_mat.
+struct TileRaw {
+  unsigned e00, e01, e10, e11;
+};
 struct TileMat {
-  float a[4];
+  float a0, a1, a2, a3;
 };
 template <bool DAG>
-__device__ __forceinline__ TileMat tile_mat(const float2 *U, const TileLane &t) {
+__device__ __forceinline__ TileRaw tile_raw(const float2 *U, const TileLane &t) {
   const unsigned *u = reinterpret_cast<const unsigned *>(U);
-  TileMat m;
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const int o = DAG ? t.od[e] : t.of[e];
-    m.a[2 * e] = __uint_as_float((u[o] & t.keep[e]) ^ (DAG ? t.neg_d : 0u));
-    m.a[2 * e + 1] = __uint_as_float((u[o ^ 1] & t.keep[e]) ^ (DAG ? 0u : t.neg_f));
+  const uint32_t o = DAG ? t.w.dag : t.w.fwd, o0 = o & 0xffffu, o1 = o >> 16;
+  return {u[o0], u[o0 ^ 1], u[o1], u[o1 ^ 1]};
+}
+template <bool DAG>
+__device__ __forceinline__ TileMat tile_mat(const TileRaw &r, const TileLane &t) {
+  const unsigned n0 = DAG ? t.neg_d : 0u, n1 = DAG ? 0u : t.neg_f;
+  return {__uint_as_float((r.e00 & t.keep0) ^ n0), __uint_as_float((r.e01 & t.keep0) ^ n1),
+          __uint_as_float((r.e10 & t.keep1) ^ n0), __uint_as_float((r.e11 & t.keep1) ^ n1)};
+}
+
+// The generator's part of a reverse step.  A is tridiagonal in a block's
+// members and its entries are all real (HR, PR) or all imaginary (HI, DH, PI,
+// and the diagonal CK), anti-Hermitian: a link (m, m + 1) with entry a = A[m+1][m]
+// gives Re(conj(l[m+1]) a p[m] - conj(l[m]) conj(a) p[m+1]).  A few FMAs per
+// fibre, so this stays on the vector ALUs beside the products.
+enum TileGen { TG_REAL, TG_IMAG, TG_DIAG };
+__device__ __forceinline__ int tile_gen_kind(int type) {
+  return type == FOCK_CK ? TG_DIAG : type == FOCK_HR || type == FOCK_PR ? TG_REAL : TG_IMAG;
+}
+struct TileGenW {
+  float w0, w1;
+};
+__device__ __forceinline__ TileGenW tile_gen_raw(const float2 *A, const TileLane &t, int kind) {
+  const uint32_t o = kind == TG_DIAG ? t.w.diag : t.w.link, o0 = o & 0xffffu, o1 = o >> 16;
+  const float *a = reinterpret_cast<const float *>(A) + (kind == TG_REAL ? 0 : 1);
+  return {a[o0 != 0xffffu ? o0 : 0u], a[o1 != 0xffffu ? o1 : 0u]};
+}
+__device__ __forceinline__ TileGenW tile_gen(const TileGenW &r, const TileLane &t, int kind) {
+  const uint32_t o = kind == TG_DIAG ? t.w.diag : t.w.link;
+  return {(o & 0xffffu) != 0xffffu ? r.w0 : 0.f, (o >> 16) != 0xffffu ? r.w1 : 0.f};
+}
+// The lane's terms at one fibre: slots 0, 1, 2 of phi (v) and lambda (l).
+template <int kind>
+__device__ __forceinline__ float tile_gen_sum(const TileGenW &w, float2 v0, float2 v1, float2 v2, float2 l0, float2 l1,
+                                              float2 l2) {
+  if (kind == TG_REAL) {
+    const float s0 = fmaf(l1.x, v0.x, fmaf(l1.y, v0.y, -fmaf(l0.x, v1.x, l0.y * v1.y)));
+    const float s1 = fmaf(l2.x, v1.x, fmaf(l2.y, v1.y, -fmaf(l1.x, v2.x, l1.y * v2.y)));
+    return fmaf(w.w0, s0, w.w1 * s1);
   }
-  return m;
+  if (kind == TG_IMAG) {  // -a (Im conj(l1) v0 + Im conj(l0) v1)
+    const float s0 = fmaf(l1.x, v0.y, fmaf(-l1.y, v0.x, fmaf(l0.x, v1.y, -l0.y * v1.x)));
+    const float s1 = fmaf(l2.x, v1.y, fmaf(-l2.y, v1.x, fmaf(l1.x, v2.y, -l1.y * v2.x)));
+    return -fmaf(w.w0, s0, w.w1 * s1);
+  }
+  return -fmaf(w.w0, fmaf(l0.x, v0.y, -l0.y * v0.x), w.w1 * fmaf(l1.x, v1.y, -l1.y * v1.x));
 }
 
 __device__ __forceinline__ f32x4 tile_mul(const TileMat &m, float2 v0, float2 v1) {
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(m.a[0], v0.x, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(m.a[1], v0.y, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(m.a[2], v1.x, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(m.a[3], v1.y, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(m.a0, v0.x, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(m.a1, v0.y, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(m.a2, v1.x, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(m.a3, v1.y, acc, 0, 0, 0);
   return acc;
 }
 
-// Fibre decomposition of a gate on tile modes with strides si < sj: fibre
-// f = low + si (mid + dm high), dm = sj / (si D).  Computed once per gate and
-// launch (the divisions cost more than the gate on a small tile).
-struct TilePair {
-  int si, sj, dm;
-  float rsi, rdm;
-};
-__device__ __forceinline__ TilePair tile_pair(int si, int sj, int D) {
-  TilePair p;
-  p.si = si;
-  p.sj = sj;
-  p.dm = sj / (si * D);
-  p.rsi = 1.0f / (float)si;
-  p.rdm = 1.0f / (float)p.dm;
-  return p;
-}
 __device__ __forceinline__ int tile_fibre(int f, const TilePair &p, int D) {
   const int t = tile_div(f, p.rsi), low = f - __mul24(t, p.si);
   const int high = tile_div(t, p.rdm), mid = t - __mul24(high, p.dm);
   return low + __mul24(__mul24(mid, p.si) + __mul24(high, p.sj), D);
 }
 
-// A gate as a wave applies it: the positions of the lane's two members relative
-// to a fibre's, and of the wave's first chunk of fibres.
+// A gate as a wave applies it: the byte offsets of the lane's members (slots 2g,
+// 2g + 1, 2g + 2) relative to a fibre's.  Offsets are positions times 8, so that
+// an LDS address is one exclusive or (sum) and the state's base.
 struct TileStep {
-  int d0, d1, base;
+  int d0, d1, d2;
 };
 template <bool P2>
-__device__ __forceinline__ TileStep tile_step(const TilePair &p, const TileLane &t, int kind, int nfib, int D) {
+__device__ __forceinline__ TileStep tile_step(const TilePair &p, const TileLane &t, int kind) {
+  const uint32_t ni = t.w.levels, nj = ni >> (kind == KIND_SUM ? 9 : 18);
+  auto off = [&](int e) {
+    return 8 * tile_pos<P2>(__mul24((ni >> (3 * e)) & 7, p.si) + __mul24((nj >> (3 * e)) & 7, p.sj));
+  };
   TileStep s;
-  s.d0 = tile_pos<P2>(__mul24(t.ni[0], p.si) + __mul24(kind == KIND_SUM ? t.nj_s[0] : t.nj_d[0], p.sj));
-  s.d1 = tile_pos<P2>(__mul24(t.ni[1], p.si) + __mul24(kind == KIND_SUM ? t.nj_s[1] : t.nj_d[1], p.sj));
-  const int f = t.c0 * 16 + (threadIdx.x & 15);
-  s.base = tile_pos<P2>(tile_fibre(f < nfib ? f : 0, p, D));
+  s.d0 = off(0);
+  s.d1 = off(1);
+  s.d2 = off(2);
   return s;
 }
+__device__ __forceinline__ float2 &tile_amp(float2 *x, int byte) {
+  return *reinterpret_cast<float2 *>(reinterpret_cast<char *>(x) + byte);
+}
 
-// phi <- U phi on the tile (m: the wave's operand of U).  Slots without a
-// member and lanes beyond the last fibre read some amplitude of the tile: their
-// matrix columns are zero, resp. their column is not written.
-template <bool P2>
-__device__ __forceinline__ void tile_gate(float2 *phi, const TilePair &p, const TileLane &t, const TileStep &s,
-                                          const TileMat &m, int nfib, int D) {
-  int f0 = t.c0 * 16;
-  int a0 = tile_at<P2>(s.base, s.d0), a1 = tile_at<P2>(s.base, s.d1);
-  float2 v0 = phi[a0], v1 = phi[a1];
-  while (true) {
-    const f32x4 r = tile_mul(m, v0, v1);
-    const bool in = f0 + (int)(threadIdx.x & 15) < nfib;
-    if (in && t.ok[0]) phi[a0] = make_float2(r[0], r[1]);
-    if (in && t.ok[1]) phi[a1] = make_float2(r[2], r[3]);
-    f0 += t.cstep * 16;
-    if (f0 >= nfib) break;
+// phi <- U phi on the tile (m: the wave's operand of U; at(f): byte offset of
+// fibre f).  Slots without a member and lanes beyond the last fibre read some
+// amplitude of the tile: their matrix columns are zero, resp. their column is
+// not written.
+template <bool P2, class At>
+__device__ __forceinline__ void tile_gate(float2 *phi, const TileLane &t, const TileStep &s, const TileMat &m, int nfib,
+                                          At at) {
+  for (int f0 = t.c0 * 16; f0 < nfib; f0 += t.cstep * 16) {
     const int f = f0 + (threadIdx.x & 15);
-    const int base = tile_pos<P2>(tile_fibre(f < nfib ? f : 0, p, D));
-    a0 = tile_at<P2>(base, s.d0);
-    a1 = tile_at<P2>(base, s.d1);
-    v0 = phi[a0];
-    v1 = phi[a1];
+    const bool in = f < nfib;
+    const int base = at(in ? f : 0);
+    const int a0 = tile_at<P2>(base, s.d0), a1 = tile_at<P2>(base, s.d1);
+    const f32x4 r = tile_mul(m, tile_amp(phi, a0), tile_amp(phi, a1));
+    if (t.whole && f0 + 16 <= nfib) {  // every lane holds two members
+      tile_amp(phi, a0) = make_float2(r[0], r[1]);
+      tile_amp(phi, a1) = make_float2(r[2], r[3]);
+    } else {
+      if (in && t.ok0) tile_amp(phi, a0) = make_float2(r[0], r[1]);
+      if (in && t.ok1) tile_amp(phi, a1) = make_float2(r[2], r[3]);
+    }
   }
 }
 
 // Reverse step: returns this lane's share of Re<lam|A phi>, then phi <- U^+ phi
-// and lam <- U^+ lam (m: operand of U^+, ma: of A).
-template <bool P2>
-__device__ __forceinline__ float tile_gate_adj(float2 *phi, float2 *lam, const TilePair &p, const TileLane &t,
-                                               const TileStep &s, const TileMat &m, const TileMat &ma, int nfib,
-                                               int D) {
-  int f0 = t.c0 * 16;
-  int a0 = tile_at<P2>(s.base, s.d0), a1 = tile_at<P2>(s.base, s.d1);
-  float2 v0 = phi[a0], v1 = phi[a1], l0 = lam[a0], l1 = lam[a1];
+// and lam <- U^+ lam (m: operand of U^+; w: the generator's weights).
+template <bool P2, int GEN, class At>
+__device__ __forceinline__ float tile_adj_loop(float2 *phi, float2 *lam, const TileLane &t, const TileStep &s,
+                                               const TileMat &m, const TileGenW &w, int nfib, At at) {
   float g = 0.f;
-  while (true) {
-    const f32x4 ap = tile_mul(ma, v0, v1);
+  for (int f0 = t.c0 * 16; f0 < nfib; f0 += t.cstep * 16) {
+    const int f = f0 + (threadIdx.x & 15);
+    const bool in = f < nfib;
+    const int base = at(in ? f : 0);
+    const int a0 = tile_at<P2>(base, s.d0), a1 = tile_at<P2>(base, s.d1), a2 = tile_at<P2>(base, s.d2);
+    const float2 v0 = tile_amp(phi, a0), v1 = tile_amp(phi, a1), l0 = tile_amp(lam, a0), l1 = tile_amp(lam, a1);
+    const float2 v2 = tile_amp(phi, a2), l2 = tile_amp(lam, a2);
     const f32x4 r = tile_mul(m, v0, v1);
     const f32x4 q = tile_mul(m, l0, l1);
-    const bool in = f0 + (int)(threadIdx.x & 15) < nfib;
-    const float c = fmaf(l0.x, ap[0], fmaf(l0.y, ap[1], fmaf(l1.x, ap[2], l1.y * ap[3])));
-    g += in ? c : 0.f;
-    if (in && t.ok[0]) {
-      phi[a0] = make_float2(r[0], r[1]);
-      lam[a0] = make_float2(q[0], q[1]);
+    const float c = tile_gen_sum<GEN>(w, v0, v1, v2, l0, l1, l2);
+    if (t.whole && f0 + 16 <= nfib) {
+      g += c;
+      tile_amp(phi, a0) = make_float2(r[0], r[1]);
+      tile_amp(lam, a0) = make_float2(q[0], q[1]);
+      tile_amp(phi, a1) = make_float2(r[2], r[3]);
+      tile_amp(lam, a1) = make_float2(q[2], q[3]);
+    } else {
+      g += in ? c : 0.f;
+      if (in && t.ok0) {
+        tile_amp(phi, a0) = make_float2(r[0], r[1]);
+        tile_amp(lam, a0) = make_float2(q[0], q[1]);
+      }
+      if (in && t.ok1) {
+        tile_amp(phi, a1) = make_float2(r[2], r[3]);
+        tile_amp(lam, a1) = make_float2(q[2], q[3]);
+      }
     }
-    if (in && t.ok[1]) {
-      phi[a1] = make_float2(r[2], r[3]);
-      lam[a1] = make_float2(q[2], q[3]);
-    }
-    f0 += t.cstep * 16;
-    if (f0 >= nfib) break;
-    const int f = f0 + (threadIdx.x & 15);
-    const int base = tile_pos<P2>(tile_fibre(f < nfib ? f : 0, p, D));
-    a0 = tile_at<P2>(base, s.d0);
-    a1 = tile_at<P2>(base, s.d1);
-    v0 = phi[a0];
-    v1 = phi[a1];
-    l0 = lam[a0];
-    l1 = lam[a1];
   }
   return g;
+}
+template <bool P2, class At>
+__device__ __forceinline__ float tile_gate_adj(float2 *phi, float2 *lam, const TileLane &t, const TileStep &s,
+                                               const TileMat &m, const TileGenW &raw, int gen, int nfib, At at) {
+  const TileGenW w = tile_gen(raw, t, gen);
+  if (gen == TG_REAL) return tile_adj_loop<P2, TG_REAL>(phi, lam, t, s, m, w, nfib, at);
+  if (gen == TG_IMAG) return tile_adj_loop<P2, TG_IMAG>(phi, lam, t, s, m, w, nfib, at);
+  return tile_adj_loop<P2, TG_DIAG>(phi, lam, t, s, m, w, nfib, at);
+}
+
+// Per-lane shares of up to 16 gates, summed in double over the wavefront by one
+// FP64 matrix instruction a gate: row q of the 16 x 16 accumulator gathers gate
+// q's 64 values in 16 column sums, which tile_sums_flush adds up once.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kTileSums = 16;
+__device__ __forceinline__ void tile_sums_add(f64x4 &acc, int q, float v) {
+  const double sel = (int)(threadIdx.x & 15) == q ? 1.0 : 0.0;
+  acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sel, (double)v, acc, 0, 0, 0);
 }
 
 // Sum over the wavefront in double by DPP moves (no LDS traffic), valid in lane 63.
@@ -260,6 +340,23 @@ __device__ __forceinline__ double wave_total_d(double v) {
   v = dpp_add_d<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
   v = dpp_add_d<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
   return v;
+}
+
+// part[q][wave] = gate q's sum over the wave.  A product with the row numbers
+// tells which row each lane's accumulator registers hold.
+__device__ __forceinline__ void tile_sums_flush(const f64x4 &acc, double (*part)[kTileWaves]) {
+  f64x4 row = {0.0, 0.0, 0.0, 0.0};
+  row = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(threadIdx.x & 15), (threadIdx.x & 63) < 16 ? 1.0 : 0.0, row, 0, 0,
+                                             0);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    double v = acc[r];
+    v = dpp_add_d<0x111, 0xf>(v);
+    v = dpp_add_d<0x112, 0xf>(v);
+    v = dpp_add_d<0x114, 0xf>(v);
+    v = dpp_add_d<0x118, 0xf>(v);
+    if ((threadIdx.x & 15) == 15) part[(int)row[r]][threadIdx.x >> 6] = v;
+  }
 }
 
 }  // namespace fock

@@ -335,8 +335,8 @@ def get_real_fusion() -> int:
 
 
 def real_fusion_plan(h: Ham, ops):
-    """[(first gate, lowest tile mode or -1), ...]: the runs an evaluation of
-    ops on real states launches (fock_real_fusion_plan; host only)."""
+    """[(first gate, lowest tile mode or -1), ...]: the runs of ops on real
+    states in the given order (fock_real_fusion_plan; host only)."""
     n = len(ops)
     k0 = (C.c_int * max(n, 1))()
     a = (C.c_int * max(n, 1))()
@@ -959,7 +959,8 @@ FUSE_OFF, FUSE_FORWARD, FUSE_ALL = 0, 1, 2
 
 
 def set_gate_fusion(mode: int):
-    """0: per-gate passes (default); 1: fused forward circuit; 2: fused forward and adjoint sweep."""
+    """0: the library plans the passes (default); 1: fused runs in the forward circuit only; 2: fused runs in the
+    forward circuit and the adjoint sweep."""
     _check(load().fock_set_gate_fusion(int(mode)))
 
 
