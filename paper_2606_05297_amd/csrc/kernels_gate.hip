@@ -26,57 +26,50 @@ FOCK_GATE_EXTERN(12) FOCK_GATE_EXTERN(13) FOCK_GATE_EXTERN(14) FOCK_GATE_EXTERN(
 // ---------------------------------------------------------------- device-side gate build
 // U = V diag(exp(i theta lambda)) V^+ per conserved block, from the FP64
 // eigendata of G = -i A (A = i G), computed once per (type, d) on the host.
-// Entry e of gate table r at angle th.
-__device__ __forceinline__ void gate_build_entry(const GateRec &r, double th, int e, const EigTables &T,
-                                                 float2 *__restrict__ utab) {
-  const int d = T.d;
-  if (r.type == FOCK_KERR || r.type == FOCK_ROT) {
-    if (e < d) {
-      const double f = r.type == FOCK_KERR ? (double)(e * e) : (double)e;
-      double sn, cs;
-      sincos(th * f, &sn, &cs);
-      utab[r.u_off + e] = make_float2((float)cs, (float)sn);
-    }
+// Entries [blockIdx.x * kBlock, + kBlock) of gate table r at angle th.  The gate's
+// phases exp(i th lambda_m) come first, one per thread, into LDS: each entry of a
+// block of b members needs b of them, and b FP64 sine-cosines in a row were most
+// of this latency-bound kernel's time (30 gates at d = 8: 6.3 -> 5.4 us).
+__device__ __forceinline__ void gate_build_part(const GateRec &r, double th, const EigTables &T,
+                                                float2 *__restrict__ utab) {
+  __shared__ double2 ph[kMaxD * kMaxD];
+  const int d = T.d, e = blockIdx.x * kBlock + threadIdx.x;
+  const bool phase = r.type == FOCK_KERR || r.type == FOCK_ROT, squeeze = r.type == FOCK_SR || r.type == FOCK_SI;
+  const double *lam = squeeze ? T.lam1[r.type == FOCK_SR ? 0 : 1] : phase ? nullptr : T.lam[table_slot(r.type)];
+  const int np = phase || squeeze ? d : d * d;
+  if ((int)threadIdx.x < np) {
+    const int m = threadIdx.x;
+    const double f = !phase ? lam[m] : r.type == FOCK_KERR ? (double)(m * m) : (double)m;
+    double sn, cs;
+    sincos(th * f, &sn, &cs);
+    ph[m] = make_double2(cs, sn);
+  }
+  __syncthreads();
+  if (phase) {
+    if (e < d) utab[r.u_off + e] = make_float2((float)ph[e].x, (float)ph[e].y);
     return;
   }
-  if (r.type == FOCK_SR || r.type == FOCK_SI) {
-    // dense d x d: U[p][q] = sum_m V[p][m] e^{i th lam_m} conj(V[q][m])
+  // U[p][q] = sum_m V[p][m] e^{i th lam_m} conj(V[q][m]) over the entry's block
+  // (squeezers: the whole d x d matrix)
+  int off = 0, loff = 0, b = d;
+  if (squeeze) {
     if (e >= d * d) return;
-    const int t = r.type == FOCK_SR ? 0 : 1;
-    const int p = e / d, q = e % d;
-    const double *V = T.V1[t];
-    const double *lam = T.lam1[t];
-    double ur = 0.0, ui = 0.0;
-    for (int m = 0; m < d; ++m) {
-      double sn, cs;
-      sincos(th * lam[m], &sn, &cs);
-      const double pr = V[2 * (p * d + m)], pi = V[2 * (p * d + m) + 1];
-      const double qr = V[2 * (q * d + m)], qi = V[2 * (q * d + m) + 1];
-      const double tr = pr * cs - pi * sn, ti = pr * sn + pi * cs;
-      ur += tr * qr + ti * qi;
-      ui += ti * qr - tr * qi;
+  } else {
+    if (e >= T.psize) return;
+    for (int s = 0; s <= 2 * d - 2; ++s) {
+      b = blk_hi(KIND_SUM, d, s) - blk_lo(KIND_SUM, d, s) + 1;
+      if (e < off + b * b) break;
+      off += b * b;
+      loff += b;
     }
-    utab[r.u_off + e] = make_float2((float)ur, (float)ui);
-    return;
-  }
-  if (e >= T.psize) return;
-  int off = 0, loff = 0, b = 1;
-  for (int s = 0; s <= 2 * d - 2; ++s) {
-    b = blk_hi(KIND_SUM, d, s) - blk_lo(KIND_SUM, d, s) + 1;
-    if (e < off + b * b) break;
-    off += b * b;
-    loff += b;
   }
   const int p = (e - off) / b, q = (e - off) % b;
-  const double *V = T.V[table_slot(r.type)] + 2 * off;
-  const double *lam = T.lam[table_slot(r.type)] + loff;
+  const double *V = squeeze ? T.V1[r.type == FOCK_SR ? 0 : 1] : T.V[table_slot(r.type)] + 2 * off;
   double ur = 0.0, ui = 0.0;
   for (int m = 0; m < b; ++m) {
-    double sn, cs;
-    sincos(th * lam[m], &sn, &cs);
+    const double cs = ph[loff + m].x, sn = ph[loff + m].y;
     const double pr = V[2 * (p * b + m)], pi = V[2 * (p * b + m) + 1];
     const double qr = V[2 * (q * b + m)], qi = V[2 * (q * b + m) + 1];
-    // V[p][m] e^{i th lam} conj(V[q][m])
     const double tr = pr * cs - pi * sn, ti = pr * sn + pi * cs;
     ur += tr * qr + ti * qi;
     ui += ti * qr - tr * qi;
@@ -89,7 +82,7 @@ __global__ __launch_bounds__(kBlock) void k_gate_build(const double *__restrict_
                                                        float2 *__restrict__ utab) {
   const int k = blockIdx.y;
   if (k >= n) return;
-  gate_build_entry(recs[k], theta[k], blockIdx.x * kBlock + threadIdx.x, T, utab);
+  gate_build_part(recs[k], theta[k], T, utab);
 }
 
 // The same with the angles and records in the kernel arguments (no staging
@@ -106,7 +99,7 @@ __global__ __launch_bounds__(kBlock) void k_gate_build_args(GateArgs ga, EigTabl
     theta_out[k] = th;
     recs_out[k] = r;
   }
-  gate_build_entry(r, th, blockIdx.x * kBlock + threadIdx.x, T, utab);
+  gate_build_part(r, th, T, utab);
 }
 
 int launch_gate_build_args(const GateArgs &ga, const EigTables &T, float2 *utab, double *theta_out,
