@@ -48,6 +48,7 @@ SOURCES = [
     "tile_runs.hip",
     "gate1_kernels.hip",
     "f64_kernels.hip",
+    "f64_small.hip",
     "adapt64.cpp",
     "dense_gate.hip",
     "mlp_kernels.hip",

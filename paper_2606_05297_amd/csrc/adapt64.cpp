@@ -40,8 +40,11 @@ struct fock_adapt64 {
   double2 *psi0 = nullptr, *phi = nullptr, *lam = nullptr, *utab = nullptr;
   double *partial = nullptr, *res = nullptr, *th_dev = nullptr;
   fock::GateRec *recs = nullptr;
+  std::vector<double> sums;    // results of the gate-by-gate evaluation
   std::map<int, double2 *> A;  // dense generator per type
   int maxblk = 0;
+  // small states (small64_ok): generator links (behind res); pinned angles, results and gates
+  double *links = nullptr, *host = nullptr;
   int iter = 0;
   bool done = false;
   fock_adapt_report_t warm{};  // warm-up optimisation done at creation (iter 0)
@@ -125,14 +128,30 @@ int fetch(fock_adapt64 *st, int n, double *host) {
   return FOCK_OK;
 }
 
-// E (Rayleigh quotient), <psi|psi>, and the gate gradients when g != nullptr,
-// for the gates st->gops at angles th.  Leaves phi = psi and lam = H psi when
-// no gradient is asked for.
-int eval_gates(fock_adapt64 *st, const std::vector<double> &th, double *E, double *n2, std::vector<double> *g) {
-  const int n = (int)st->gops.size();
-  if (n > st->cap) return set_error(FOCK_ERR_SIZE, "more gates (%d) than the run's capacity (%d)", n, st->cap);
-  for (int k = 0; k < n; ++k)
-    if (!std::isfinite(th[k])) return set_error(FOCK_ERR_NONFINITE, "theta[%d] is not finite", k);
+// Pinned buffer of the one-launch evaluation: angles, then results, then gates.
+constexpr size_t kHost64 = sizeof(double) * (2 * kGates64 + 2) + sizeof(int) * kGates64;
+
+// E, <psi|psi> and the gate sums of a small state (f64_small.hip) into out.
+int eval_small(fock_adapt64 *st, const std::vector<double> &th, bool grad, const double **out) {
+  const int n = (int)th.size();
+  double *res = st->host + kGates64;
+  int *gates = (int *)(res + 2 + kGates64);
+  for (int k = 0; k < n; ++k) {
+    const fock_op_t &op = st->gops[k];
+    st->host[k] = th[k];
+    gates[k] = op.type | op.i << 8 | (op.j < 0 ? 0xff : op.j) << 16;
+  }
+  Small64 it{st->psi0, st->phi, st->lam, st->host, (const double2 *)st->links, gates, res, n, grad ? 1 : 0, 0, 0};
+  const int rc = launch64_small(it, st->h, st->T, st->s);
+  if (rc) return rc;
+  FOCK_HIP(hipStreamSynchronize(st->s));
+  *out = res;
+  return FOCK_OK;
+}
+
+// The same gate by gate, for states of any size.
+int eval_launches(fock_adapt64 *st, const std::vector<double> &th, bool grad, const double **out) {
+  const int n = (int)th.size();
   if (n > 0) {
     // gate records (table offset, reverse-step workgroups) change only with the gate list
     bool same = st->rec_ops.size() == st->gops.size();
@@ -164,7 +183,7 @@ int eval_gates(fock_adapt64 *st, const std::vector<double> &th, double *E, doubl
   if (rc) return rc;
   rc = launch_reduce(st->partial, G, 2, st->res, st->s);
   if (rc) return rc;
-  if (g) {
+  if (grad) {
     for (int k = n - 1; k >= 0; --k) {
       const Fib64 a = make_fib64(st->L, st->d, st->gops[k]);
       const double2 *A = nullptr;
@@ -178,8 +197,24 @@ int eval_gates(fock_adapt64 *st, const std::vector<double> &th, double *E, doubl
     rc = launch_reduce_rows(st->partial + (size_t)2 * st->maxblk, st->maxblk, st->recs, n, st->res + 2, st->s);
     if (rc) return rc;
   }
-  std::vector<double> host(2 + (g ? n : 0));
-  rc = fetch(st, (int)host.size(), host.data());
+  st->sums.resize(2 + (grad ? n : 0));
+  rc = fetch(st, (int)st->sums.size(), st->sums.data());
+  if (rc) return rc;
+  *out = st->sums.data();
+  return FOCK_OK;
+}
+
+// E (Rayleigh quotient), <psi|psi>, and the gate gradients when g != nullptr,
+// for the gates st->gops at angles th.  Leaves phi = psi and lam = H psi when
+// no gradient is asked for.
+int eval_gates(fock_adapt64 *st, const std::vector<double> &th, double *E, double *n2, std::vector<double> *g) {
+  const int n = (int)st->gops.size();
+  if (n > st->cap) return set_error(FOCK_ERR_SIZE, "more gates (%d) than the run's capacity (%d)", n, st->cap);
+  for (int k = 0; k < n; ++k)
+    if (!std::isfinite(th[k])) return set_error(FOCK_ERR_NONFINITE, "theta[%d] is not finite", k);
+  const double *host = nullptr;
+  const int rc = small64_ok(st->d, st->namp, n) ? eval_small(st, th, g != nullptr, &host)
+                                                : eval_launches(st, th, g != nullptr, &host);
   if (rc) return rc;
   if (!std::isfinite(host[0]) || !(host[1] > 0.0))
     return set_error(FOCK_ERR_NONFINITE, "non-finite energy or zero norm (E=%g, norm2=%g)", host[0], host[1]);
@@ -234,6 +269,7 @@ void release(fock_adapt64 *st) {
   for (void *p : {(void *)st->psi0, (void *)st->phi, (void *)st->lam, (void *)st->utab, (void *)st->partial,
                   (void *)st->res, (void *)st->th_dev, (void *)st->recs})
     if (p) (void)hipFree(p);
+  if (st->host) (void)hipHostFree(st->host);
   for (auto &kv : st->A) (void)hipFree(kv.second);
   if (st->s) (void)hipStreamDestroy(st->s);
 }
@@ -299,7 +335,9 @@ int adapt64_create(const fock_ham_t *ham, const fock_op_t *pool, int P, const vo
     const uint32_t fpw = (uint32_t)std::max(1, kBlock / M), nf = namp / (uint32_t)M;
     st->maxblk = std::max(st->maxblk, (int)((nf + fpw - 1) / fpw));
   }
-  const int rows = std::max(2 + st->cap, P) + 2;
+  const int rows = (std::max(2 + st->cap, P) + 3) & ~1;  // even: the links behind them are read in pairs
+  std::vector<double> links;
+  if (small64_ok(st->d, st->namp, 0)) small64_links(st->d, links);
   auto fail = [&](int code) {
     release(st);
     delete st;
@@ -312,7 +350,7 @@ int adapt64_create(const fock_ham_t *ham, const fock_op_t *pool, int P, const vo
       hipMalloc(&st->lam, bs) != hipSuccess ||
       hipMalloc(&st->utab, sizeof(double2) * (size_t)st->cap * st->Mmax * st->Mmax) != hipSuccess ||
       hipMalloc(&st->partial, sizeof(double) * (size_t)rows * st->maxblk) != hipSuccess ||
-      hipMalloc(&st->res, sizeof(double) * rows) != hipSuccess ||
+      hipMalloc(&st->res, sizeof(double) * (rows + links.size())) != hipSuccess ||
       hipMalloc(&st->th_dev, sizeof(double) * st->cap) != hipSuccess ||
       hipMalloc(&st->recs, sizeof(GateRec) * st->cap) != hipSuccess)
     return fail(set_error(FOCK_ERR_HIP, "device allocation failed"));
@@ -322,6 +360,12 @@ int adapt64_create(const fock_ham_t *ham, const fock_op_t *pool, int P, const vo
   if (hipMemcpyAsync(st->psi0, psi0, bs, hipMemcpyDeviceToDevice, st->s) != hipSuccess)
     return fail(set_error(FOCK_ERR_HIP, "copy of psi0 failed"));
   if ((rc = get_tables(ham->d, &st->T))) return fail(rc);
+  if (!links.empty()) {
+    st->links = st->res + rows;
+    if (hipMemcpyAsync(st->links, links.data(), sizeof(double) * links.size(), hipMemcpyHostToDevice, st->s) != hipSuccess ||
+        hipHostMalloc(&st->host, kHost64, hipHostMallocDefault) != hipSuccess)
+      return fail(set_error(FOCK_ERR_HIP, "set-up of the small-state evaluation failed"));
+  }
   st->warm.iter = 0;
   st->warm.k_sel = -1;
   double E0 = 0.0, n2 = 0.0;

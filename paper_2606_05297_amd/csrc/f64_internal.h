@@ -1,5 +1,7 @@
-// FP64-state path: parameters and launchers (f64_kernels.hip).
+// FP64-state path: parameters and launchers (f64_kernels.hip, f64_small.hip).
 #pragma once
+
+#include <vector>
 
 #include "device_common.h"
 
@@ -30,5 +32,30 @@ int launch64_fib_pool(const Fib64 &a, const double2 *psi, const double2 *hpsi, c
 // Dense M x M tables of n gates at utab + recs[k].u_off (Mmax = largest M).
 int launch64_build(const double *theta, const GateRec *recs, int n, const EigTables &T, int Mmax, double2 *utab,
                    hipStream_t s);
+
+// One evaluation of a small state by one workgroup (f64_small.hip): psi0 through
+// the n gates, then (<phi|H phi>, <phi|phi>) into res[0..1] and, with grad,
+// Re<lam_k|A_k phi_k> into res[2 + k]; without grad the states go to phi and
+// lam.  theta, gates (type | i << 8 | j << 16, j = 255: single mode) and res are
+// host-visible; links: the rows of small64_links on the device.
+struct Small64 {
+  const double2 *psi0;
+  double2 *phi, *lam;
+  const double *theta;
+  const double2 *links;
+  const int *gates;
+  double *res;
+  int n, grad;
+  int cap, batch;  // gate tables in LDS at a time, built `batch` at a time (set by the launcher)
+};
+
+// States and circuits it takes: both states and a few gate tables in one
+// workgroup's LDS.
+bool small64_ok(int d, uint32_t namp, int n);
+// The diagonal and the links between levels of every generator at cutoff d.
+void small64_links(int d, std::vector<double> &out);
+int launch64_small(const Small64 &it, const H64 &h, const EigTables &T, hipStream_t s);
+// Circuits of at most so many gates.
+constexpr int kGates64 = 256;
 
 }  // namespace fock
