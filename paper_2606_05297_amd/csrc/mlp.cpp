@@ -15,7 +15,10 @@ struct fock_mlp {
   float *params = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr, *partial = nullptr;
   uint16_t *wb = nullptr;
   Count *cnt = nullptr;
-  double *lossp = nullptr, *loss = nullptr;
+  double *lossp = nullptr;
+  // host-visible, written by the update kernel: loss, gradient
+  double *loss = nullptr;
+  float *host_grad = nullptr;
   int step = 0;
 };
 
@@ -33,22 +36,20 @@ int check_batch(const fock_mlp *n, int B) {
   return FOCK_OK;
 }
 
-// Forward, backward and the loss of one batch; partials and the loss stay on
-// the device.  Returns the number of workgroup partials.
-int loss_grad_dev(fock_mlp *n, const float *X, const float *T, const int *nv, int B, hipStream_t s, int *nwg) {
-  int rc = launch_mlp_count(nv, B, n->cnt, s);
-  if (rc) return rc;
-  *nwg = (B + ROWS - 1) / ROWS;
+// Forward and backward of one batch, then the sums over workgroups: loss,
+// gradient (grad: device or host-visible) and, with ad.on, the Adam update.
+int train(fock_mlp *n, const float *X, const float *T, const int *nv, int B, const AdamArgs &ad, float *grad,
+          hipStream_t s) {
   {
     ProfScope ps(FOCK_K_MLP_TRAIN, s, 149504.0 * B);
-    rc = launch_mlp(true, weights_of(n), X, T, nv, n->cnt, B, nullptr, n->partial, n->lossp, s);
+    const int rc = launch_mlp(true, weights_of(n), X, T, nv, n->cnt, B, nullptr, n->partial, n->lossp, s);
     if (rc) return rc;
   }
-  return launch_mlp_loss(n->lossp, *nwg, n->cnt, n->loss, s);
+  return launch_mlp_update(n->partial, mlp_workgroups(B), grad, n->params, n->m, n->v, ad, n->wb, n->lossp, n->cnt,
+                           n->loss, s);
 }
 
-int fetch_loss(fock_mlp *n, double *loss, hipStream_t s) {
-  FOCK_HIP(hipMemcpyAsync(loss, n->loss, sizeof(double), hipMemcpyDeviceToHost, s));
+int finish(hipStream_t s) {
   FOCK_HIP(hipStreamSynchronize(s));
   prof_harvest();
   return FOCK_OK;
@@ -65,11 +66,11 @@ int fock_mlp_create(int max_batch, fock_mlp_t **out) {
     return set_error(FOCK_ERR_ARG, "max_batch %d outside [1, 2^20]", max_batch);
   fock_mlp *n = new fock_mlp;
   n->max_batch = max_batch;
-  n->max_wg = (max_batch + ROWS - 1) / ROWS;
+  n->max_wg = mlp_partials(max_batch);
   const size_t sp = al256(sizeof(float) * NPAR);
   const size_t sizes[] = {sp, sp, sp, sp, al256(sizeof(float) * NPAR * (size_t)n->max_wg),
                           al256(sizeof(uint16_t) * WB_TOTAL), al256(sizeof(Count)),
-                          al256(sizeof(double) * n->max_wg), al256(sizeof(double))};
+                          al256(sizeof(double) * n->max_wg)};
   size_t total = 0;
   for (size_t x : sizes) total += x;
   if (hipMalloc(&n->dev, total) != hipSuccess) {
@@ -84,9 +85,15 @@ int fock_mlp_create(int max_batch, fock_mlp_t **out) {
   n->partial = (float *)p, p += sizes[4];
   n->wb = (uint16_t *)p, p += sizes[5];
   n->cnt = (Count *)p, p += sizes[6];
-  n->lossp = (double *)p, p += sizes[7];
-  n->loss = (double *)p;
+  n->lossp = (double *)p;
+  if (hipHostMalloc(&n->loss, 256 + sizeof(float) * NPAR, hipHostMallocDefault) != hipSuccess) {
+    (void)hipFree(n->dev);
+    delete n;
+    return set_error(FOCK_ERR_HIP, "allocation of the network's result buffer failed");
+  }
+  n->host_grad = (float *)((char *)n->loss + 256);
   if (hipMemset(n->dev, 0, total) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+    (void)hipHostFree(n->loss);
     (void)hipFree(n->dev);
     delete n;
     return set_error(FOCK_ERR_HIP, "clearing the network buffers failed");
@@ -105,7 +112,7 @@ int fock_mlp_set_params(fock_mlp_t *n, const float *params, int count, fock_stre
   FOCK_HIP(hipMemsetAsync(n->m, 0, sizeof(float) * NPAR, s));
   FOCK_HIP(hipMemsetAsync(n->v, 0, sizeof(float) * NPAR, s));
   AdamArgs off{};
-  int rc = launch_mlp_update(n->partial, 0, n->grad, n->params, n->m, n->v, off, n->wb, s);
+  int rc = launch_mlp_update(n->partial, 0, n->grad, n->params, n->m, n->v, off, n->wb, n->lossp, n->cnt, n->loss, s);
   if (rc) return rc;
   FOCK_HIP(hipStreamSynchronize(s));  // params is a caller buffer: finish the copy before returning
   n->step = 0;
@@ -136,15 +143,12 @@ int fock_mlp_loss_grad(fock_mlp_t *n, const float *X, const float *T, const int 
   int rc = check_batch(n, B);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
-  int nwg = 0;
-  rc = loss_grad_dev(n, X, T, nvalid, B, s, &nwg);
-  if (rc) return rc;
   AdamArgs off{};
-  rc = launch_mlp_update(n->partial, nwg, n->grad, n->params, n->m, n->v, off, n->wb, s);
-  if (rc) return rc;
-  if (grad) FOCK_HIP(hipMemcpyAsync(grad, n->grad, sizeof(float) * NPAR, hipMemcpyDeviceToHost, s));
-  if (loss) return fetch_loss(n, loss, s);
-  if (grad) FOCK_HIP(hipStreamSynchronize(s));
+  rc = train(n, X, T, nvalid, B, off, grad ? n->host_grad : n->grad, s);
+  if (rc || (!grad && !loss)) return rc;
+  if ((rc = finish(s))) return rc;
+  if (grad) memcpy(grad, n->host_grad, sizeof(float) * NPAR);
+  if (loss) *loss = *n->loss;
   return FOCK_OK;
 }
 
@@ -155,9 +159,6 @@ int fock_mlp_adam_step(fock_mlp_t *n, const float *X, const float *T, const int 
   int rc = check_batch(n, B);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
-  int nwg = 0;
-  rc = loss_grad_dev(n, X, T, nvalid, B, s, &nwg);
-  if (rc) return rc;
   n->step += 1;
   AdamArgs ad;
   ad.on = 1;
@@ -167,9 +168,10 @@ int fock_mlp_adam_step(fock_mlp_t *n, const float *X, const float *T, const int 
   ad.eps = 1e-8f;
   ad.bc1 = (float)(1.0 - std::pow(0.9, n->step));
   ad.bc2 = (float)(1.0 - std::pow(0.999, n->step));
-  rc = launch_mlp_update(n->partial, nwg, n->grad, n->params, n->m, n->v, ad, n->wb, s);
-  if (rc) return rc;
-  if (loss) return fetch_loss(n, loss, s);
+  rc = train(n, X, T, nvalid, B, ad, n->grad, s);
+  if (rc || !loss) return rc;
+  if ((rc = finish(s))) return rc;
+  *loss = *n->loss;
   return FOCK_OK;
 }
 
@@ -177,6 +179,7 @@ int fock_mlp_destroy(fock_mlp_t *n) {
   if (!n) return FOCK_OK;
   (void)hipDeviceSynchronize();
   if (n->dev) (void)hipFree(n->dev);
+  if (n->loss) (void)hipHostFree(n->loss);
   delete n;
   return FOCK_OK;
 }

@@ -8,7 +8,10 @@ namespace mlp {
 
 constexpr int NIN = 4, NH = 128, NOUT = 64;
 constexpr int KIN = 32;   // layer-1 reduction padded to one MFMA step (entries >= NIN are zero)
-constexpr int ROWS = 64;  // batch rows per workgroup
+constexpr int kCUs = 256;
+// Batches up to so many rows have N summed by every workgroup (32 loads a thread
+// at most) instead of by a launch of its own.
+constexpr int kCountInline = 8192;
 
 // FP32 master parameters, in this order; W is [out x in] row-major.
 constexpr int OW1 = 0, OB1 = OW1 + NH * NIN, OW2 = OB1 + NH, OB2 = OW2 + NH * NH, OW3 = OB2 + NH,
@@ -35,12 +38,15 @@ struct AdamArgs {
   float lr, beta1, beta2, eps, bc1, bc2;
 };
 
-int launch_mlp(bool bwd, const Weights &w, const float *X, const float *T, const int *nvalid, const Count *cnt, int B,
+// Workgroups (and gradient partials) of a batch; the most of any batch up to max_batch.
+int mlp_workgroups(int B);
+int mlp_partials(int max_batch);
+// Forward, or (bwd) loss numerators and gradient partials, N into cnt.
+int launch_mlp(bool bwd, const Weights &w, const float *X, const float *T, const int *nvalid, Count *cnt, int B,
                float *Y, float *partial, double *lossp, hipStream_t s);
-int launch_mlp_count(const int *nvalid, int B, Count *cnt, hipStream_t s);
-int launch_mlp_loss(const double *lossp, int nwg, const Count *cnt, double *out, hipStream_t s);
 int launch_mlp_update(const float *partial, int nwg, float *grad, float *params, float *m, float *v,
-                      const AdamArgs &ad, uint16_t *wb, hipStream_t s);
+                      const AdamArgs &ad, uint16_t *wb, const double *lossp, const Count *cnt, double *loss,
+                      hipStream_t s);
 
 }  // namespace mlp
 }  // namespace fock
