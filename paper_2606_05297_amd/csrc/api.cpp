@@ -125,7 +125,7 @@ struct Pinned {
     return FOCK_OK;
   }
 };
-static thread_local Pinned tl_in, tl_out;
+static thread_local Pinned tl_in;
 
 // Results written by a kernel straight into host memory: fine-grained
 // (coherent) pinned memory, so the stream synchronisation that follows the
@@ -174,16 +174,12 @@ Layout make_layout(uint32_t namp, int Lm, int d, int P, int n, int half) {
   L.utab = o;
   o = al(o + sizeof(float2) * (size_t)gate_stride(d) * L.nmax);
   L.partial = o;
-  // gate rows, plus two rows after them for the energy partials of a gradient
-  // evaluation on real states (reduced with the gate rows)
-  const size_t rows = std::max<size_t>({2, (size_t)L.nmax + 2, (size_t)L.pmax});
+  // gate or pool rows, plus two rows after them for the energy partials (reduced
+  // with the others)
+  const size_t rows = (size_t)std::max(L.nmax, L.pmax) + 2;
   o = al(o + sizeof(double) * rows * std::max(L.G, L.rs));
   L.result = o;
   o = al(o + sizeof(double) * (2 + std::max(L.nmax, std::max(P, 1))));
-  L.pairs = o;
-  o = al(o + sizeof(PoolPair) * kMaxPairs);
-  L.diags = o;
-  o = al(o + sizeof(PoolDiag) * kMaxDiagOps);
   L.wdense = o;
   o = al(o + dense_w_bytes(d));
   L.total = o;
@@ -320,24 +316,40 @@ int forward_gate(Ctx &c, const fock_op_t &op, int k, bool dag, const float2 *src
   return launch_gate(c.g, op.i, op.j, gate_kind(op.type), dag, U, src, psi, c.s);
 }
 
-int apply_h_dev(Ctx &c, const float2 *psi, float2 *hpsi, double *res2) {
-  int G = 0;
-  {
-    ProfScope ps(FOCK_K_APPLY_H, c.s, 16.0 * c.g.n_amp);
-    int rc = c.h.slab ? launch_apply_h2(c.h, psi, hpsi, (double *)(c.ws + c.L.partial), &G, c.s)
-                      : launch_apply_h(c.h, psi, hpsi, (double *)(c.ws + c.L.partial), &G, c.s);
-    if (rc) return rc;
-  }
-  return launch_reduce((const double *)(c.ws + c.L.partial), G, 2, res2, c.s);
+// hpsi = H psi with the energy and norm partials (2 *G doubles) in part.
+static int apply_h_part(Ctx &c, const float2 *psi, float2 *hpsi, double *part, int *G) {
+  ProfScope ps(FOCK_K_APPLY_H, c.s, 16.0 * c.g.n_amp);
+  return c.h.slab ? launch_apply_h2(c.h, psi, hpsi, part, G, c.s) : launch_apply_h(c.h, psi, hpsi, part, G, c.s);
 }
 
-int fetch_results(Ctx &c, int count, double *host) {
-  int rc = tl_out.reserve(sizeof(double) * count);
-  if (rc) return rc;
-  FOCK_HIP(hipMemcpyAsync(tl_out.p, c.ws + c.L.result, sizeof(double) * count, hipMemcpyDeviceToHost, c.s));
+int apply_h_dev(Ctx &c, const float2 *psi, float2 *hpsi, double *res2) {
+  double *part = (double *)(c.ws + c.L.partial);
+  int G = 0;
+  const int rc = apply_h_part(c, psi, hpsi, part, &G);
+  return rc ? rc : launch_reduce(part, G, 2, res2, c.s);
+}
+
+// Row r of the partials; the two rows after the gates' or pool's hold the energy
+// partials until they are reduced with the others.
+static double *partial_row(Ctx &c, int r) { return (double *)(c.ws + c.L.partial) + (size_t)r * std::max(c.L.G, c.L.rs); }
+static int check_energy_rows(const Ctx &c, int G) {
+  if (G > std::max(c.L.G, c.L.rs)) return set_error(FOCK_ERR_SIZE, "energy partials beyond the workspace");
+  return FOCK_OK;
+}
+
+// Where the reductions of a call write its count results: host memory.  A copy of
+// its own after them costs 4 us on the device and as much before and after: 30
+// gates with gradients at L = 6, d = 8 take 266 us, 280 with the copy and the
+// energy's reduction apart.
+static int host_results(int count, double **res) {
+  const int rc = tl_res.reserve((size_t)count);
+  *res = tl_res.p;
+  return rc;
+}
+// The results are there once the stream is done.
+static int wait_results(Ctx &c) {
   FOCK_HIP(hipStreamSynchronize(c.s));
   prof_harvest();
-  memcpy(host, tl_out.p, sizeof(double) * count);
   return FOCK_OK;
 }
 
@@ -393,7 +405,7 @@ static float2 *stored_state(const Ctx &c, int k) { return c.store + (size_t)(k -
 // Reverse sweep with the forward states kept: gate k reads phi_k from the
 // store (read-only) and updates lam <- U_k^+ lam; 24 B per amplitude instead
 // of 32.
-static int reverse_sweep_stored(Ctx &c, const fock_op_t *ops, int n, float2 *lam, double *res) {
+static int reverse_sweep_stored(Ctx &c, const fock_op_t *ops, int n, float2 *lam, int Ge, double *res) {
   const float2 *utab = (const float2 *)(c.ws + c.L.utab);
   double *part = (double *)(c.ws + c.L.partial);
   const int stride = gate_stride(c.g.d);
@@ -409,14 +421,15 @@ static int reverse_sweep_stored(Ctx &c, const fock_op_t *ops, int n, float2 *lam
                                          pk, c.s, false);
     if (rc) return rc;
   }
-  return launch_reduce_rows(part, c.L.rs, (const GateRec *)(c.ws + c.L.recs), n, res, c.s);
+  return launch_reduce_rows_energy(part, c.L.rs, (const GateRec *)(c.ws + c.L.recs), n, partial_row(c, n), Ge, res, c.s);
 }
 
 // Reverse sweep from phi = psi_n, lam = H psi_n (both overwritten): per-gate
-// sums of Re<lam|A_k phi> reduced into res[0..n) (device), in stream order.
+// sums of Re<lam|A_k phi> reduced into res[0..n), in stream order; with Ge > 0
+// energy partials in the rows after the gates', (<H>, <1>) into res[0..1] and the
+// sums into res[2..).
 static int reverse_sweep(Ctx &c, const fock_op_t *ops, int n, const std::vector<GateGroup> &groups, float2 *phi,
-                         float2 *lam, double *res) {
-  if (n == 0) return FOCK_OK;
+                         float2 *lam, int Ge, double *res) {
   int rc = FOCK_OK;
   const float2 *utab = (const float2 *)(c.ws + c.L.utab);
   double *part = (double *)(c.ws + c.L.partial);
@@ -451,6 +464,9 @@ static int reverse_sweep(Ctx &c, const fock_op_t *ops, int n, const std::vector<
       if (rc) return rc;
     }
   }
+  if (Ge > 0)
+    return launch_reduce_rows_energy(part, c.L.rs, (const GateRec *)(c.ws + c.L.recs), n, partial_row(c, n), Ge, res,
+                                     c.s);
   return launch_reduce_rows(part, c.L.rs, (const GateRec *)(c.ws + c.L.recs), n, res, c.s);
 }
 
@@ -639,30 +655,17 @@ static int forward_real(Ctx &c, const fock_op_t *ops, int n, const std::vector<R
   return launch_real_convert(c.g.n_amp, true, c.phi_r, phi, c.s);
 }
 
-// H phi_r into lam_r and (<psi|H psi>, <psi|psi>) into res2, on real states;
-// with defer, the energy partials go to the two rows after the n gate rows
-// and *G receives their count, for reverse_real's reduction.
-static int apply_h_real(Ctx &c, double *res2, int n = 0, bool defer = false, int *Gout = nullptr) {
-  int G = 0;
-  double *part = (double *)(c.ws + c.L.partial) + (defer ? (size_t)n * c.L.rs : 0);
-  {
-    ProfScope ps(FOCK_K_APPLY_H_REAL, c.s, 8.0 * c.g.n_amp);
-    const int rc = launch_apply_h2_real(c.h, c.phi_r, c.lam_r, part, &G, c.s);
-    if (rc) return rc;
-  }
-  if (defer) {
-    if (G > std::max(c.L.G, c.L.rs) || n > c.L.nmax)  // rows n, n + 1 hold the 2 G partials
-      return set_error(FOCK_ERR_SIZE, "energy partials beyond the workspace");
-    *Gout = G;
-    return FOCK_OK;
-  }
-  return launch_reduce(part, G, 2, res2, c.s);
+// H phi_r into lam_r on real states, energy and norm partials (2 *G) in part.
+static int apply_h_real(Ctx &c, double *part, int *G) {
+  ProfScope ps(FOCK_K_APPLY_H_REAL, c.s, 8.0 * c.g.n_amp);
+  return launch_apply_h2_real(c.h, c.phi_r, c.lam_r, part, G, c.s);
 }
 
 // Reverse sweep on real states from phi_r and lam_r = H phi_r: per gate the
-// partial sums of lam . A phi, then phi_r, lam_r <- U^T phi_r, U^T lam_r.
-static int reverse_real(Ctx &c, const fock_op_t *ops, int n, const std::vector<RealRun> &runs, double *res,
-                        int Ge = 0) {
+// partial sums of lam . A phi, then phi_r, lam_r <- U^T phi_r, U^T lam_r.  The
+// sums go to res[2..), with the energy partials in the rows after the gates'
+// reduced to res[0..1].
+static int reverse_real(Ctx &c, const fock_op_t *ops, int n, const std::vector<RealRun> &runs, int Ge, double *res) {
   const float2 *utab = (const float2 *)(c.ws + c.L.utab);
   double *part = (double *)(c.ws + c.L.partial);
   const int stride = gate_stride(c.g.d);
@@ -683,10 +686,7 @@ static int reverse_real(Ctx &c, const fock_op_t *ops, int n, const std::vector<R
     }
     if (rc) return rc;
   }
-  if (Ge > 0)  // with the energy partials of apply_h_real(defer): res[0..1] and res[2..]
-    return launch_reduce_rows_energy(part, c.L.rs, (const GateRec *)(c.ws + c.L.recs), n, part + (size_t)n * c.L.rs,
-                                     Ge, res, c.s);
-  return launch_reduce_rows(part, c.L.rs, (const GateRec *)(c.ws + c.L.recs), n, res, c.s);
+  return launch_reduce_rows_energy(part, c.L.rs, (const GateRec *)(c.ws + c.L.recs), n, partial_row(c, n), Ge, res, c.s);
 }
 
 // ---------------------------------------------------------------- small states
@@ -745,11 +745,12 @@ int run_score(Ctx &c, const fock_op_t *ops, const double *theta, int n, const vo
               float2 *lam, const fock_op_t *pool, int P, double *E, double *norm2, double *g) {
   std::vector<GateGroup> groups;
   std::vector<RealRun> runs;
-  double *res = (double *)(c.ws + c.L.result);
-  int rc;
+  double *res = nullptr;
+  int rc = host_results(2 + P, &res);
+  if (rc) return rc;
   if (small_used(c, n)) {  // leaves phi and H phi, and the energy and norm in res
     if ((rc = enqueue_small(c, ops, theta, n, psi0, phi, lam, false, res))) return rc;
-    if ((rc = pool_dev(c, pool, P, phi, lam, res + 2))) return rc;
+    if ((rc = pool_dev(c, pool, P, phi, lam, res + 2, 0))) return rc;
   } else {
     if (real_eval(c, ops, n)) {
       const RealCircuit o = real_order(c.g, ops, theta, n);
@@ -761,14 +762,13 @@ int run_score(Ctx &c, const fock_op_t *ops, const double *theta, int n, const vo
     }
     if ((rc = score_dev(c, pool, P, phi, lam, res))) return rc;
   }
-  std::vector<double> host(2 + P);
-  if ((rc = fetch_results(c, 2 + P, host.data()))) return rc;
-  const double nrm = host[1];
-  if (!std::isfinite(host[0]) || !std::isfinite(nrm) || nrm <= 0.0)
-    return set_error(FOCK_ERR_NONFINITE, "non-finite energy or zero norm (E=%g, norm2=%g)", host[0], nrm);
-  *E = host[0] / nrm;
+  if ((rc = wait_results(c))) return rc;
+  const double nrm = res[1];
+  if (!std::isfinite(res[0]) || !std::isfinite(nrm) || nrm <= 0.0)
+    return set_error(FOCK_ERR_NONFINITE, "non-finite energy or zero norm (E=%g, norm2=%g)", res[0], nrm);
+  *E = res[0] / nrm;
   if (norm2) *norm2 = nrm;
-  for (int k = 0; k < P; ++k) g[k] = host[2 + k];
+  for (int k = 0; k < P; ++k) g[k] = res[2 + k];
   return FOCK_OK;
 }
 
@@ -788,13 +788,12 @@ static int finish_eval(const double *res, int n, bool grad, double *E, double *n
 // Energy and (optionally) all dE/dtheta of a circuit; see fock_energy_grad_adjoint.
 int run_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int n, const void *psi0, float2 *phi,
                        float2 *lam, bool grad, double *E, double *norm2, double *dE) {
+  double *res = nullptr;
+  int rc = host_results(2 + n, &res);
+  if (rc) return rc;
   if (small_used(c, n)) {
-    int rc = tl_res.reserve(2 + (size_t)n);
-    if (rc) return rc;
-    if ((rc = enqueue_small(c, ops, theta, n, psi0, phi, lam, grad, tl_res.p))) return rc;
-    FOCK_HIP(hipStreamSynchronize(c.s));
-    prof_harvest();
-    return finish_eval(tl_res.p, n, grad, E, norm2, dE);
+    if ((rc = enqueue_small(c, ops, theta, n, psi0, phi, lam, grad, res)) || (rc = wait_results(c))) return rc;
+    return finish_eval(res, n, grad, E, norm2, dE);
   }
   std::vector<GateGroup> groups;
   std::vector<RealRun> runs;
@@ -812,53 +811,39 @@ int run_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int n, const 
     for (int k = 0; k < n; ++k) dE[order.at[k]] = g[k];
     return r;
   };
-  int rc = real ? stage_real(c, ops, theta, n, &runs) : stage_circuit(c, ops, theta, n, &groups);
-  if (rc) return rc;
-  double *res = (double *)(c.ws + c.L.result);
+  if ((rc = real ? stage_real(c, ops, theta, n, &runs) : stage_circuit(c, ops, theta, n, &groups))) return rc;
+  // With gradients one reduction gives the energy, the norm and all of them.
+  const bool rev = grad && n > 0;
+  double *const epart = partial_row(c, n);
+  int Ge = 0;
   if (real) {
     // H psi on the real states when the slab passes take them, else on a
     // complex64 copy whose real part is kept
     const bool rh = apply_h2_real_supported(c.h) && c.h.slab;
     if ((rc = forward_real(c, ops, n, runs, rh ? nullptr : phi))) return rc;
-    if (rh && grad && n > 0) {  // one reduction for the energy, the norm and all gradients,
-      int Ge = 0;                 // written straight into host memory
-      if ((rc = tl_res.reserve(2 + (size_t)n))) return rc;
-      if ((rc = apply_h_real(c, res, n, true, &Ge))) return rc;
-      if ((rc = reverse_real(c, ops, n, runs, tl_res.p, Ge))) return rc;
-      FOCK_HIP(hipStreamSynchronize(c.s));
-      prof_harvest();
-      return finish(tl_res.p);
+    if (rh) {
+      if ((rc = apply_h_real(c, epart, &Ge))) return rc;
     } else {
-      if (rh) {
-        if ((rc = apply_h_real(c, res))) return rc;
-      } else {
-        if ((rc = apply_h_dev(c, phi, lam, res))) return rc;
-        if (grad && n > 0) {
-          ProfScope ps(FOCK_K_CONVERT, c.s, 12.0 * c.g.n_amp);
-          if ((rc = launch_real_convert(c.g.n_amp, false, lam, c.lam_r, c.s))) return rc;
-        }
+      if ((rc = apply_h_part(c, phi, lam, epart, &Ge))) return rc;
+      if (rev) {
+        ProfScope ps(FOCK_K_CONVERT, c.s, 12.0 * c.g.n_amp);
+        if ((rc = launch_real_convert(c.g.n_amp, false, lam, c.lam_r, c.s))) return rc;
       }
-      if (grad && n > 0 && (rc = reverse_real(c, ops, n, runs, res + 2))) return rc;
     }
+    if ((rc = check_energy_rows(c, Ge))) return rc;
+    rc = rev ? reverse_real(c, ops, n, runs, Ge, res) : launch_reduce(epart, Ge, 2, res, c.s);
   } else if (grad && use_store(c, ops, n, groups)) {
     // forward states kept: H psi_n reads the last one; phi is not touched
     if ((rc = forward_stored(c, ops, n, psi0))) return rc;
-    if ((rc = apply_h_dev(c, stored_state(c, n), lam, res))) return rc;
-    if ((rc = reverse_sweep_stored(c, ops, n, lam, res + 2))) return rc;
+    if ((rc = apply_h_part(c, stored_state(c, n), lam, epart, &Ge)) || (rc = check_energy_rows(c, Ge))) return rc;
+    rc = reverse_sweep_stored(c, ops, n, lam, Ge, res);
   } else {
     if ((rc = forward_circuit(c, ops, n, groups, psi0, phi))) return rc;
-    rc = apply_h_dev(c, phi, lam, res);
-    if (rc) return rc;
-    if (grad && n > 0) {
-      rc = reverse_sweep(c, ops, n, groups, phi, lam, res + 2);
-      if (rc) return rc;
-    }
+    if ((rc = apply_h_part(c, phi, lam, epart, &Ge)) || (rc = check_energy_rows(c, Ge))) return rc;
+    rc = rev ? reverse_sweep(c, ops, n, groups, phi, lam, Ge, res) : launch_reduce(epart, Ge, 2, res, c.s);
   }
-  const int cnt = 2 + ((grad && n > 0) ? n : 0);
-  std::vector<double> host(cnt);
-  rc = fetch_results(c, cnt, host.data());
-  if (rc) return rc;
-  return finish(host.data());
+  if (rc || (rc = wait_results(c))) return rc;
+  return finish(res);
 }
 
 // All dE/dtheta by the reverse sweep alone, from phi = psi_n and lam = H psi_n
@@ -869,12 +854,9 @@ int run_reverse(Ctx &c, const fock_op_t *ops, const double *theta, int n, float2
   std::vector<GateGroup> groups;
   int rc = stage_circuit(c, ops, theta, n, &groups);
   if (rc || n == 0) return rc;
-  double *res = (double *)(c.ws + c.L.result);
-  rc = reverse_sweep(c, ops, n, groups, phi, lam, res);
-  if (rc) return rc;
-  std::vector<double> host(n);
-  rc = fetch_results(c, n, host.data());
-  if (rc) return rc;
+  double *host = nullptr;
+  if ((rc = host_results(n, &host)) || (rc = reverse_sweep(c, ops, n, groups, phi, lam, 0, host))) return rc;
+  if ((rc = wait_results(c))) return rc;
   for (int k = 0; k < n; ++k) {
     if (!std::isfinite(host[k])) return set_error(FOCK_ERR_NONFINITE, "non-finite gradient entry %d", k);
     dE[k] = 2.0 * host[k] / norm2;
@@ -949,18 +931,25 @@ int score_dev(Ctx &c, const fock_op_t *pool, int P, const float2 *psi, float2 *h
       int rc = launch_score_slab(sp, c.h, psi, hpsi, hpart, ppart, c.s);
       if (rc) return rc;
     }
-    int rc = launch_reduce(hpart, apply_h2_blocks(c.h), 2, res, c.s);
-    if (rc) return rc;
-    return launch_reduce(ppart, pool_slab_blocks(c.h), P, res + 2, c.s);
+    return launch_reduce_score(hpart, apply_h2_blocks(c.h), res, ppart, pool_slab_blocks(c.h), P, res + 2, c.s);
   }
   if (c.g.half) return set_error(FOCK_ERR_UNSUPPORTED, "pool outside the slab scoring in the parity-halved layout");
-  int rc = apply_h_dev(c, psi, hpsi, res);
-  if (rc) return rc;
-  return pool_dev(c, pool, P, psi, hpsi, res + 2);
+  int Ge = 0;
+  int rc = apply_h_part(c, psi, hpsi, partial_row(c, c.L.pmax), &Ge);
+  if (rc || (rc = check_energy_rows(c, Ge))) return rc;
+  return pool_dev(c, pool, P, psi, hpsi, res + 2, Ge);
 }
 
-// Pool gradients 2 Re <hpsi|A_k psi> into res[0..P) on the device.
-int pool_dev(Ctx &c, const fock_op_t *pool, int P, const float2 *psi, const float2 *hpsi, double *res) {
+// Pool gradients 2 Re <hpsi|A_k psi> into res[0..P).  Ge > 0 energy partials in
+// the rows after the pool's are reduced along into res[-2..-1].
+int pool_dev(Ctx &c, const fock_op_t *pool, int P, const float2 *psi, const float2 *hpsi, double *res, int Ge) {
+  // one launch for a chunk's columns and, the first time, the energy's
+  auto reduce = [&](const double *p, int G, int cols, double *out) {
+    const int ne = Ge;
+    Ge = 0;
+    return ne > 0 ? launch_reduce_score(partial_row(c, c.L.pmax), ne, res - 2, p, G, cols, out, c.s)
+                  : launch_reduce(p, G, cols, out, c.s);
+  };
   if (c.g.half) {  // one slab chunk: nearest-neighbour pairs only
     SlabPool sp;
     if (!slab_pool_of(c, pool, P, &sp))
@@ -972,7 +961,7 @@ int pool_dev(Ctx &c, const fock_op_t *pool, int P, const float2 *psi, const floa
       int rc = launch_pool_slab(sp, c.h, psi, hpsi, part, &G, c.s);
       if (rc) return rc;
     }
-    return launch_reduce(part, G, P, res, c.s);
+    return reduce(part, G, P, res);
   }
   PoolArgs a;
   memset(&a, 0, sizeof(a));
@@ -1057,7 +1046,7 @@ int pool_dev(Ctx &c, const fock_op_t *pool, int P, const float2 *psi, const floa
           int rc = launch_pool_slab(sp, c.h, psi, hpsi, part, &G, c.s);
           if (rc) return rc;
         }
-        int rc = launch_reduce(part, G, sp.nslots, res + k0, c.s);
+        int rc = reduce(part, G, sp.nslots, res + k0);
         if (rc) return rc;
         for (int k : sq) {
           const fock_op_t &op = pool[k];
@@ -1067,7 +1056,7 @@ int pool_dev(Ctx &c, const fock_op_t *pool, int P, const float2 *psi, const floa
             rc = launch_pool1(c.g, op.i, c.T.A1[op.type == FOCK_SR ? 0 : 1], psi, hpsi, part, &G1, c.s);
             if (rc) return rc;
           }
-          rc = launch_reduce(part, G1, 1, res + k, c.s);
+          rc = reduce(part, G1, 1, res + k);
           if (rc) return rc;
         }
         k0 = k1;
@@ -1077,24 +1066,18 @@ int pool_dev(Ctx &c, const fock_op_t *pool, int P, const float2 *psi, const floa
     a.npairs = (int)pairs.size();
     a.ndiag = (int)diags.size();
     a.nslots = k1 - k0;
-    int rc = tl_in.reserve(c.L.diags + sizeof(PoolDiag) * kMaxDiagOps);
-    if (rc) return rc;
-    char *hp = (char *)tl_in.p;
-    if (!pairs.empty()) memcpy(hp + c.L.pairs, pairs.data(), sizeof(PoolPair) * pairs.size());
-    if (!diags.empty()) memcpy(hp + c.L.diags, diags.data(), sizeof(PoolDiag) * diags.size());
-    FOCK_HIP(hipMemcpyAsync(c.ws + c.L.pairs, hp + c.L.pairs, c.L.diags + sizeof(PoolDiag) * kMaxDiagOps - c.L.pairs,
-                            hipMemcpyHostToDevice, c.s));
-    rc = tl_in.mark(c.s);
-    if (rc) return rc;
+    int rc = FOCK_OK;
     if (!pairs.empty() || !diags.empty()) {  // a chunk of squeezer entries only needs no stencil pass
       int G = 0;
       {
         ProfScope ps(FOCK_K_POOL, c.s, 16.0 * c.g.n_amp);
-        rc = launch_pool(a, (const PoolPair *)(c.ws + c.L.pairs), (const PoolDiag *)(c.ws + c.L.diags), psi, hpsi,
-                         part, &G, c.s);
+        PoolLists lists;
+        std::copy(pairs.begin(), pairs.end(), lists.pair);
+        std::copy(diags.begin(), diags.end(), lists.diag);
+        rc = launch_pool(a, lists, psi, hpsi, part, &G, c.s);
         if (rc) return rc;
       }
-      rc = launch_reduce(part, G, a.nslots, res + k0, c.s);
+      rc = reduce(part, G, a.nslots, res + k0);
       if (rc) return rc;
     }
     for (int k : sq) {  // stream order: after the chunk's reduction has read the partials
@@ -1105,7 +1088,7 @@ int pool_dev(Ctx &c, const fock_op_t *pool, int P, const float2 *psi, const floa
         rc = launch_pool1(c.g, op.i, c.T.A1[op.type == FOCK_SR ? 0 : 1], psi, hpsi, part, &G1, c.s);
         if (rc) return rc;
       }
-      rc = launch_reduce(part, G1, 1, res + k, c.s);
+      rc = reduce(part, G1, 1, res + k);
       if (rc) return rc;
     }
     k0 = k1;
@@ -1143,8 +1126,7 @@ int fock_prepare(int L, int d) {
   }
   // pinned staging of this thread at its minimum size, and its results buffer
   if ((rc = tl_in.reserve(1))) return rc;
-  if ((rc = tl_res.reserve(kHostResults))) return rc;
-  return tl_out.reserve(1);
+  return tl_res.reserve(kHostResults);
 }
 
 int fock_workspace_bytes(const fock_ham_t *ham, int n_pool, int n_ops, size_t *bytes) {
@@ -1168,22 +1150,21 @@ int fock_apply_H(const fock_ham_t *ham, const void *psi, void *hpsi, double *E, 
   Ctx c;
   rc = make_ctx(*ham, namp, 0, 0, ws, ws_bytes, (hipStream_t)stream, &c);
   if (rc) return rc;
-  double *res = (double *)(c.ws + c.L.result);
+  double *res = (double *)(c.ws + c.L.result);  // not asked for: no wait, no use of host memory
+  if ((E || norm2) && (rc = host_results(2, &res))) return rc;
   if (ham->layout & FOCK_LAYOUT_REAL) {
     c.phi_r = (float *)const_cast<void *>(psi);
     c.lam_r = (float *)hpsi;
-    rc = apply_h_real(c, res);
+    int G = 0;
+    rc = apply_h_real(c, (double *)(c.ws + c.L.partial), &G);
+    if (!rc) rc = launch_reduce((double *)(c.ws + c.L.partial), G, 2, res, c.s);
   } else {
     rc = apply_h_dev(c, (const float2 *)psi, (float2 *)hpsi, res);
   }
-  if (rc) return rc;
-  if (E || norm2) {
-    double h2[2];
-    rc = fetch_results(c, 2, h2);
-    if (rc) return rc;
-    if (E) *E = h2[0];
-    if (norm2) *norm2 = h2[1];
-  }
+  if (rc || !(E || norm2)) return rc;
+  if ((rc = wait_results(c))) return rc;
+  if (E) *E = res[0];
+  if (norm2) *norm2 = res[1];
   return FOCK_OK;
 }
 
@@ -1311,9 +1292,12 @@ int fock_pool_grads(const fock_ham_t *ham, const fock_op_t *pool, int P, const v
   Ctx c;
   rc = make_ctx(*ham, namp, P, 0, ws, ws_bytes, (hipStream_t)stream, &c);
   if (rc) return rc;
-  rc = pool_dev(c, pool, P, (const float2 *)psi, (const float2 *)hpsi, (double *)(c.ws + c.L.result));
-  if (rc) return rc;
-  return fetch_results(c, P, grads);
+  double *res = nullptr;
+  if ((rc = host_results(P, &res)) || (rc = pool_dev(c, pool, P, (const float2 *)psi, (const float2 *)hpsi, res, 0)))
+    return rc;
+  if ((rc = wait_results(c))) return rc;
+  std::copy(res, res + P, grads);
+  return FOCK_OK;
 }
 
 int fock_energy_grad_adjoint(const fock_ham_t *ham, const fock_op_t *ops, const double *theta, int n,
@@ -1393,15 +1377,13 @@ int fock_score(const fock_ham_t *ham, const fock_op_t *pool, int P, const void *
       if (rc) return rc;
       break;
     }
-  double *res = (double *)(c.ws + c.L.result);
-  rc = score_dev(c, pool, P, (const float2 *)psi, (float2 *)hpsi, res);
-  if (rc) return rc;
-  std::vector<double> host(2 + P);
-  rc = fetch_results(c, 2 + P, host.data());
-  if (rc) return rc;
-  if (E) *E = host[0];
-  if (norm2) *norm2 = host[1];
-  for (int k = 0; k < P; ++k) grads[k] = host[2 + k];
+  double *res = nullptr;
+  if ((rc = host_results(2 + P, &res)) || (rc = score_dev(c, pool, P, (const float2 *)psi, (float2 *)hpsi, res)))
+    return rc;
+  if ((rc = wait_results(c))) return rc;
+  if (E) *E = res[0];
+  if (norm2) *norm2 = res[1];
+  std::copy(res + 2, res + 2 + P, grads);
   return FOCK_OK;
 }
 

@@ -66,6 +66,11 @@ struct PoolPair {
 struct PoolDiag {
   int16_t r, type, slot, r2;  // KERR / ROT on mode r (r2 = -1), CK on modes (r, r2)
 };
+// A chunk's entries, passed to the pool pass as kernel arguments (2.9 KB).
+struct PoolLists {
+  PoolPair pair[kMaxPairs];
+  PoolDiag diag[kMaxDiagOps];
+};
 // Pool entries scored by the slab kernels (L = 8, d = 8): slot[p][type] for
 // the pairs p = 0..6 ~ (p, p + 1) and p = 7 ~ the ring pair (0, 7), types
 // HR..PI (-1 = absent); up to kSlabDiag diagonal entries (KERR, ROT, CK).
@@ -190,7 +195,7 @@ int apply_h_blocks(const HamArgs &h);
 // Rows per workgroup tile of the stencil-type kernels (apply-H, pool gradients).
 int apply_h_tile_rows(int L, int d);
 int apply_h_hi_modes(int L, int d, int periodic_wrap);
-int launch_pool(const PoolArgs &a, const PoolPair *pairs, const PoolDiag *diags, const float2 *psi,
+int launch_pool(const PoolArgs &a, const PoolLists &lists, const float2 *psi,
                 const float2 *hpsi, double *partial, int *nblocks, hipStream_t s);
 int pool_blocks(const PoolArgs &a);
 int launch_gate_build(const double *theta, const GateRec *recs, int n, const EigTables &T, float2 *utab,
@@ -255,6 +260,10 @@ int launch_reduce(const double *partial, int nblocks, int ncols, double *out, hi
 // out[k] = sum_{b < recs[k].nblk} partial[k * row_stride + b] for k < n, in a fixed order.
 int launch_reduce_rows(const double *partial, int row_stride, const GateRec *recs, int n, double *out,
                        hipStream_t s);
+// launch_reduce of a pool pass and of the energy / norm partials epart (two
+// columns of ne rows, into eout[0], eout[1]), one launch.
+int launch_reduce_score(const double *epart, int ne, double *eout, const double *partial, int nblocks, int ncols,
+                        double *out, hipStream_t s);
 // The gate rows (into out[2 + k]) and the energy / norm partials epart (two
 // columns of ne rows, into out[0], out[1]) of a gradient evaluation, one launch.
 int launch_reduce_rows_energy(const double *partial, int row_stride, const GateRec *recs, int n,

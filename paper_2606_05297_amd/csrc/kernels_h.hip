@@ -101,6 +101,28 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rows_e(const double *__restri
   if (threadIdx.x == 0) out[k < n ? 2 + k : k - n] = s;
 }
 
+// Columns of a pool pass, and (workgroups 0, 1) the two of the energy partials.
+__global__ __launch_bounds__(kBlock) void k_reduce_score(const double *__restrict__ epart, int ne, double *__restrict__ eout,
+                                                         const double *__restrict__ partial, int nblocks, int ncols,
+                                                         double *__restrict__ out) {
+  __shared__ double red[4];
+  const bool energy = blockIdx.x < 2;
+  const int c = energy ? blockIdx.x : blockIdx.x - 2, cols = energy ? 2 : ncols, nb = energy ? ne : nblocks;
+  const double *p = energy ? epart : partial;
+  double s = 0.0;
+  for (int b = threadIdx.x; b < nb; b += kBlock) s += p[(size_t)b * cols + c];
+  s = block_sum_d(s, red);
+  if (threadIdx.x == 0) (energy ? eout : out)[c] = s;
+}
+
+int launch_reduce_score(const double *epart, int ne, double *eout, const double *partial, int nblocks, int ncols,
+                        double *out, hipStream_t s) {
+  if (ne <= 0 || ncols <= 0) return set_error(FOCK_ERR_ARG, "reduction of %d columns and %d energy partials", ncols, ne);
+  hipLaunchKernelGGL(k_reduce_score, dim3(2 + ncols), dim3(kBlock), 0, s, epart, ne, eout, partial, nblocks, ncols, out);
+  FOCK_HIP(hipGetLastError());
+  return FOCK_OK;
+}
+
 int launch_reduce_rows_energy(const double *partial, int row_stride, const GateRec *recs, int n,
                               const double *epart, int ne, double *out, hipStream_t s) {
   if (n < 0 || ne <= 0) return set_error(FOCK_ERR_ARG, "reduction of %d rows and %d energy partials", n, ne);

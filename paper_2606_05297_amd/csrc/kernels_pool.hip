@@ -22,30 +22,28 @@ namespace fock {
 
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_pool(const float2 *__restrict__ psi, const float2 *__restrict__ hpsi,
-                                                 double *__restrict__ partial, PoolArgs a,
-                                                 const PoolPair *__restrict__ pairs,
-                                                 const PoolDiag *__restrict__ diags) {
+                                                 double *__restrict__ partial, PoolArgs a, PoolLists lists) {
   __shared__ double acc[4][kMaxSlots];
   __shared__ float4 tile4[(PTile<D>::MAXROWS * PTile<D>::RS + 1) / 2];
-  pool_block<D>(a.order ? a.order[blockIdx.x] : xcd_remap(blockIdx.x, gridDim.x), psi, hpsi, partial, a, pairs, diags,
+  pool_block<D>(a.order ? a.order[blockIdx.x] : xcd_remap(blockIdx.x, gridDim.x), psi, hpsi, partial, a, lists.pair, lists.diag,
                 reinterpret_cast<float2 *>(tile4), acc);
 }
 
 int pool_blocks(const PoolArgs &a) { return a.nrows / apply_h_tile_rows(a.L, a.d); }
 
 template <int D>
-static void launch_pool_t(const PoolArgs &a, const PoolPair *pairs, const PoolDiag *diags, const float2 *psi,
+static void launch_pool_t(const PoolArgs &a, const PoolLists &lists, const float2 *psi,
                           const float2 *hpsi, double *partial, int G, hipStream_t s) {
-  hipLaunchKernelGGL(k_pool<D>, dim3(G), dim3(kBlock), 0, s, psi, hpsi, partial, a, pairs, diags);
+  hipLaunchKernelGGL(k_pool<D>, dim3(G), dim3(kBlock), 0, s, psi, hpsi, partial, a, lists);
 }
 
-int launch_pool(const PoolArgs &a, const PoolPair *pairs, const PoolDiag *diags, const float2 *psi,
-                const float2 *hpsi, double *partial, int *nblocks, hipStream_t s) {
+int launch_pool(const PoolArgs &a, const PoolLists &lists, const float2 *psi, const float2 *hpsi,
+                double *partial, int *nblocks, hipStream_t s) {
   const int G = pool_blocks(a);
   *nblocks = G;
   switch (a.d) {
 #define CASE(D) \
-  case D: launch_pool_t<D>(a, pairs, diags, psi, hpsi, partial, G, s); break;
+  case D: launch_pool_t<D>(a, lists, psi, hpsi, partial, G, s); break;
     CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(11) CASE(12) CASE(13)
     CASE(14) CASE(15) CASE(16)
 #undef CASE

@@ -7,7 +7,7 @@
 namespace fock {
 
 struct Layout {
-  size_t theta = 0, recs = 0, utab = 0, partial = 0, result = 0, pairs = 0, diags = 0, wdense = 0, total = 0;
+  size_t theta = 0, recs = 0, utab = 0, partial = 0, result = 0, wdense = 0, total = 0;
   int G = 0;     // blocks of the row-parallel kernels
   int rs = 0;    // row stride of the per-gate reverse-step partials
   int nmax = 0;  // gates
@@ -59,7 +59,6 @@ SmallItem small_item(const HamArgs &h, uint32_t namp, int n, bool grad);
 // psi <- O_k src (src == psi: in place)
 int forward_gate(Ctx &c, const fock_op_t &op, int k, bool dag, const float2 *src, float2 *psi);
 int apply_h_dev(Ctx &c, const float2 *psi, float2 *hpsi, double *res2);
-int fetch_results(Ctx &c, int count, double *host);
 // Energy (Rayleigh quotient) and optionally all dE/dtheta of ops/theta applied to psi0.
 int run_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int n, const void *psi0, float2 *phi,
                 float2 *lam, bool grad, double *E, double *norm2, double *dE);
@@ -71,9 +70,10 @@ int run_reverse(Ctx &c, const fock_op_t *ops, const double *theta, int n, float2
 int run_score(Ctx &c, const fock_op_t *ops, const double *theta, int n, const void *psi0, float2 *phi,
               float2 *lam, const fock_op_t *pool, int P, double *E, double *norm2, double *g);
 // H psi, (<psi|H psi>, <psi|psi>) into res[0..1] and the pool gradients into
-// res[2..2+P) (device); fused slab scoring where the pool allows it.
+// res[2..2+P); fused slab scoring where the pool allows it.
 int score_dev(Ctx &c, const fock_op_t *pool, int P, const float2 *psi, float2 *hpsi, double *res);
-// 2 Re <hpsi|A_k psi> for the pool into res[0..P) (device).
-int pool_dev(Ctx &c, const fock_op_t *pool, int P, const float2 *psi, const float2 *hpsi, double *res);
+// 2 Re <hpsi|A_k psi> for the pool into res[0..P); Ge: energy partials to reduce
+// along (0: none).
+int pool_dev(Ctx &c, const fock_op_t *pool, int P, const float2 *psi, const float2 *hpsi, double *res, int Ge);
 
 }  // namespace fock
