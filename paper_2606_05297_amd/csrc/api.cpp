@@ -173,6 +173,8 @@ Layout make_layout(uint32_t namp, int Lm, int d, int P, int n, int half) {
   o = al(o + sizeof(GateRec) * L.nmax);
   L.utab = o;
   o = al(o + sizeof(float2) * (size_t)gate_stride(d) * L.nmax);
+  L.rtab = o;
+  if (fuse_supported(d)) o = al(o + sizeof(float) * (size_t)fuse_table(d) * L.nmax);
   L.partial = o;
   // gate or pool rows, plus two rows after them for the energy partials (reduced
   // with the others)
@@ -221,6 +223,9 @@ int make_ctx(const fock_ham_t &ham, uint32_t namp, int P, int n, void *ws, size_
   return FOCK_OK;
 }
 
+static float *rtab_of(Ctx &c) { return fuse_supported(c.g.d) ? (float *)(c.ws + c.L.rtab) : nullptr; }
+static FuseTables tables_of(Ctx &c) { return {(const float2 *)(c.ws + c.L.utab), (const float *)(c.ws + c.L.rtab)}; }
+
 int stage_gates(Ctx &c, const fock_op_t *ops, const double *theta, int n, const int *nblk) {
   const int stride = gate_stride(c.g.d);
   if (n <= kArgGates) {  // angles and records ride in the build kernel's arguments
@@ -237,7 +242,7 @@ int stage_gates(Ctx &c, const fock_op_t *ops, const double *theta, int n, const 
       r.nblk = nblk && nblk[k] > 0 ? nblk[k] : is_single_mode(ops[k].type) ? Gd : gate_blocks_count(c.g, ops[k].i);
       r.modes = gate_modes(ops[k]);
     }
-    return launch_gate_build_args(ga, c.T, (float2 *)(c.ws + c.L.utab), (double *)(c.ws + c.L.theta),
+    return launch_gate_build_args(ga, c.T, (float2 *)(c.ws + c.L.utab), rtab_of(c), (double *)(c.ws + c.L.theta),
                                   (GateRec *)(c.ws + c.L.recs), c.s);
   }
   const size_t bt = sizeof(double) * n, br = sizeof(GateRec) * n;
@@ -260,7 +265,7 @@ int stage_gates(Ctx &c, const fock_op_t *ops, const double *theta, int n, const 
   rc = tl_in.mark(c.s);
   if (rc) return rc;
   return launch_gate_build((const double *)(c.ws + c.L.theta), (const GateRec *)(c.ws + c.L.recs), n, c.T,
-                           (float2 *)(c.ws + c.L.utab), c.s);
+                           (float2 *)(c.ws + c.L.utab), rtab_of(c), c.s);
 }
 
 static std::atomic<int> g_state_store{FOCK_STORE_AUTO};
@@ -446,7 +451,7 @@ static int reverse_sweep(Ctx &c, const fock_op_t *ops, int n, const std::vector<
     }
     if (gr.s > 0 && reverse_fused()) {
       ProfScope ps(FOCK_K_ADJ, c.s, 32.0 * c.g.n_amp);
-      rc = launch_fuse_adj(make_fuse_args(c.g, c.T, gr, ops), phi, lam, utab, part, c.L.rs, c.s);
+      rc = launch_fuse_adj(make_fuse_args(c.g, c.T, gr, ops), phi, lam, tables_of(c), part, c.L.rs, c.s);
       if (rc) return rc;
       continue;
     }
@@ -497,7 +502,7 @@ static int forward_circuit(Ctx &c, const fock_op_t *ops, int n, const std::vecto
       rc = forward_gate(c, ops[gr.k.front()], gr.k.front(), false, src, phi);
     } else {
       ProfScope ps(FOCK_K_GATE, c.s, 16.0 * c.g.n_amp);
-      rc = launch_fuse_fwd(make_fuse_args(c.g, c.T, gr, ops), src, phi, utab, c.s);
+      rc = launch_fuse_fwd(make_fuse_args(c.g, c.T, gr, ops), src, phi, tables_of(c), c.s);
     }
     if (rc) return rc;
   }

@@ -198,9 +198,10 @@ int apply_h_hi_modes(int L, int d, int periodic_wrap);
 int launch_pool(const PoolArgs &a, const PoolLists &lists, const float2 *psi,
                 const float2 *hpsi, double *partial, int *nblocks, hipStream_t s);
 int pool_blocks(const PoolArgs &a);
-int launch_gate_build(const double *theta, const GateRec *recs, int n, const EigTables &T, float2 *utab,
+// rtab (nullable): the fuse_table of every gate as well.
+int launch_gate_build(const double *theta, const GateRec *recs, int n, const EigTables &T, float2 *utab, float *rtab,
                       hipStream_t s);
-int launch_gate_build_args(const GateArgs &ga, const EigTables &T, float2 *utab, double *theta_out,
+int launch_gate_build_args(const GateArgs &ga, const EigTables &T, float2 *utab, float *rtab, double *theta_out,
                            GateRec *recs_out, hipStream_t s);
 // psi <- U src (dag = false) or U^+ src (dag = true) for a two-mode gate on
 // (i, j); src == psi applies it in place.

@@ -11,12 +11,34 @@ constexpr int kMaxFuseModes = 13;   // tile modes
 constexpr int kMaxFuseGates = 16;   // gates per run
 constexpr int kTileMaxAmps = 8192;  // amplitudes of a tile
 
+// LDS position of a tile's local index a.  At power-of-two d the five low bits are
+// mixed with higher ones: 32 consecutive fibres of any mode pair of a 4-mode tile
+// at d = 8 then lie in 32 different 8-byte banks (6 modes at d = 4: 1.3 to a
+// bank).  Linear over bits, and a fibre's base and a member's offset have no bits
+// in common: their positions combine by exclusive or.
+__host__ __device__ constexpr int run_pos(int d, int a) {
+  return (d & (d - 1)) == 0 ? a ^ (((a >> 3) ^ (a >> 5) ^ (a >> 6)) & 31) : a;
+}
+
 struct FuseGate {
   int type;
   int ki, kj;  // tile positions of the gate's modes (kj = -1: single-mode gate on ki)
   int u_off;   // offset of the gate's table in the gate-table block
   int k;       // index of the gate in the circuit (row of its gradient partials)
   TilePair p;  // local strides of its modes (tile_pair; a single mode with its next stride)
+  // LDS byte offsets (8 run_pos) of 1, 2 and 4 levels of its modes
+  int bi[3], bj[3];
+};
+
+// A gate's entries as a fused run reads them (fibre_gate.h): group g's at g d^2,
+// the block of rows n_i <= g, then the other, one float an entry (the real part,
+// or where A is imaginary and row and column are an odd number of levels apart
+// the imaginary one); CK: (re, im) of the group's d members.
+__host__ __device__ constexpr int fuse_table(int d) { return d * d * d; }
+// The gate tables of a circuit: u by FuseGate::u_off, r by FuseGate::k.
+struct FuseTables {
+  const float2 *u;
+  const float *r;
 };
 
 struct FuseArgs {
@@ -49,8 +71,8 @@ FuseArgs make_fuse_args(const Geometry &g, const EigTables &T, const GateGroup &
 // Wavefronts and dynamic LDS of a run's workgroups.
 int fuse_waves(int D, int T);
 size_t fuse_lds(const FuseArgs &a, bool rev);
-int launch_fuse_fwd(const FuseArgs &a, const float2 *src, float2 *dst, const float2 *utab, hipStream_t s);
-int launch_fuse_adj(const FuseArgs &a, float2 *phi, float2 *lam, const float2 *utab, double *partial, int rs,
+int launch_fuse_fwd(const FuseArgs &a, const float2 *src, float2 *dst, const FuseTables &tab, hipStream_t s);
+int launch_fuse_adj(const FuseArgs &a, float2 *phi, float2 *lam, const FuseTables &tab, double *partial, int rs,
                     hipStream_t s);
 
 }  // namespace fock

@@ -23,19 +23,22 @@ unsigned mode_mask(const fock_op_t &o) { return (1u << o.i) | (o.j >= 0 ? 1u << 
 }  // namespace
 
 // Modes of a fused run's tile: as many as the LDS of one workgroup holds (both
-// states of the reverse sweep, kTileMaxAmps each) while 128 tiles are left to
-// keep the chip busy; a state too small for that takes up to four modes while 32
-// tiles are left.  Measured, an evaluation in us: 8^6, 4 modes (64 tiles) 308, 3
-// (512) 318; 6^6, 4 modes (36) 267, 3 (216) 281; 4^8, 4 modes (256) 237, 5 (64)
-// 224, 6 (16) 299; 5^8, 4 modes (625) 247, 5 (125) 338.
+// states of the reverse sweep, kTileMaxAmps each) while 100 tiles are left to
+// keep the chip busy, but never so few that a wavefront's lanes (a fibre each,
+// d^(s - 2) of them) stay empty: half of them filled on a handful of CUs is faster
+// than many CUs with few, and the longer runs save passes.  Measured, an
+// evaluation in us by modes (tiles): 8^5 4 (8) 217, 3 (64) 293; 5^6 5 (5) 137,
+// 4 (25) 153, 3 (125) 184; 7^5 4 (7) 158, 3 (49) 198; 3^9 6 (27) 200, 5 (81) 219;
+// 4^8 5 (64) 215, 4 (256) 240; 5^8 5 (125) 206, 4 (625) 220; 6^8 5 (216) 455, 4
+// (1296) 603; but 6^7 5 (36) 315, 4 (216) 276; 6^6 5 (6) 290, 4 (36) 237.
 int fuse_modes(const Geometry &g) {
   const int Lf = g.half ? g.L - 1 : g.L;
-  int s128 = 0, s32 = 0, s = 1;
+  int many = 0, full = 0, s = 1;
   for (long T = g.d; s <= Lf && s <= kMaxFuseModes && T <= kTileMaxAmps; T *= g.d, ++s) {
-    if ((long)g.n_amp / T >= 128) s128 = s;
-    if ((long)g.n_amp / T >= 32 && s <= 4) s32 = s;
+    if ((long)g.n_amp / T >= 100) many = s;
+    if (!full && T / (g.d * g.d) >= 32 && (long)g.n_amp / T >= 4) full = s;
   }
-  return std::max(s128, s32);
+  return std::max(many, full);
 }
 
 std::vector<GateGroup> plan_gate_groups(const Geometry &g, const fock_op_t *ops, int n, bool fuse) {
@@ -126,6 +129,10 @@ FuseArgs make_fuse_args(const Geometry &g, const EigTables &T, const GateGroup &
     for (int e = 0; e < f.ki; ++e) si *= d;
     for (int e = 0; e < (f.kj < 0 ? f.ki + 1 : f.kj); ++e) sj *= d;
     f.p = tile_pair(si, sj, d);
+    for (int b = 0; b < 3; ++b) {
+      f.bi[b] = 8 * run_pos(d, si << b);
+      f.bj[b] = 8 * run_pos(d, sj << b);
+    }
   }
   return a;
 }

@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <cstring>
 
+#include "fuse_internal.h"
 #include "gate_kernels.h"
 
 namespace fock {
@@ -29,9 +30,10 @@ FOCK_GATE_EXTERN(12) FOCK_GATE_EXTERN(13) FOCK_GATE_EXTERN(14) FOCK_GATE_EXTERN(
 // Entries [blockIdx.x * kBlock, + kBlock) of gate table r at angle th.  The gate's
 // phases exp(i th lambda_m) come first, one per thread, into LDS: each entry of a
 // block of b members needs b of them, and b FP64 sine-cosines in a row were most
-// of this latency-bound kernel's time (30 gates at d = 8: 6.3 -> 5.4 us).
+// of this latency-bound kernel's time (30 gates at d = 8: 6.3 -> 5.4 us).  rtab
+// (nullable): the gate's fuse_table.
 __device__ __forceinline__ void gate_build_part(const GateRec &r, double th, const EigTables &T,
-                                                float2 *__restrict__ utab) {
+                                                float2 *__restrict__ utab, float *__restrict__ rtab) {
   __shared__ double2 ph[kMaxD * kMaxD];
   const int d = T.d, e = blockIdx.x * kBlock + threadIdx.x;
   const bool phase = r.type == FOCK_KERR || r.type == FOCK_ROT, squeeze = r.type == FOCK_SR || r.type == FOCK_SI;
@@ -51,12 +53,12 @@ __device__ __forceinline__ void gate_build_part(const GateRec &r, double th, con
   }
   // U[p][q] = sum_m V[p][m] e^{i th lam_m} conj(V[q][m]) over the entry's block
   // (squeezers: the whole d x d matrix)
-  int off = 0, loff = 0, b = d;
+  int off = 0, loff = 0, b = d, s = 0;
   if (squeeze) {
     if (e >= d * d) return;
   } else {
     if (e >= T.psize) return;
-    for (int s = 0; s <= 2 * d - 2; ++s) {
+    for (; s <= 2 * d - 2; ++s) {
       b = blk_hi(KIND_SUM, d, s) - blk_lo(KIND_SUM, d, s) + 1;
       if (e < off + b * b) break;
       off += b * b;
@@ -75,21 +77,34 @@ __device__ __forceinline__ void gate_build_part(const GateRec &r, double th, con
     ui += ti * qr - tr * qi;
   }
   utab[r.u_off + e] = make_float2((float)ur, (float)ui);
+  if (!rtab || squeeze) return;
+  const int g = s < d ? s : s - d;
+  float *const out = rtab + (size_t)g * d * d;
+  if (r.type == FOCK_CK) {
+    const int m = s < d ? p : g + 1 + p;  // n_i
+    if (p == q) {
+      out[2 * m] = (float)ur;
+      out[2 * m + 1] = (float)ui;
+    }
+  } else {
+    const bool im = ((p - q) & 1) && r.type != FOCK_HR && r.type != FOCK_PR;
+    out[(s < d ? 0 : (g + 1) * (g + 1)) + e - off] = (float)(im ? ui : ur);
+  }
 }
 
 __global__ __launch_bounds__(kBlock) void k_gate_build(const double *__restrict__ theta,
                                                        const GateRec *__restrict__ recs, int n, EigTables T,
-                                                       float2 *__restrict__ utab) {
+                                                       float2 *__restrict__ utab, float *__restrict__ rtab) {
   const int k = blockIdx.y;
   if (k >= n) return;
-  gate_build_part(recs[k], theta[k], T, utab);
+  gate_build_part(recs[k], theta[k], T, utab, rtab ? rtab + (size_t)k * fuse_table(T.d) : nullptr);
 }
 
 // The same with the angles and records in the kernel arguments (no staging
 // copy); workgroup (0, k) also stores gate k's record and angle for the
 // kernels that read them later (the reduction of the reverse-step partials).
 __global__ __launch_bounds__(kBlock) void k_gate_build_args(GateArgs ga, EigTables T, float2 *__restrict__ utab,
-                                                            double *__restrict__ theta_out,
+                                                            float *__restrict__ rtab, double *__restrict__ theta_out,
                                                             GateRec *__restrict__ recs_out) {
   const int k = blockIdx.y;
   if (k >= ga.n) return;
@@ -99,24 +114,24 @@ __global__ __launch_bounds__(kBlock) void k_gate_build_args(GateArgs ga, EigTabl
     theta_out[k] = th;
     recs_out[k] = r;
   }
-  gate_build_part(r, th, T, utab);
+  gate_build_part(r, th, T, utab, rtab ? rtab + (size_t)k * fuse_table(T.d) : nullptr);
 }
 
-int launch_gate_build_args(const GateArgs &ga, const EigTables &T, float2 *utab, double *theta_out,
+int launch_gate_build_args(const GateArgs &ga, const EigTables &T, float2 *utab, float *rtab, double *theta_out,
                            GateRec *recs_out, hipStream_t s) {
   if (ga.n <= 0) return FOCK_OK;
   if (ga.n > kArgGates) return set_error(FOCK_ERR_SIZE, "%d gates in the kernel arguments (at most %d)", ga.n, kArgGates);
   const int ex = (T.psize + kBlock - 1) / kBlock;
-  hipLaunchKernelGGL(k_gate_build_args, dim3(ex, ga.n), dim3(kBlock), 0, s, ga, T, utab, theta_out, recs_out);
+  hipLaunchKernelGGL(k_gate_build_args, dim3(ex, ga.n), dim3(kBlock), 0, s, ga, T, utab, rtab, theta_out, recs_out);
   FOCK_HIP(hipGetLastError());
   return FOCK_OK;
 }
 
-int launch_gate_build(const double *theta, const GateRec *recs, int n, const EigTables &T, float2 *utab,
+int launch_gate_build(const double *theta, const GateRec *recs, int n, const EigTables &T, float2 *utab, float *rtab,
                       hipStream_t s) {
   if (n <= 0) return FOCK_OK;
   const int ex = (T.psize + kBlock - 1) / kBlock;
-  hipLaunchKernelGGL(k_gate_build, dim3(ex, n), dim3(kBlock), 0, s, theta, recs, n, T, utab);
+  hipLaunchKernelGGL(k_gate_build, dim3(ex, n), dim3(kBlock), 0, s, theta, recs, n, T, utab, rtab);
   FOCK_HIP(hipGetLastError());
   return FOCK_OK;
 }

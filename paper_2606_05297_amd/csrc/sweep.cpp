@@ -66,6 +66,7 @@ struct DGroup {
   double *theta = nullptr;
   GateRec *recs = nullptr;
   float2 *utab = nullptr;
+  float *rtab = nullptr;  // the same for fused runs (cutoffs that have them)
   size_t theta_off = 0;  // offset (doubles) of this group's angles in the upload block
 };
 
@@ -217,6 +218,7 @@ int build_lists(fock_sweep *sw, const std::vector<char> &sel, bool grad, Lists *
         r.phi = P.phi;
         r.lam = P.lam;
         r.utab = utab;
+        r.rtab = G.rtab + (size_t)P.gate_base * fuse_table(G.d);
         r.partial = P.partial;
         for (int q : gr.k) nblk[q] = r.a.ntile;
         const int waves = fuse_waves(r.a.d, r.a.T);
@@ -330,7 +332,7 @@ int enqueue_eval(fock_sweep *sw, const Lists &Ls, bool grad, bool upload) {
     FOCK_HIP(hipMemcpyAsync(sw->up_d, pin_up(sw), sizeof(double) * sw->n_up, hipMemcpyHostToDevice, s));
     FOCK_HIP(hipMemcpyAsync(sw->active_d, pin_active(sw), sizeof(int) * sw->pts.size(), hipMemcpyHostToDevice, s));
     for (auto &G : sw->groups) {
-      int rc = launch_gate_build(G.theta, G.recs, G.ngates, G.T, G.utab, s);
+      int rc = launch_gate_build(G.theta, G.recs, G.ngates, G.T, G.utab, G.rtab, s);
       if (rc) return rc;
     }
   }
@@ -797,6 +799,7 @@ int fock_sweep_create(const fock_sweep_point_t *pts, int npts, const fock_adapt_
     G.theta_off = sw->n_up;
     sw->n_up += G.ngates;
     bytes += al256(sizeof(GateRec) * G.ngates) + al256(sizeof(float2) * (size_t)gate_stride(G.d) * G.ngates);
+    if (fuse_supported(G.d)) bytes += al256(sizeof(float) * (size_t)fuse_table(G.d) * G.ngates);
   }
   const size_t up_off = bytes;
   bytes += al256(sizeof(double) * sw->n_up);
@@ -817,6 +820,10 @@ int fock_sweep_create(const fock_sweep_point_t *pts, int npts, const fock_adapt_
     goff += al256(sizeof(GateRec) * G.ngates);
     G.utab = (float2 *)(b + goff);
     goff += al256(sizeof(float2) * (size_t)gate_stride(G.d) * G.ngates);
+    if (fuse_supported(G.d)) {
+      G.rtab = (float *)(b + goff);
+      goff += al256(sizeof(float) * (size_t)fuse_table(G.d) * G.ngates);
+    }
     G.theta = sw->up_d + G.theta_off;
     if ((rc = get_tables(G.d, &G.T))) break;
   }

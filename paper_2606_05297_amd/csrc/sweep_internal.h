@@ -62,6 +62,7 @@ struct SweepRun {
   GPtr<float2> phi;
   GPtr<float2> lam;
   CPtr<const float2> utab;
+  CPtr<const float> rtab;
   GPtr<double> partial;
 };
 

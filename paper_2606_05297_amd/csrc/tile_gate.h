@@ -1,6 +1,7 @@
 // Gates and reverse steps on a tile of amplitudes in LDS, on the FP32 matrix
-// cores: the code shared by the whole-circuit evaluation of small states
-// (small_eval.hip) and the fused runs of gates on larger ones (tile_runs.hip).
+// cores: the code of the whole-circuit evaluation of small states
+// (small_eval.hip), which have too few fibres for a lane each (fibre_gate.h), and
+// the sums that it shares with the fused runs of gates on larger ones.
 //
 // A tile holds the amplitudes over a few modes (all D levels each, local index
 // a = sum_k n_k D^k).  A two-mode gate on tile modes (i, j) mixes, in each of
