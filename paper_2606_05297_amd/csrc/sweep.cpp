@@ -82,7 +82,6 @@ struct fock_sweep {
   hipEvent_t fork = nullptr, join[kSideStreams] = {};
   void *dbuf = nullptr;
   int *active_d = nullptr;
-  double *res_d = nullptr;
   double *up_d = nullptr;  // device upload block: angles of all groups
   size_t n_up = 0, n_res = 0;
   void *pin = nullptr;  // pinned: [angles][active flags][results]
@@ -329,16 +328,33 @@ int enqueue_eval(fock_sweep *sw, const Lists &Ls, bool grad, bool upload) {
   hipStream_t s = sw->s;
   char *base = (char *)sw->items_d;
   if (upload) {
-    FOCK_HIP(hipMemcpyAsync(sw->up_d, pin_up(sw), sizeof(double) * sw->n_up, hipMemcpyHostToDevice, s));
-    FOCK_HIP(hipMemcpyAsync(sw->active_d, pin_active(sw), sizeof(int) * sw->pts.size(), hipMemcpyHostToDevice, s));
+    // angles and active flags, adjacent here and there
+    FOCK_HIP(hipMemcpyAsync(sw->up_d, pin_up(sw), al256(sizeof(double) * sw->n_up) + sizeof(int) * sw->pts.size(),
+                            hipMemcpyHostToDevice, s));
     for (auto &G : sw->groups) {
       int rc = launch_gate_build(G.theta, G.recs, G.ngates, G.T, G.utab, G.rtab, s);
       if (rc) return rc;
     }
   }
-  int chains = (int)Ls.small.size();
-  for (const GroupLists &GL : Ls.g) chains += !GL.h.v.empty();
-  const int nside = chains > 1 ? std::min(chains - 1, kSideStreams) : 0;  // the first chain stays on s
+  // Side by side only where that saves more than the fork and the join cost (about
+  // 40 us a round): the chains' times, in us, from the kernels' measured ones.  A
+  // sweep of four short chains takes 34 ms with side streams and 39 without, of two
+  // short ones 17.9 - 19.2 and 16.9 - 17.2.
+  int chains = 0;
+  double total = 0.0, longest = 0.0;
+  auto chain_of = [&](double us) {
+    ++chains;
+    total += us;
+    longest = std::max(longest, us);
+  };
+  for (const GroupLists &GL : Ls.g)
+    if (!GL.h.v.empty()) chain_of(25.0 + (grad ? 24.0 : 10.0) * (double)GL.layers.size());
+  for (const DevList<SmallItem> &l : Ls.small) {
+    double us = 0.0;
+    for (const SmallItem &it : l.v) us = std::max(us, 10.0 + it.n * (1.2 + 8.5e-4 * it.N));
+    chain_of(us);
+  }
+  const int nside = total - longest > 40.0 ? std::min(chains - 1, kSideStreams) : 0;  // the first chain stays on s
   if (nside > 0) FOCK_HIP(hipEventRecord(sw->fork, s));
   for (int b = 0; b < nside; ++b) FOCK_HIP(hipStreamWaitEvent(sw->side[b], sw->fork, 0));
   int chain = 0;
@@ -395,7 +411,6 @@ int enqueue_eval(fock_sweep *sw, const Lists &Ls, bool grad, bool upload) {
   }
   for (int b = 0; b < nside; ++b) FOCK_HIP(hipEventRecord(sw->join[b], sw->side[b]));
   for (int b = 0; b < nside; ++b) FOCK_HIP(hipStreamWaitEvent(s, sw->join[b], 0));
-  FOCK_HIP(hipMemcpyAsync(pin_res(sw), sw->res_d, sizeof(double) * sw->n_res, hipMemcpyDeviceToHost, s));
   return FOCK_OK;
 }
 
@@ -679,7 +694,6 @@ int score_phase(fock_sweep *sw, const std::vector<char> &sel, std::vector<std::v
   }
   rc = sweep_launch_reduce((const SweepRItem *)(base + ro), (int)red.size(), sw->active_d, sw->grid, sw->s);
   if (rc) return rc;
-  FOCK_HIP(hipMemcpyAsync(pin_res(sw), sw->res_d, sizeof(double) * sw->n_res, hipMemcpyDeviceToHost, sw->s));
   FOCK_HIP(hipStreamSynchronize(sw->s));
   const double *r = pin_res(sw);
   grads->assign(sw->pts.size(), {});
@@ -803,9 +817,7 @@ int fock_sweep_create(const fock_sweep_point_t *pts, int npts, const fock_adapt_
   }
   const size_t up_off = bytes;
   bytes += al256(sizeof(double) * sw->n_up);
-  const size_t res_off = bytes;
-  bytes += al256(sizeof(double) * sw->n_res);
-  const size_t act_off = bytes;
+  const size_t act_off = bytes;  // right after the angles: one upload
   bytes += al256(sizeof(int) * npts);
   if (hipMalloc(&sw->dbuf, bytes) != hipSuccess) {
     fock_sweep_destroy(sw);
@@ -813,7 +825,6 @@ int fock_sweep_create(const fock_sweep_point_t *pts, int npts, const fock_adapt_
   }
   char *b = (char *)sw->dbuf;
   sw->up_d = (double *)(b + up_off);
-  sw->res_d = (double *)(b + res_off);
   sw->active_d = (int *)(b + act_off);
   for (auto &G : sw->groups) {
     G.recs = (GateRec *)(b + goff);
@@ -843,7 +854,7 @@ int fock_sweep_create(const fock_sweep_point_t *pts, int npts, const fock_adapt_
     P.partial = (double *)(pb + 3 * sb);
     P.pairs = (PoolPair *)(pb + 3 * sb + al256(sizeof(double) * rows * std::max(P.G, P.rs)));
     P.diags = (PoolDiag *)((char *)P.pairs + al256(sizeof(PoolPair) * kMaxPairs));
-    P.res = sw->res_d + P.res_off;
+    P.res = pin_res(sw) + P.res_off;  // the reductions write to host memory
     if (hipMemcpyAsync(P.psi0, pts[p].psi0, sizeof(float2) * P.g.n_amp, hipMemcpyDeviceToDevice, sw->s) !=
         hipSuccess)
       rc = set_error(FOCK_ERR_HIP, "copy of psi0 failed");
