@@ -14,9 +14,18 @@ __device__ __forceinline__ int xcd_remap(int b, int G) {
   return (b & 7) * q + (b >> 3);
 }
 
-__device__ __forceinline__ float wave_sum_f(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// Sum over the wavefront by DPP moves (no LDS traffic), valid in lane 63.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add_f(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ float wave_total_f(float v) {
+  v = dpp_add_f<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: lane 15 of each row of 16 holds the row's sum
+  v = dpp_add_f<0x112, 0xf>(v);
+  v = dpp_add_f<0x114, 0xf>(v);
+  v = dpp_add_f<0x118, 0xf>(v);
+  v = dpp_add_f<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+  v = dpp_add_f<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
   return v;
 }
 

@@ -789,8 +789,8 @@ __device__ __forceinline__ void pool_block(int vb, const float2 *__restrict__ ps
 #pragma unroll
     for (int t = 0; t < 5; ++t) {
       if (pp.slot[t] >= 0) {
-        const float v = wave_sum_f(vals[t]);
-        if (lane == 0) acc[wave][pp.slot[t]] += (double)v;
+        const float v = wave_total_f(vals[t]);
+        if (lane == 63) acc[wave][pp.slot[t]] = (double)v;
       }
     }
   }
@@ -820,8 +820,8 @@ __device__ __forceinline__ void pool_block(int vb, const float2 *__restrict__ ps
         v = fmaf(f, s, v);
       }
     }
-    v = wave_sum_f(-2.f * v);
-    if (lane == 0) acc[wave][pd.slot] += (double)v;
+    v = wave_total_f(-2.f * v);
+    if (lane == 63) acc[wave][pd.slot] = (double)v;
   }
   __syncthreads();
   for (int k = threadIdx.x; k < a.nslots; k += kBlock)
