@@ -223,10 +223,10 @@ int make_ctx(const fock_ham_t &ham, uint32_t namp, int P, int n, void *ws, size_
   return FOCK_OK;
 }
 
-static float *rtab_of(Ctx &c) { return fuse_supported(c.g.d) ? (float *)(c.ws + c.L.rtab) : nullptr; }
 static FuseTables tables_of(Ctx &c) { return {(const float2 *)(c.ws + c.L.utab), (const float *)(c.ws + c.L.rtab)}; }
 
-int stage_gates(Ctx &c, const fock_op_t *ops, const double *theta, int n, const int *nblk) {
+int stage_gates(Ctx &c, const fock_op_t *ops, const double *theta, int n, const int *nblk, bool runs) {
+  float *const rtab = runs ? (float *)(c.ws + c.L.rtab) : nullptr;  // the tables of fused runs
   const int stride = gate_stride(c.g.d);
   if (n <= kArgGates) {  // angles and records ride in the build kernel's arguments
     GateArgs ga;
@@ -242,7 +242,7 @@ int stage_gates(Ctx &c, const fock_op_t *ops, const double *theta, int n, const 
       r.nblk = nblk && nblk[k] > 0 ? nblk[k] : is_single_mode(ops[k].type) ? Gd : gate_blocks_count(c.g, ops[k].i);
       r.modes = gate_modes(ops[k]);
     }
-    return launch_gate_build_args(ga, c.T, (float2 *)(c.ws + c.L.utab), rtab_of(c), (double *)(c.ws + c.L.theta),
+    return launch_gate_build_args(ga, c.T, (float2 *)(c.ws + c.L.utab), rtab, (double *)(c.ws + c.L.theta),
                                   (GateRec *)(c.ws + c.L.recs), c.s);
   }
   const size_t bt = sizeof(double) * n, br = sizeof(GateRec) * n;
@@ -265,7 +265,7 @@ int stage_gates(Ctx &c, const fock_op_t *ops, const double *theta, int n, const 
   rc = tl_in.mark(c.s);
   if (rc) return rc;
   return launch_gate_build((const double *)(c.ws + c.L.theta), (const GateRec *)(c.ws + c.L.recs), n, c.T,
-                           (float2 *)(c.ws + c.L.utab), rtab_of(c), c.s);
+                           (float2 *)(c.ws + c.L.utab), rtab, c.s);
 }
 
 static std::atomic<int> g_state_store{FOCK_STORE_AUTO};
@@ -386,11 +386,14 @@ static int stage_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int 
   *groups = plan_gate_groups(c.g, ops, n, fused_runs(c));
   if (n == 0) return FOCK_OK;
   std::vector<int> nblk(n, 0);
-  if (reverse_fused())
-    for (const GateGroup &gr : *groups)
-      if (gr.s > 0)
-        for (int k : gr.k) nblk[k] = fuse_tiles(c.g, gr);
-  return stage_gates(c, ops, theta, n, nblk.data());
+  bool runs = false;
+  for (const GateGroup &gr : *groups) {
+    if (gr.s == 0) continue;
+    runs = true;
+    if (reverse_fused())
+      for (int k : gr.k) nblk[k] = fuse_tiles(c.g, gr);
+  }
+  return stage_gates(c, ops, theta, n, nblk.data(), runs);
 }
 
 // True when a gradient evaluation of this circuit can keep its forward states:

@@ -53,7 +53,8 @@ int make_ctx(const fock_ham_t &ham, uint32_t namp, int P, int n, void *ws, size_
 // Attach a store of nmax forward states to c if switched on and the device has
 // room; *owner receives the allocation to free (nullptr: no store).
 int attach_state_store(Ctx &c, int nmax, void **owner);
-int stage_gates(Ctx &c, const fock_op_t *ops, const double *theta, int n, const int *nblk);
+// Tables of the gates, with those that fused runs read if `runs`.
+int stage_gates(Ctx &c, const fock_op_t *ops, const double *theta, int n, const int *nblk, bool runs = false);
 // An evaluation's item with the lattice filled in (small_eval.h).
 SmallItem small_item(const HamArgs &h, uint32_t namp, int n, bool grad);
 // psi <- O_k src (src == psi: in place)
