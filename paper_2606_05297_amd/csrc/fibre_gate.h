@@ -40,9 +40,18 @@ template <int D>
 __device__ __forceinline__ int run_at(int base, int off) {
   return (D & (D - 1)) == 0 ? base ^ off : base + off;
 }
-__device__ __forceinline__ float2 &run_amp(float2 *x, int byte) {
-  return *reinterpret_cast<float2 *>(reinterpret_cast<char *>(x) + byte);
+// An amplitude at an LDS address: phi's start plus its byte offset, so that a
+// member costs one instruction (an exclusive or combines positions because phi
+// starts at 0: dynamic LDS is all that the kernels have).  As pointers a member
+// cost an addition more: 30 gates with gradients at 8^6 250 us, now 235, at 8^8
+// 1,720 and 1,630.
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) f2 LdsAmp;
+__device__ __forceinline__ float2 amp_load(int byte) {
+  const f2 v = *(const LdsAmp *)(uint32_t)byte;
+  return make_float2(v.x, v.y);
 }
+__device__ __forceinline__ void amp_store(int byte, float2 v) { *(LdsAmp *)(uint32_t)byte = f2{v.x, v.y}; }
 
 // A gate's modes: byte offsets of 1, 2 and 4 levels of mode i and of mode j
 // (other D: of one level).  Scalars.
@@ -118,10 +127,10 @@ __device__ __forceinline__ float block_links(KFloat *A, const float2 (&x)[D], co
 }
 
 // Group G of one wavefront's fibres: phi <- U phi, or (REV) phi, lam <- U^+ and
-// this lane's share of Re<lam|A phi>.  u: the group's table; A: the generator's
+// this lane's share of Re<lam|A phi>.  lam: distance from phi in bytes; u: the group's table; A: the generator's
 // packed blocks; base: the lane's fibre (in: it has one).
 template <int D, int G, bool SUM, bool IM, bool REV>
-__device__ __forceinline__ float fibre_group(float2 *phi, float2 *lam, KFloat *u, KFloat *A, ModeStep<D> st,
+__device__ __forceinline__ float fibre_group(int lam, KFloat *u, KFloat *A, ModeStep<D> st,
                                              int base, bool in) {
   pin_steps<D>(st);
   constexpr int B0 = G + 1, B1 = D - 1 - G;
@@ -135,13 +144,13 @@ __device__ __forceinline__ float fibre_group(float2 *phi, float2 *lam, KFloat *u
 #pragma unroll
   for (int m = 0; m < D; ++m) {
     at[m] = run_at<D>(base, member_off<D>(st, G, m, SUM));
-    x[m] = run_amp(phi, at[m]);
+    x[m] = amp_load(at[m]);
   }
   float s = 0.f;
   if constexpr (REV) {
     float2 l[D], z[D];
 #pragma unroll
-    for (int m = 0; m < D; ++m) l[m] = run_amp(lam, at[m]);
+    for (int m = 0; m < D; ++m) l[m] = amp_load(at[m] + lam);
     s = block_links<D, 0, B0, IM>(A + 2 * block_off<D>(G), x, l);
     if constexpr (B1 > 0) s += block_links<D, B0, B1, IM>(A + 2 * block_off<D>(G + D), x, l);
     block_rows<D, 0, B0, IM, true>(u0, x, y);
@@ -153,8 +162,8 @@ __device__ __forceinline__ float fibre_group(float2 *phi, float2 *lam, KFloat *u
     if (in) {
 #pragma unroll
       for (int m = 0; m < D; ++m) {
-        run_amp(phi, at[m]) = y[m];
-        run_amp(lam, at[m]) = z[m];
+        amp_store(at[m], y[m]);
+        amp_store(at[m] + lam, z[m]);
       }
     }
   } else {
@@ -162,7 +171,7 @@ __device__ __forceinline__ float fibre_group(float2 *phi, float2 *lam, KFloat *u
     if constexpr (B1 > 0) block_rows<D, B0, B1, IM, false>(u1, x, y);
     if (in) {
 #pragma unroll
-      for (int m = 0; m < D; ++m) run_amp(phi, at[m]) = y[m];
+      for (int m = 0; m < D; ++m) amp_store(at[m], y[m]);
     }
   }
   return in ? s : 0.f;
@@ -170,35 +179,35 @@ __device__ __forceinline__ float fibre_group(float2 *phi, float2 *lam, KFloat *u
 
 // The same for CK = exp(i theta n_i n_j): one complex entry a member.
 template <int D, bool REV>
-__device__ __forceinline__ float fibre_diag(float2 *phi, float2 *lam, KFloat *u, int g, const ModeStep<D> &st, int base, bool in) {
+__device__ __forceinline__ float fibre_diag(int lam, KFloat *u, int g, const ModeStep<D> &st, int base, bool in) {
   float s = 0.f;
 #pragma unroll
   for (int m = 0; m < D; ++m) {
     const int at = run_at<D>(base, member_off<D>(st, g, m, true));
-    const float2 w = make_float2(u[2 * m], u[2 * m + 1]), x = run_amp(phi, at);
+    const float2 w = make_float2(u[2 * m], u[2 * m + 1]), x = amp_load(at);
     float2 y = make_float2(0.f, 0.f);
     if constexpr (REV) {
-      const float2 l = run_amp(lam, at);
+      const float2 l = amp_load(at + lam);
       float2 z = y;
       s = fmaf(-(float)(m * ((g - m) + (m > g ? D : 0))), fmaf(l.x, x.y, -l.y * x.x), s);
       cmac_conj(y, w, x);
       cmac_conj(z, w, l);
-      if (in) run_amp(lam, at) = z;
+      if (in) amp_store(at + lam, z);
     } else {
       cmac(y, w, x);
     }
-    if (in) run_amp(phi, at) = y;
+    if (in) amp_store(at, y);
   }
   return in ? s : 0.f;
 }
 
 template <int D, bool SUM, bool IM, bool REV>
-__device__ __forceinline__ float fibre_any(int g, float2 *phi, float2 *lam, KFloat *u, KFloat *A,
+__device__ __forceinline__ float fibre_any(int g, int lam, KFloat *u, KFloat *A,
                                            const ModeStep<D> &st, int base, bool in) {
   switch (g) {
 #define FOCK_GROUP(G) \
   case G:             \
-    if constexpr (G < D) return fibre_group<D, (G < D ? G : 0), SUM, IM, REV>(phi, lam, u, A, st, base, in); \
+    if constexpr (G < D) return fibre_group<D, (G < D ? G : 0), SUM, IM, REV>(lam, u, A, st, base, in); \
     break;
     FOCK_GROUP(0) FOCK_GROUP(1) FOCK_GROUP(2) FOCK_GROUP(3) FOCK_GROUP(4) FOCK_GROUP(5) FOCK_GROUP(6) FOCK_GROUP(7)
 #undef FOCK_GROUP
@@ -207,13 +216,15 @@ __device__ __forceinline__ float fibre_any(int g, float2 *phi, float2 *lam, KFlo
 }
 
 // A wavefront's units of a gate (group unit % D of fibres 64 (unit / D) ..) and
-// its lanes' share of Re<lam|A phi>.  rt: the gate's FuseTable; fib: byte offset
+// its lanes' share of Re<lam|A phi>.  lam: its distance from phi in bytes; rt: the
+// gate's fuse_table; fib: byte offset
 // of every fibre.
 template <int D, bool REV>
-__device__ __forceinline__ float fibre_gate(const FuseGate &gt, float2 *phi, float2 *lam, const float *rt,
+__device__ __forceinline__ float fibre_gate(const FuseGate &gt, float2 *phi, int lam, const float *rt,
                                             const float2 *A, const uint16_t *fib, int nfib) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6, lane = threadIdx.x & 63;
   const int type = gt.type;
+  const int origin = (int)(uint32_t)(uintptr_t)(LdsAmp *)phi;
   ModeStep<D> st;
 #pragma unroll
   for (int b = 0; b < 3; ++b) {
@@ -225,14 +236,14 @@ __device__ __forceinline__ float fibre_gate(const FuseGate &gt, float2 *phi, flo
   for (int c = wave; c < D * ((nfib + 63) >> 6); c += nw) {
     const int g = c % D, f = (c / D) * 64 + lane;
     const bool in = f < nfib;
-    const int base = fib[in ? f : 0];
+    const int base = origin + fib[in ? f : 0];
     KFloat *const ug = u + g * (D * D);
     switch (type) {
-      case FOCK_CK: s += fibre_diag<D, REV>(phi, lam, ug, g, st, base, in); break;
-      case FOCK_HR: s += fibre_any<D, true, false, REV>(g, phi, lam, ug, a, st, base, in); break;
-      case FOCK_PR: s += fibre_any<D, false, false, REV>(g, phi, lam, ug, a, st, base, in); break;
-      case FOCK_PI: s += fibre_any<D, false, true, REV>(g, phi, lam, ug, a, st, base, in); break;
-      default: s += fibre_any<D, true, true, REV>(g, phi, lam, ug, a, st, base, in); break;  // HI, DH
+      case FOCK_CK: s += fibre_diag<D, REV>(lam, ug, g, st, base, in); break;
+      case FOCK_HR: s += fibre_any<D, true, false, REV>(g, lam, ug, a, st, base, in); break;
+      case FOCK_PR: s += fibre_any<D, false, false, REV>(g, lam, ug, a, st, base, in); break;
+      case FOCK_PI: s += fibre_any<D, false, true, REV>(g, lam, ug, a, st, base, in); break;
+      default: s += fibre_any<D, true, true, REV>(g, lam, ug, a, st, base, in); break;  // HI, DH
     }
   }
   return s;

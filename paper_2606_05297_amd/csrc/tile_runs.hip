@@ -194,7 +194,7 @@ __device__ __forceinline__ void run_tile(const FuseArgs &a, int t, const float2 
     if (g.kj < 0)
       acc = run_phase<D, REV>(tp, tl, tab.u + g.u_off, g.type == FOCK_KERR, g.p.si, T);
     else
-      acc = fibre_gate<D, REV>(g, tp, tl, tab.r + (size_t)g.k * fuse_table(D), a.A[table_slot(g.type)], fib + q * nfib,
+      acc = fibre_gate<D, REV>(g, tp, 8 * TP, tab.r + (size_t)g.k * fuse_table(D), a.A[table_slot(g.type)], fib + q * nfib,
                                nfib);
     if constexpr (REV) {
       tile_sums_add(sums, q, acc);
