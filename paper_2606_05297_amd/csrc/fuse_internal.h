@@ -61,6 +61,14 @@ struct GateGroup {
   bool diag = false;
 };
 
+// Dynamic LDS of a run's workgroup: states, sums, row offsets and fibre positions
+// of ng gates (tile_runs.hip), and the most there is.
+constexpr size_t kFuseLds = 163840;
+inline size_t fuse_lds(int d, int T, int ng, bool rev) {
+  return sizeof(float2) * (size_t)((T + 31) & ~31) * (rev ? 2 : 1) + (rev ? sizeof(double) * 16 * 16 : 0) +
+         sizeof(uint32_t) * (size_t)(T / d) + sizeof(uint16_t) * (size_t)ng * (T / (d * d));
+}
+
 bool fuse_supported(int d);
 // Passes of ops[0..n) in the order they run; fuse: with fused runs.
 std::vector<GateGroup> plan_gate_groups(const Geometry &g, const fock_op_t *ops, int n, bool fuse);
@@ -68,9 +76,9 @@ int fuse_modes(const Geometry &g);
 // Workgroups (tiles) of a fused run.
 int fuse_tiles(const Geometry &g, const GateGroup &gr);
 FuseArgs make_fuse_args(const Geometry &g, const EigTables &T, const GateGroup &gr, const fock_op_t *ops);
-// Wavefronts and dynamic LDS of a run's workgroups.
+// Wavefronts of a run's workgroups.
 int fuse_waves(int D, int T);
-size_t fuse_lds(const FuseArgs &a, bool rev);
+inline size_t fuse_lds(const FuseArgs &a, bool rev) { return fuse_lds(a.d, a.T, a.ng, rev); }
 int launch_fuse_fwd(const FuseArgs &a, const float2 *src, float2 *dst, const FuseTables &tab, hipStream_t s);
 int launch_fuse_adj(const FuseArgs &a, float2 *phi, float2 *lam, const FuseTables &tab, double *partial, int rs,
                     hipStream_t s);

@@ -35,6 +35,7 @@ int fuse_modes(const Geometry &g) {
   const int Lf = g.half ? g.L - 1 : g.L;
   int many = 0, full = 0, s = 1;
   for (long T = g.d; s <= Lf && s <= kMaxFuseModes && T <= kTileMaxAmps; T *= g.d, ++s) {
+    if (fuse_lds(g.d, (int)T, kMaxFuseGates, true) > kFuseLds) break;  // d = 2, 8,192 amplitudes: fibre positions
     if ((long)g.n_amp / T >= 100) many = s;
     if (!full && T / (g.d * g.d) >= 32 && (long)g.n_amp / T >= 4) full = s;
   }

@@ -30,6 +30,7 @@ static_assert(kMaxFuseGates <= kTileSums, "one accumulator row per gate of a run
 
 // The gates' sums of a reverse run, per wavefront.
 typedef double RunSums[kTileSums][kTileWaves];
+static_assert(sizeof(RunSums) == sizeof(double) * 16 * 16, "fuse_lds");
 
 // Global index, relative to the tile's base, of row r of the tile (its d
 // amplitudes along mode 0 are contiguous).
@@ -244,11 +245,6 @@ bool fuse_supported(int d) { return d >= kTileMinD && d <= kTileMaxD; }
 int fuse_waves(int D, int T) {
   const int units = D * ((T / (D * D) + 63) / 64), rounds = (units + kTileWaves - 1) / kTileWaves;
   return std::max(4, (units + rounds - 1) / rounds);
-}
-
-size_t fuse_lds(const FuseArgs &a, bool rev) {
-  return sizeof(float2) * (size_t)((a.T + 31) & ~31) * (rev ? 2 : 1) + (rev ? sizeof(RunSums) : 0) + sizeof(uint32_t) * (a.T / a.d) +
-         sizeof(uint16_t) * (size_t)(a.ng * (a.T / (a.d * a.d)));
 }
 
 #define FOCK_RUN_SWITCH(d, STMT)                                              \

@@ -18,7 +18,7 @@ from paper_2606_05297_amd import lib
 pytestmark = pytest.mark.gpu
 
 ALL = ("HR", "HI", "DH", "PR", "PI", "CK")
-CASES = [(15, 2, True, 40), (9, 3, False, 30), (10, 3, True, 24), (7, 4, True, 30), (8, 4, False, 40), (6, 5, True, 30),
+CASES = [(15, 2, True, 40), (20, 2, False, 16), (9, 3, False, 30), (10, 3, True, 24), (7, 4, True, 30), (8, 4, False, 40), (6, 5, True, 30),
          (7, 5, False, 24), (6, 6, True, 40), (7, 6, False, 24), (5, 7, True, 25), (6, 7, False, 20), (5, 8, True, 40),
          (6, 8, True, 30)]
 
