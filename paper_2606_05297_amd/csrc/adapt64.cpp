@@ -139,7 +139,7 @@ int eval_small(fock_adapt64 *st, const std::vector<double> &th, bool grad, const
   for (int k = 0; k < n; ++k) {
     const fock_op_t &op = st->gops[k];
     st->host[k] = th[k];
-    gates[k] = op.type | op.i << 8 | (op.j < 0 ? 0xff : op.j) << 16;
+    gates[k] = op.type | gate_modes(op) << 8;
   }
   Small64 it{st->psi0, st->phi, st->lam, st->host, (const double2 *)st->links, gates, res, n, grad ? 1 : 0, 0, 0};
   const int rc = launch64_small(it, st->h, st->T, st->s);

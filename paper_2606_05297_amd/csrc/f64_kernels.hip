@@ -289,7 +289,7 @@ Fib64 make_fib64(int L, int d, const fock_op_t &op) {
   Fib64 a;
   a.L = L;
   a.d = d;
-  const bool one = op.j < 0;
+  const bool one = op_j(op) < 0;
   a.i = op.i;
   a.j = one ? -1 : op.j;
   uint32_t s = 1;

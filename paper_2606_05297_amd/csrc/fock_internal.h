@@ -106,7 +106,10 @@ struct GateRec {
   int modes;        // i in bits 0-7, j in bits 8-15 (0xff: none)
 };
 
-inline int gate_modes(const fock_op_t &op) { return (op.i & 0xff) | ((op.j & 0xff) << 8); }
+// Mode j of an op, -1 for a single-mode op: callers may leave anything in its j.
+bool is_single_mode(int type);
+inline int op_j(const fock_op_t &op) { return is_single_mode(op.type) ? -1 : op.j; }
+inline int gate_modes(const fock_op_t &op) { return (op.i & 0xff) | ((op_j(op) & 0xff) << 8); }
 
 // Per-(d) gate eigendata on the device: for each two-mode type t < 5, the
 // packed blocks of V (complex double, b x b row-major per block, column m is
@@ -177,7 +180,6 @@ inline int packed_size(int d) {  // sum of b^2 over blocks (same for SUM and DIF
 // two-mode types, d x d for single-mode types), complex double interleaved.
 void generator_dense(int type, int d, std::vector<double> &m);
 int gate_kind(int type);
-bool is_single_mode(int type);
 // Generators diagonal in the Fock basis (KERR, ROT, CK): pool scoring takes
 // them as -2 f(n) Im(conj(H psi) psi) terms instead of pair terms.
 bool is_pool_diagonal(int type);

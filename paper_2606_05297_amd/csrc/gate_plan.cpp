@@ -18,7 +18,7 @@ struct Item {
   bool fusable;
 };
 
-unsigned mode_mask(const fock_op_t &o) { return (1u << o.i) | (o.j >= 0 ? 1u << o.j : 0u); }
+unsigned mode_mask(const fock_op_t &o) { return (1u << o.i) | (op_j(o) >= 0 ? 1u << o.j : 0u); }
 
 }  // namespace
 
@@ -123,7 +123,7 @@ FuseArgs make_fuse_args(const Geometry &g, const EigTables &T, const GateGroup &
     FuseGate &f = a.g[q];
     f.type = o.type;
     f.ki = pos[o.i];
-    f.kj = o.j < 0 ? -1 : pos[o.j];
+    f.kj = op_j(o) < 0 ? -1 : pos[o.j];
     f.u_off = k * gate_stride(d);
     f.k = k;
     int si = 1, sj = 1;
