@@ -199,8 +199,9 @@ def main():
                     help="run real-state gates and reverse steps gate by gate (fused runs off)")
     ap.add_argument("--prof-sample", type=int, default=4,
                     help="time one launch in this many per kernel family with HIP events (1: every launch)")
-    ap.add_argument("--gate-fusion", type=int, choices=[0, 1, 2], default=None,
-                    help="0 per-gate passes (library default), 1 fused forward circuit, 2 fused forward and adjoint")
+    ap.add_argument("--gate-fusion", type=int, choices=[0, 1, 2, 3], default=None,
+                    help="0 per-gate passes, 1 fused forward circuit, 2 fused forward and adjoint, 3 passes planned "
+                         "by the library (its default)")
     args = ap.parse_args()
     if args.gpus != 1:
         print(f"bench.py runs on one GPU only (asked for --gpus {args.gpus}); the multi-GPU design is "

@@ -452,12 +452,16 @@ int fock_get_gate_variant(void);
  * staged in LDS and the gates, or their reverse steps, are applied there one
  * after another; a gate may move past others on disjoint modes, with which it
  * commutes.  The rest runs gate by gate.  The paths agree to FP32/FP64 rounding,
- * not bitwise.  Process-wide mode: FOCK_FUSE_OFF (the default): as above;
+ * not bitwise.  Process-wide mode: FOCK_FUSE_AUTO (the default): as above;
+ * FOCK_FUSE_OFF: gate by gate (runs of single-mode phase gates stay one pass);
  * FOCK_FUSE_FORWARD: no whole evaluations, fused runs in the forward circuit
- * only; FOCK_FUSE_ALL: no whole evaluations, fused runs both ways (phi_work and
- * lam_work then end as after fock_adjoint_sweep).  With the dense gate variant or
- * a forward-state store the gates run one by one. */
-enum { FOCK_FUSE_OFF = 0, FOCK_FUSE_FORWARD = 1, FOCK_FUSE_ALL = 2 };
+ * only; FOCK_FUSE_ALL: no whole evaluations, fused runs both ways (states of
+ * fewer than four such tiles: gate by gate).  After a
+ * gradient evaluation in any mode but AUTO phi_work and lam_work end as after
+ * fock_adjoint_sweep.  The batched sweep runs gate by gate in every mode but
+ * AUTO.  With the dense gate variant or a forward-state store the gates run one
+ * by one. */
+enum { FOCK_FUSE_OFF = 0, FOCK_FUSE_FORWARD = 1, FOCK_FUSE_ALL = 2, FOCK_FUSE_AUTO = 3 };
 int fock_set_gate_fusion(int mode);
 int fock_get_gate_fusion(void);
 

@@ -359,7 +359,8 @@ static int wait_results(Ctx &c) {
 }
 
 // ---------------------------------------------------------------- gate fusion
-static std::atomic<int> g_fuse{FOCK_FUSE_OFF};
+static std::atomic<int> g_fuse{FOCK_FUSE_AUTO};
+int gate_fusion_mode() { return g_fuse.load(); }
 
 // Stage the gate tables of a circuit (with the per-gate partial counts of the
 // reverse step, which depend on how the gates are grouped) and plan its groups.
@@ -371,10 +372,12 @@ bool half_layout_op_ok(const fock_op_t &op, int L) {
 }
 
 // Fused runs are on unless the caller asks for a path that works gate by gate
-// (dense gates, kept forward states); FOCK_FUSE_FORWARD keeps the reverse sweep
-// gate by gate.
-static bool fused_runs(const Ctx &c) { return !c.store && gate_variant() == FOCK_GATE_BLOCK; }
-static bool reverse_fused() { return g_fuse.load() != FOCK_FUSE_FORWARD; }
+// (FOCK_FUSE_OFF, dense gates, kept forward states); FOCK_FUSE_FORWARD keeps the
+// reverse sweep gate by gate.  c.fuse: the mode when the evaluation began.
+static bool fused_runs(const Ctx &c) {
+  return c.fuse != FOCK_FUSE_OFF && !c.store && gate_variant() == FOCK_GATE_BLOCK;
+}
+static bool reverse_fused(const Ctx &c) { return c.fuse != FOCK_FUSE_FORWARD; }
 
 static int stage_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int n, std::vector<GateGroup> *groups) {
   if (n > c.L.nmax) return set_error(FOCK_ERR_SIZE, "circuit of %d gates exceeds the workspace's %d", n, c.L.nmax);
@@ -390,7 +393,7 @@ static int stage_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int 
   for (const GateGroup &gr : *groups) {
     if (gr.s == 0) continue;
     runs = true;
-    if (reverse_fused())
+    if (reverse_fused(c))
       for (int k : gr.k) nblk[k] = fuse_tiles(c.g, gr);
   }
   return stage_gates(c, ops, theta, n, nblk.data(), runs);
@@ -452,7 +455,7 @@ static int reverse_sweep(Ctx &c, const fock_op_t *ops, int n, const std::vector<
       if (rc) return rc;
       continue;
     }
-    if (gr.s > 0 && reverse_fused()) {
+    if (gr.s > 0 && reverse_fused(c)) {
       ProfScope ps(FOCK_K_ADJ, c.s, 32.0 * c.g.n_amp);
       rc = launch_fuse_adj(make_fuse_args(c.g, c.T, gr, ops), phi, lam, tables_of(c), part, c.L.rs, c.s);
       if (rc) return rc;
@@ -700,13 +703,13 @@ static int reverse_real(Ctx &c, const fock_op_t *ops, int n, const std::vector<R
 // ---------------------------------------------------------------- small states
 // Small states are evaluated by one workgroup in one launch (small_eval.hip):
 // whenever both states of the reverse sweep fit its LDS (about 9,500
-// amplitudes), unless the caller asks for a particular gate path (dense gates,
-// fused runs, kept forward states).  Measured per call, against gate by gate:
+// amplitudes), unless the caller asks for a particular gate path (gate by gate,
+// dense gates, fused runs, kept forward states).  Measured per call, against gate by gate:
 // 21 gates on 64 amplitudes 64 against 159 us, 30 gates on 4,096 amplitudes 172
 // against 387 us, 35 gates on 7,776 amplitudes (the largest of d = 6) 286
 // against 347 us.
 static bool small_used(const Ctx &c, int n) {
-  return !c.g.half && !c.store && gate_variant() == FOCK_GATE_BLOCK && g_fuse.load() == FOCK_FUSE_OFF &&
+  return !c.g.half && !c.store && gate_variant() == FOCK_GATE_BLOCK && c.fuse == FOCK_FUSE_AUTO &&
          small_eval_ok(c.g.L, c.g.d, c.g.n_amp, n);
 }
 
@@ -753,6 +756,7 @@ int run_score(Ctx &c, const fock_op_t *ops, const double *theta, int n, const vo
               float2 *lam, const fock_op_t *pool, int P, double *E, double *norm2, double *g) {
   std::vector<GateGroup> groups;
   std::vector<RealRun> runs;
+  c.fuse = gate_fusion_mode();
   double *res = nullptr;
   int rc = host_results(2 + P, &res);
   if (rc) return rc;
@@ -796,6 +800,7 @@ static int finish_eval(const double *res, int n, bool grad, double *E, double *n
 // Energy and (optionally) all dE/dtheta of a circuit; see fock_energy_grad_adjoint.
 int run_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int n, const void *psi0, float2 *phi,
                        float2 *lam, bool grad, double *E, double *norm2, double *dE) {
+  c.fuse = gate_fusion_mode();
   double *res = nullptr;
   int rc = host_results(2 + n, &res);
   if (rc) return rc;
@@ -860,6 +865,7 @@ int run_reverse(Ctx &c, const fock_op_t *ops, const double *theta, int n, float2
                 double *dE) {
   if (!(norm2 > 0.0) || !std::isfinite(norm2)) return set_error(FOCK_ERR_ARG, "norm2 must be finite and > 0");
   std::vector<GateGroup> groups;
+  c.fuse = gate_fusion_mode();
   int rc = stage_circuit(c, ops, theta, n, &groups);
   if (rc || n == 0) return rc;
   double *host = nullptr;
@@ -1186,8 +1192,8 @@ int fock_set_gate_variant(int variant) {
 int fock_get_gate_variant(void) { return g_gate_variant.load(); }
 
 int fock_set_gate_fusion(int mode) {
-  if (mode < FOCK_FUSE_OFF || mode > FOCK_FUSE_ALL)
-    return set_error(FOCK_ERR_ARG, "gate fusion mode %d not in [0, 2]", mode);
+  if (mode < FOCK_FUSE_OFF || mode > FOCK_FUSE_AUTO)
+    return set_error(FOCK_ERR_ARG, "gate fusion mode %d not in [0, 3]", mode);
   g_fuse.store(mode);
   return FOCK_OK;
 }

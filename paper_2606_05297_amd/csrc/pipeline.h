@@ -31,7 +31,10 @@ struct Ctx {
   // Real states (d = 8, ADAPT driver): float32 copies of psi0 and the forward
   // and adjoint states, used by evaluations whose gates are all HR or PR.
   float *psi0_r = nullptr, *phi_r = nullptr, *lam_r = nullptr;
+  int fuse = FOCK_FUSE_AUTO;  // gate fusion mode of the evaluation under way
 };
+
+int gate_fusion_mode();  // FOCK_FUSE_*
 
 int check_geometry(int L, int d, uint32_t *namp);
 // check_ham takes full d^L states only; check_ham_layout also the parity-halved

@@ -86,6 +86,7 @@ struct fock_sweep {
   size_t n_up = 0, n_res = 0;
   void *pin = nullptr;  // pinned: [angles][active flags][results]
   int grid = 1024;
+  bool planned = true;  // the current lists hold the library's passes (FOCK_FUSE_AUTO), else one gate a pass
   // item lists (device) for the current ansatz lengths
   void *items_d = nullptr;
   size_t items_cap = 0;
@@ -146,18 +147,21 @@ struct Lists {
 
 // Whether a point's circuit is evaluated whole by one workgroup (the rule of
 // the single-point path).
-bool point_small(const SPoint &P) { return small_eval_ok(P.g.L, P.g.d, P.g.n_amp, (int)P.ops.size()); }
+bool point_small(const fock_sweep *sw, const SPoint &P) {
+  return sw->planned && small_eval_ok(P.g.L, P.g.d, P.g.n_amp, (int)P.ops.size());
+}
 
 // The passes of a point are those of the single-point driver (plan_gate_groups).
 int build_lists(fock_sweep *sw, const std::vector<char> &sel, bool grad, Lists *Ls) {
   const size_t npt = sw->pts.size();
+  sw->planned = gate_fusion_mode() == FOCK_FUSE_AUTO;
   std::vector<std::vector<GateGroup>> groups(npt);
   std::vector<DiagRun> runs;
   std::vector<size_t> run_base(npt, 0);
   for (size_t p = 0; p < npt; ++p) {
     const SPoint &P = sw->pts[p];
-    if (point_small(P)) continue;
-    groups[p] = plan_gate_groups(P.g, P.ops.data(), (int)P.ops.size(), true);
+    if (point_small(sw, P)) continue;
+    groups[p] = plan_gate_groups(P.g, P.ops.data(), (int)P.ops.size(), sw->planned);
     run_base[p] = runs.size();
     for (auto &g : groups[p])
       if (g.diag) runs.push_back(diag_run_params(P.g, P.ops.data(), g.k.front(), g.k.back() + 1));
@@ -181,7 +185,7 @@ int build_lists(fock_sweep *sw, const std::vector<char> &sel, bool grad, Lists *
     GroupLists &GL = Ls->g[P.group];
     const int stride = gate_stride(P.g.d);
     const int n = (int)P.ops.size();
-    if (point_small(P)) {
+    if (point_small(sw, P)) {
       SmallItem it = small_item(P.h, P.g.n_amp, n, grad);
       it.point = (int)pi;
       it.psi0 = P.psi0;
@@ -673,7 +677,7 @@ int score_phase(fock_sweep *sw, const std::vector<char> &sel, std::vector<std::v
     SPoint &P = sw->pts[pi];
     pargs.push_back(P.pa);
     if (!sel[pi]) continue;
-    const float2 *st = P.ops.empty() && !point_small(P) ? P.psi0 : P.phi;
+    const float2 *st = P.ops.empty() && !point_small(sw, P) ? P.psi0 : P.phi;
     for (int vb = 0; vb < P.GH; ++vb) pitems[P.group].push_back(SweepHItem{(int)pi, vb, st, P.lam, P.partial});
     for (int k = 0; k < P.P; ++k) red.push_back(SweepRItem{(int)pi, 0, P.GH, P.P, k, 0, P.partial, P.res + 2 + k});
   }

@@ -955,12 +955,12 @@ def get_gate_variant() -> int:
     return int(load().fock_get_gate_variant())
 
 
-FUSE_OFF, FUSE_FORWARD, FUSE_ALL = 0, 1, 2
+FUSE_OFF, FUSE_FORWARD, FUSE_ALL, FUSE_AUTO = 0, 1, 2, 3
 
 
 def set_gate_fusion(mode: int):
-    """0: the library plans the passes (default); 1: fused runs in the forward circuit only; 2: fused runs in the
-    forward circuit and the adjoint sweep."""
+    """FUSE_AUTO: the library plans the passes (default); FUSE_OFF: gate by gate; FUSE_FORWARD: fused runs in the
+    forward circuit only; FUSE_ALL: fused runs in the forward circuit and the adjoint sweep."""
     _check(load().fock_set_gate_fusion(int(mode)))
 
 

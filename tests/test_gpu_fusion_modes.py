@@ -1,0 +1,158 @@
+"""What the gate fusion modes run: FUSE_OFF one pass a gate (and the per-gate
+kernels against the FP64 oracle at every cutoff), the library's plan otherwise;
+the batched sweep follows the mode and equals the single-point driver bit for bit
+on small states evaluated side by side.
+
+Tolerances as for the gate-by-gate evaluation: 1e-5 on amplitudes, 1e-5 |E|,
+1e-4 max(1, |g|)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import workload as W
+from paper_2606_05297_amd import lib
+
+pytestmark = pytest.mark.gpu
+
+GATE, ADJ, DIAG = 2, 3, 4
+TWO = ("HR", "HI", "DH", "PR", "PI", "CK")
+
+
+@pytest.fixture
+def off():
+    prev = lib.get_gate_fusion()
+    lib.set_gate_fusion(lib.FUSE_OFF)
+    yield
+    lib.set_gate_fusion(prev)
+
+
+def launches(fn):
+    """Launches of forward gates and reverse steps that fn() enqueues."""
+    lib.prof_reset()
+    lib.prof_enable(True)
+    try:
+        fn()
+        return [lib.prof_query(k)["launches"] for k in (GATE, ADJ)]
+    finally:
+        lib.prof_enable(False)
+        lib.prof_reset()
+
+
+@pytest.mark.parametrize("L,d", [(4, 4), (6, 6), (5, 8)])
+def test_launches_of_each_mode(L, d):
+    h = lib.ham(L, d, False, 1.0, 0.5, 0.1, 0.3, 0.0)
+    ops, th = W.random_circuit(W.pool(L, "all", False, TWO), 20, seed=d)
+    x = torch.from_numpy(W.random_state(L, d, seed=2)).cuda()
+    a, b = torch.empty_like(x), torch.empty_like(x)
+    ws = lib.workspace(h, 0, len(ops))
+    prev = lib.get_gate_fusion()
+    got = {}
+    try:
+        for m in (lib.FUSE_OFF, lib.FUSE_FORWARD, lib.FUSE_ALL, lib.FUSE_AUTO):
+            lib.set_gate_fusion(m)
+            got[m] = launches(lambda: lib.energy_grad_adjoint(h, ops, th, x, a, b, ws))
+    finally:
+        lib.set_gate_fusion(prev)
+    print("[case] launches", L, d, got, flush=True)
+    n = len(ops)
+    assert got[lib.FUSE_OFF] == [n, n]
+    if d ** L == 256:  # too few tiles for fused runs: one launch, or gate by gate
+        assert got[lib.FUSE_FORWARD] == got[lib.FUSE_ALL] == [n, n] and got[lib.FUSE_AUTO] == [0, 1]
+        return
+    assert got[lib.FUSE_FORWARD][0] < n and got[lib.FUSE_FORWARD][1] == n
+    assert got[lib.FUSE_ALL][0] < n and got[lib.FUSE_ALL][1] < n
+    assert got[lib.FUSE_AUTO] == got[lib.FUSE_ALL]
+
+
+@pytest.mark.parametrize("L,d", [(6, 2), (5, 3), (4, 4), (4, 5), (6, 6), (4, 7), (6, 8), (3, 9)])
+def test_gate_by_gate_matches_oracle(L, d, off):
+    """Every two-mode type on every pair of modes 0, 1, 2 and the last (the
+    kernels of mode 0 and of higher modes), with phase gates and squeezers."""
+    print("[case] gate by gate", L, d, flush=True)
+    prm = (1.0, 0.7, 0.2, 0.4, 0.15)
+    ho, hl = O.Ham(L, d, True, *prm), lib.ham(L, d, True, *prm)
+    m = sorted({0, 1, 2, L - 1})
+    ops = [(t, i, j) for t in TWO for i in m for j in m if i < j] + W.site_ops(L, ("KERR", "SR", "ROT", "SI"))
+    rng = np.random.default_rng(10 * L + d)
+    ops = [ops[k] for k in rng.permutation(len(ops))]
+    th = rng.uniform(-0.4, 0.4, len(ops))
+    psi0 = W.random_state(L, d, seed=4)
+    x = torch.from_numpy(psi0).cuda()
+    a, b = torch.empty_like(x), torch.empty_like(x)
+    ws = lib.workspace(hl, 0, len(ops))
+    E, n2, g = lib.energy_grad_adjoint(hl, ops, th, x, a, b, ws)
+    assert np.abs(a.cpu().numpy() - psi0).max() <= 1e-5  # undone by the reverse sweep
+    Eo, go, n2o = O.energy_and_grad_adjoint(ho, psi0.astype(np.complex128), ops, th)
+    assert abs(E - Eo / n2o) <= 1e-5 * max(1.0, abs(Eo)) and abs(n2 - n2o) <= 1e-5
+    assert np.abs(g - go).max() <= 1e-4 * max(1.0, np.abs(go).max())
+    E2, m2, _ = lib.energy_grad_adjoint(hl, ops, th, x, a, b, ws, grad=False)
+    assert (E2, m2) == (E, n2)
+    psi = O.ansatz_state(psi0.astype(np.complex128), ops, th, L, d)
+    assert np.abs(a.cpu().numpy() - psi).max() <= 1e-5
+    assert np.array_equal(lib.adjoint_sweep(hl, ops, th, a, b, n2, ws), g)
+
+
+def small_entries():
+    out = []
+    for L, d in ((2, 4), (5, 4), (4, 4), (3, 6), (4, 8), (5, 6)):
+        x = torch.zeros(d ** L, dtype=torch.complex64, device="cuda")
+        x[W.fock_index(L, d, [1] * L)] = 1
+        warm = W.warmup_ops(L, True) if L % 2 else []
+        out.append(dict(ham=lib.ham(L, d, True, 1.0, 0.6 + 0.1 * L), pool=W.pool(L, "nn", True, W.BH_TYPES), psi0=x,
+                        warm_ops=warm, warm_theta0=W.warmup_theta0(len(warm), L) if warm else np.zeros(0)))
+    return out
+
+
+def key(r):
+    return r["k_sel"], r["E"], r["bfgs_evals"], r["g_inf"]
+
+
+@pytest.mark.parametrize("mode", ["FUSE_AUTO", "FUSE_OFF"])
+def test_small_sweep_points_equal_single_runs(mode):
+    """Points of one cutoff and several sizes that one launch evaluates side by
+    side, some of them finished earlier than others."""
+    print("[case] small sweep", mode, flush=True)
+    prev = lib.get_gate_fusion()
+    lib.set_gate_fusion(getattr(lib, mode))
+    lib.set_real_states(lib.REAL_OFF)
+    try:
+        entries = small_entries()
+        singles = [lib.Adapt(e["ham"], e["pool"], e["psi0"], max_iters=5, warm_ops=e["warm_ops"],
+                             warm_theta0=e["warm_theta0"]) for e in entries]
+        sw = lib.Sweep(entries, max_iters=5)
+        warm = sw.warm_reports()
+        for k, e in enumerate(entries):
+            assert len(e["warm_ops"]) == 0 or warm[k]["E"] == singles[k].warm_report()["E"], k
+        live = list(range(len(singles)))
+        for it in range(4):
+            if not live:
+                break
+            reps, _ = sw.step()
+            for k in list(live):
+                r = singles[k].step()
+                assert key(reps[k]) == key(r), (k, it)
+                if r["converged"] or r["capped"]:
+                    live.remove(k)
+        sw.close()
+        for a in singles:
+            a.close()
+    finally:
+        lib.set_gate_fusion(prev)
+        lib.set_real_states(lib.REAL_AUTO)
+
+
+def test_sweep_of_forced_runs_is_gate_by_gate():
+    """Only the library's own plan fuses in the sweep."""
+    print("[case] sweep modes", flush=True)
+    prev = lib.get_gate_fusion()
+    got = []
+    try:
+        for mode in (lib.FUSE_OFF, lib.FUSE_ALL, lib.FUSE_FORWARD):
+            lib.set_gate_fusion(mode)
+            sw = lib.Sweep(small_entries(), max_iters=2)
+            got.append([key(r) for r in sw.warm_reports() + sw.step()[0]])
+            sw.close()
+    finally:
+        lib.set_gate_fusion(prev)
+    assert got[0] == got[1] == got[2]
