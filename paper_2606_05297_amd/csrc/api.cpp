@@ -701,16 +701,13 @@ static int reverse_real(Ctx &c, const fock_op_t *ops, int n, const std::vector<R
 }
 
 // ---------------------------------------------------------------- small states
-// Small states are evaluated by one workgroup in one launch (small_eval.hip):
-// whenever both states of the reverse sweep fit its LDS (about 9,500
-// amplitudes), unless the caller asks for a particular gate path (gate by gate,
-// dense gates, fused runs, kept forward states).  Measured per call, against gate by gate:
-// 21 gates on 64 amplitudes 64 against 159 us, 30 gates on 4,096 amplitudes 172
-// against 387 us, 35 gates on 7,776 amplitudes (the largest of d = 6) 286
-// against 347 us.
-static bool small_used(const Ctx &c, int n) {
-  return !c.g.half && !c.store && gate_variant() == FOCK_GATE_BLOCK && c.fuse == FOCK_FUSE_AUTO &&
-         small_eval_ok(c.g.L, c.g.d, c.g.n_amp, n);
+// Small states are evaluated by one workgroup in one launch (small_eval.hip) where
+// the plan says so (small_planned), unless the caller asks for a particular gate
+// path (gate by gate, dense gates, fused runs, kept forward states).  Measured per
+// call, against gate by gate: 21 gates on 64 amplitudes 64 against 159 us, 30
+// gates on 4,096 amplitudes (d = 8) 172 against 419 us.
+static bool small_used(const Ctx &c, const fock_op_t *ops, int n) {
+  return !c.store && gate_variant() == FOCK_GATE_BLOCK && c.fuse == FOCK_FUSE_AUTO && small_planned(c.g, ops, n);
 }
 
 SmallItem small_item(const HamArgs &h, uint32_t namp, int n, bool grad) {
@@ -760,7 +757,7 @@ int run_score(Ctx &c, const fock_op_t *ops, const double *theta, int n, const vo
   double *res = nullptr;
   int rc = host_results(2 + P, &res);
   if (rc) return rc;
-  if (small_used(c, n)) {  // leaves phi and H phi, and the energy and norm in res
+  if (small_used(c, ops, n)) {  // leaves phi and H phi, and the energy and norm in res
     if ((rc = enqueue_small(c, ops, theta, n, psi0, phi, lam, false, res))) return rc;
     if ((rc = pool_dev(c, pool, P, phi, lam, res + 2, 0))) return rc;
   } else {
@@ -804,7 +801,7 @@ int run_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int n, const 
   double *res = nullptr;
   int rc = host_results(2 + n, &res);
   if (rc) return rc;
-  if (small_used(c, n)) {
+  if (small_used(c, ops, n)) {
     if ((rc = enqueue_small(c, ops, theta, n, psi0, phi, lam, grad, res)) || (rc = wait_results(c))) return rc;
     return finish_eval(res, n, grad, E, norm2, dE);
   }

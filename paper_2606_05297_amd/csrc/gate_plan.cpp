@@ -6,6 +6,7 @@
 #include <cstring>
 
 #include "fuse_internal.h"
+#include "small_eval.h"
 
 namespace fock {
 
@@ -40,6 +41,40 @@ int fuse_modes(const Geometry &g) {
     if (!full && T / (g.d * g.d) >= 32 && (long)g.n_amp / T >= 4) full = s;
   }
   return std::max(many, full);
+}
+
+// Whether the library's plan evaluates a circuit on a small state whole, in one
+// workgroup (small_eval.hip), rather than pass by pass.
+//
+// Above 2,048 amplitudes not where fused runs are at hand: the chip is faster than
+// one CU there.  30 gates with gradients, us, fused / whole: 8,192 amplitudes at
+// d = 2 164 / 407, 6,561 (d = 3) 164 / 294, 7,776 (d = 6) 207 / 298, 4,096 (d = 4,
+// six gates) 63 / 69; but 2,048 (d = 2, six gates) 64 / 66, 1,024 147 / 121.
+//
+// Elsewhere a two-mode gate saves 4 us at least against a pass forward and one in
+// reverse, and the call 4 us by itself, but two things cost more than in passes:
+// a squeezer (dense: one thread a fibre) at d >= 6, 1, 2.5 and 5 us, and each phase
+// gate that a diagonal pass would take along, up to N / 2000 us.  Pass by pass /
+// whole: 30 squeezers at d = 8, 512 amplitudes 241 / 358, one or two alone 39 / 42 at
+// 3,125 (d = 5), 30 phase gates at 4,096 amplitudes (d = 8) 80 / 116, ten at 1,024
+// (d = 4) 50 / 54.
+bool small_planned(const Geometry &g, const fock_op_t *ops, int n) {
+  if (g.half || !small_eval_ok(g.L, g.d, g.n_amp, n)) return false;
+  if (g.n_amp > 2048 && fuse_supported(g.d) && fuse_modes(g) >= 3) return false;
+  double saved = 4.0, lost = 0.0;
+  int squeezers = 0;
+  for (int k = 0; k < n;) {
+    const int end = std::max(diag_run_end(ops, n, k), k + 1);
+    if (is_squeeze(ops[k].type)) {
+      ++squeezers;
+      lost += g.d == 8 ? 5.0 : g.d == 7 ? 2.5 : g.d == 6 ? 1.0 : 0.0;
+    } else if (!is_single_mode(ops[k].type)) {
+      saved += 4.0;
+    }
+    lost += (end - k - 1) * (double)g.n_amp / 2000.0;
+    k = end;
+  }
+  return saved >= lost && (n == 0 || n > 2 || squeezers < n);
 }
 
 std::vector<GateGroup> plan_gate_groups(const Geometry &g, const fock_op_t *ops, int n, bool fuse) {

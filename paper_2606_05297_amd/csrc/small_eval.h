@@ -27,6 +27,8 @@ struct SmallItem {
 // the LDS of one workgroup, and d <= 8 (a group of d members fills one matrix
 // operand), circuits of up to kSmallGates gates (their descriptions in LDS).
 bool small_eval_ok(int L, int d, uint32_t namp, int n);
+// Those the library's plan gives to it (gate_plan.cpp).
+bool small_planned(const Geometry &g, const fock_op_t *ops, int n);
 int small_chunk(int d, uint32_t namp, int n);
 // LDS of one item's workgroup.
 size_t small_lds_bytes(const SmallItem &it);

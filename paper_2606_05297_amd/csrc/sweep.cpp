@@ -148,7 +148,7 @@ struct Lists {
 // Whether a point's circuit is evaluated whole by one workgroup (the rule of
 // the single-point path).
 bool point_small(const fock_sweep *sw, const SPoint &P) {
-  return sw->planned && small_eval_ok(P.g.L, P.g.d, P.g.n_amp, (int)P.ops.size());
+  return sw->planned && small_planned(P.g, P.ops.data(), (int)P.ops.size());
 }
 
 // The passes of a point are those of the single-point driver (plan_gate_groups).

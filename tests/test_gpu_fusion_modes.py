@@ -27,13 +27,13 @@ def off():
     lib.set_gate_fusion(prev)
 
 
-def launches(fn):
+def launches(fn, families=(GATE, ADJ)):
     """Launches of forward gates and reverse steps that fn() enqueues."""
     lib.prof_reset()
     lib.prof_enable(True)
     try:
         fn()
-        return [lib.prof_query(k)["launches"] for k in (GATE, ADJ)]
+        return [lib.prof_query(k)["launches"] for k in families]
     finally:
         lib.prof_enable(False)
         lib.prof_reset()
@@ -63,6 +63,58 @@ def test_launches_of_each_mode(L, d):
     assert got[lib.FUSE_FORWARD][0] < n and got[lib.FUSE_FORWARD][1] == n
     assert got[lib.FUSE_ALL][0] < n and got[lib.FUSE_ALL][1] < n
     assert got[lib.FUSE_AUTO] == got[lib.FUSE_ALL]
+
+
+def two(L, n):
+    return [(TWO[k % 6], k % (L - 1), k % (L - 1) + 1) for k in range(n)]
+
+
+def phases(L, n):
+    return [(("KERR", "ROT")[k % 2], k % L, -1) for k in range(n)]
+
+
+def squeezers(L, n):
+    return [(("SR", "SI")[k % 2], k % L, -1) for k in range(n)]
+
+
+# (L, d, circuit, one launch): 2,048 amplitudes, the largest without runs, and the
+# first with them; circuits of squeezers and of phase gates, and the share of
+# two-mode gates that outweighs them
+PLANS = [(11, 2, two(11, 12), True), (12, 2, two(12, 12), False), (7, 3, two(7, 12), True), (8, 3, two(8, 12), False),
+         (6, 4, two(6, 12), False), (5, 5, two(5, 12), True), (5, 6, two(5, 12), False), (4, 7, two(4, 12), True),
+         (4, 8, two(4, 12), True), (4, 8, [], True), (4, 4, [], True),
+         (1, 8, squeezers(1, 1), False), (3, 8, squeezers(3, 2), False), (3, 8, squeezers(3, 2) + two(3, 2), True), (3, 4, squeezers(3, 2), False), (3, 4, squeezers(3, 3), True),
+         (3, 7, squeezers(3, 2), False), (3, 6, squeezers(3, 4), True), (3, 6, squeezers(3, 5), False),
+         (3, 5, squeezers(3, 30), True), (4, 8, phases(4, 2), True), (4, 8, phases(4, 3), False),
+         (4, 8, phases(4, 4) + two(4, 1), True), (3, 4, phases(3, 32), True)]
+
+
+@pytest.mark.parametrize("k", range(len(PLANS)))
+def test_small_states_leave_passes_that_are_faster(k):
+    """One launch or passes, by amplitudes and by what the circuit is made of."""
+    L, d, ops, one = PLANS[k]
+    h = lib.ham(L, d, False, 1.0, 0.5, 0.1, 0.3, 0.0)
+    x = torch.from_numpy(W.random_state(L, d, seed=2)).cuda()
+    a, b = torch.empty_like(x), torch.empty_like(x)
+    ws = lib.workspace(h, 0, len(ops))
+    th = np.linspace(-0.4, 0.5, len(ops))
+
+    def run():
+        return lib.energy_grad_adjoint(h, ops, th, x, a, b, ws)
+
+    APPLY_H = 0
+    got = launches(run, (GATE, ADJ, APPLY_H))
+    print("[case] plan", L, d, len(ops), got, flush=True)
+    assert (got == [0, 1, 0]) == one and (got[2] == 1) == (not one)
+    E, _, g = run()
+    prev = lib.get_gate_fusion()
+    lib.set_gate_fusion(lib.FUSE_OFF)
+    try:
+        Eu, _, gu = run()
+    finally:
+        lib.set_gate_fusion(prev)
+    assert abs(E - Eu) <= 1e-5 * max(1.0, abs(Eu))
+    assert len(ops) == 0 or np.abs(g - gu).max() <= 1e-4 * max(1.0, np.abs(gu).max())
 
 
 @pytest.mark.parametrize("L,d", [(6, 2), (5, 3), (4, 4), (4, 5), (6, 6), (4, 7), (6, 8), (3, 9)])
