@@ -445,9 +445,8 @@ int fock_get_gate_variant(void);
 
 /* Circuits on complex64 states (fock_energy_grad_adjoint, fock_adjoint_sweep,
  * the ADAPT, HVA and sweep drivers) run in passes the library plans.  Small
- * states (d <= 8, up to 2,048 amplitudes, or 4,096 where no runs of gates are at
- * hand; at most 256 gates, not mostly phase gates and squeezers) are evaluated
- * whole in one launch.  On larger ones at d <= 8, gates whose modes fit one tile (mode 0 and
+ * states (d <= 8, up to 4,096 amplitudes, 2,048 at d = 2; at most 256 gates, not
+ * mostly phase gates and squeezers) are evaluated whole in one launch.  On larger ones at d <= 8, gates whose modes fit one tile (mode 0 and
  * two to twelve others, at most 8192 amplitudes) run as one pass: the tile is
  * staged in LDS and the gates, or their reverse steps, are applied there one
  * after another; a gate may move past others on disjoint modes, with which it

@@ -46,10 +46,12 @@ int fuse_modes(const Geometry &g) {
 // Whether the library's plan evaluates a circuit on a small state whole, in one
 // workgroup (small_eval.hip), rather than pass by pass.
 //
-// Above 2,048 amplitudes not where fused runs are at hand: the chip is faster than
-// one CU there.  30 gates with gradients, us, fused / whole: 8,192 amplitudes at
-// d = 2 164 / 407, 6,561 (d = 3) 164 / 294, 7,776 (d = 6) 207 / 298, 4,096 (d = 4,
-// six gates) 63 / 69; but 2,048 (d = 2, six gates) 64 / 66, 1,024 147 / 121.
+// Above 4,096 amplitudes (d = 2: 2,048) not where fused runs are at hand: the chip
+// is faster than one CU there.  30 gates with gradients, us, fused / whole: 8,192
+// amplitudes at d = 2 164 / 407, 4,096 166 / 244, 6,561 (d = 3) 164 / 294, 7,776
+// (d = 6) 207 / 298; but 4,096 at d = 4 with a warm-up layer 142 / 135, and 1,024
+// at d = 2 147 / 121.  With one or two gates on 4,096 amplitudes of six modes H psi
+// is most of the call, 37 us by its own kernel, 41 whole.
 //
 // Elsewhere a two-mode gate saves 4 us at least against a pass forward and one in
 // reverse, and the call 4 us by itself, but two things cost more than in passes:
@@ -60,7 +62,10 @@ int fuse_modes(const Geometry &g) {
 // (d = 4) 50 / 54.
 bool small_planned(const Geometry &g, const fock_op_t *ops, int n) {
   if (g.half || !small_eval_ok(g.L, g.d, g.n_amp, n)) return false;
-  if (g.n_amp > 2048 && fuse_supported(g.d) && fuse_modes(g) >= 3) return false;
+  if (fuse_supported(g.d) && fuse_modes(g) >= 3) {
+    if (g.n_amp > (g.d == 2 ? 2048u : 4096u)) return false;
+    if (g.n_amp == 4096 && n > 0 && n <= 2) return false;
+  }
   double saved = 4.0, lost = 0.0;
   int squeezers = 0;
   for (int k = 0; k < n;) {

@@ -77,11 +77,12 @@ def squeezers(L, n):
     return [(("SR", "SI")[k % 2], k % L, -1) for k in range(n)]
 
 
-# (L, d, circuit, one launch): 2,048 amplitudes, the largest without runs, and the
-# first with them; circuits of squeezers and of phase gates, and the share of
+# (L, d, circuit, one launch): the most amplitudes with and without runs at hand, and
+# the first beyond; circuits of squeezers and of phase gates, and the share of
 # two-mode gates that outweighs them
 PLANS = [(11, 2, two(11, 12), True), (12, 2, two(12, 12), False), (7, 3, two(7, 12), True), (8, 3, two(8, 12), False),
-         (6, 4, two(6, 12), False), (5, 5, two(5, 12), True), (5, 6, two(5, 12), False), (4, 7, two(4, 12), True),
+         (6, 4, two(6, 3), True), (6, 4, two(6, 2), False), (6, 4, two(6, 6) + phases(6, 12), True),
+         (5, 5, two(5, 12), True), (5, 6, two(5, 12), False), (4, 7, two(4, 12), True),
          (4, 8, two(4, 12), True), (4, 8, [], True), (4, 4, [], True),
          (1, 8, squeezers(1, 1), False), (3, 8, squeezers(3, 2), False), (3, 8, squeezers(3, 2) + two(3, 2), True), (3, 4, squeezers(3, 2), False), (3, 4, squeezers(3, 3), True),
          (3, 7, squeezers(3, 2), False), (3, 6, squeezers(3, 4), True), (3, 6, squeezers(3, 5), False),
