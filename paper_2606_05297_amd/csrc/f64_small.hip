@@ -57,6 +57,11 @@ struct Gate64 {
   double th;
 };
 
+// Doubles of a gate's table: d groups of d x d entries, or d^2 complex ones of a
+// diagonal gate, read as double2: an even number, so that every table starts on 16
+// bytes.
+__host__ __device__ constexpr int table64(int d) { return (d * d * d + 1) & ~1; }
+
 __host__ __device__ constexpr int links64(int d) { return kTwoModeTypes * d * d + 4 * d; }
 
 __host__ __device__ inline int link_row(int type, int d) {
@@ -150,7 +155,8 @@ template <int D, int P>
 __global__ __launch_bounds__(kThreads64) void k64_small(Small64 it, H64 h, EigTables T) {
   extern __shared__ double2 lds[];
   __shared__ double en[2][kWaves64], root[D + 1];
-  constexpr int us = D * D * D, rows = (D + P - 1) / P;
+  constexpr int ne = D * D * D, us = table64(D), rows = (D + P - 1) / P;
+  static_assert(us % 2 == 0 && us >= ne && us >= 2 * D * D, "tables are read as double2");
   const int N = (int)h.n_amp, n = it.n, cap = it.cap;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   double2 *const phi = lds, *const lam = phi + N, *const links = lam + N;
@@ -214,10 +220,10 @@ __global__ __launch_bounds__(kThreads64) void k64_small(Small64 it, H64 h, EigTa
         }
       }
       __syncthreads();
-      for (int x = tid; x < cnt * us; x += kThreads64) {
-        const int g = x / us;
+      for (int x = tid; x < cnt * ne; x += kThreads64) {
+        const int g = x / ne, e = x - g * ne;
         if (!diagonal(gates[g0 + g].type))
-          tab[(size_t)(g0 - k0) * us + x] = entry64<D>(gates[g0 + g], ph + g * D * D, x % us, T);
+          tab[(size_t)(g0 - k0 + g) * us + e] = entry64<D>(gates[g0 + g], ph + g * D * D, e, T);
       }
       __syncthreads();
     }
@@ -482,7 +488,7 @@ __global__ __launch_bounds__(kThreads64) void k64_small(Small64 it, H64 h, EigTa
 size_t small64_fixed(int d, uint32_t namp, int n) {
   return sizeof(double2) * (2 * (size_t)namp + links64(d)) + sizeof(Gate64) * n;
 }
-size_t small64_gate(int d) { return sizeof(double) * (d * d * d + kWaves64); }
+size_t small64_gate(int d) { return sizeof(double) * (table64(d) + kWaves64); }
 size_t small64_phase(int d) { return sizeof(double2) * d * d; }
 
 // Gates in LDS at a time (0: none fit), of which `batch` are built at a time.
