@@ -213,8 +213,8 @@ int eval_gates(fock_adapt64 *st, const std::vector<double> &th, double *E, doubl
   for (int k = 0; k < n; ++k)
     if (!std::isfinite(th[k])) return set_error(FOCK_ERR_NONFINITE, "theta[%d] is not finite", k);
   const double *host = nullptr;
-  const int rc = small64_ok(st->d, st->namp, n) ? eval_small(st, th, g != nullptr, &host)
-                                                : eval_launches(st, th, g != nullptr, &host);
+  const int rc = small64_used(st->h, n, g != nullptr) ? eval_small(st, th, g != nullptr, &host)
+                                                      : eval_launches(st, th, g != nullptr, &host);
   if (rc) return rc;
   if (!std::isfinite(host[0]) || !(host[1] > 0.0))
     return set_error(FOCK_ERR_NONFINITE, "non-finite energy or zero norm (E=%g, norm2=%g)", host[0], host[1]);

@@ -52,6 +52,8 @@ struct Small64 {
 // States and circuits it takes: both states and a few gate tables in one
 // workgroup's LDS.
 bool small64_ok(int d, uint32_t namp, int n);
+// Those that are faster in it than gate by gate.
+bool small64_used(const H64 &h, int n, bool grad);
 // The diagonal and the links between levels of every generator at cutoff d.
 void small64_links(int d, std::vector<double> &out);
 int launch64_small(const Small64 &it, const H64 &h, const EigTables &T, hipStream_t s);

@@ -519,6 +519,14 @@ bool small64_ok(int d, uint32_t namp, int n) {
   return n == 0 ? small64_fixed(d, namp, 0) < kLds64 : small64_cap(d, namp, n, &batch) >= std::min(n, kLeast64);
 }
 
+// The energy of two gates or fewer on many bonds is all H psi, which the chip has
+// sooner than one CU: 4,096 amplitudes of twelve modes, one gate, 47 us by launches,
+// 60 in one (with the gradient 72 and 64); 2,048 of eleven 47 and 41.
+bool small64_used(const H64 &h, int n, bool grad) {
+  const bool all_h = n == 0 || (n <= 2 && !grad);
+  return small64_ok(h.d, h.n_amp, n) && !(all_h && (long)h.n_amp * (h.L - 1) > 30000);
+}
+
 // (diagonal, link to the next level) of every generator's groups, in the order
 // of link_row; zero where a link would leave its block.
 void small64_links(int d, std::vector<double> &out) {

@@ -209,3 +209,26 @@ def test_sweep_of_forced_runs_is_gate_by_gate():
     finally:
         lib.set_gate_fusion(prev)
     assert got[0] == got[1] == got[2]
+
+
+@pytest.mark.parametrize("n", [0, 1, 2, 3])
+def test_complex128_few_gates_on_many_bonds(n):
+    """The first state whose energy of a few gates goes by launches (twelve modes),
+    with and without the gradient, against the oracle.  Tolerance: a gate rounds each
+    amplitude by at most about 2 d eps of the state, on |H| bounded term by term."""
+    L, d = 12, 2
+    print("[case] complex128", L, d, n, flush=True)
+    prm = (1.0, 0.5, 0.1, 0.3, 0.0)
+    ho, hl = O.Ham(L, d, False, *prm), lib.ham(L, d, False, *prm)
+    pool = W.pool(L, "all", False, TWO) + W.site_ops(L, ("KERR", "SR"))
+    ops, th = W.random_circuit(pool, n, seed=n + 1)
+    psi0 = W.random_state(L, d, seed=2, dtype=np.complex128)
+    ad = lib.Adapt64(hl, pool, torch.from_numpy(psi0).cuda(), max_iters=4)
+    Eo, go, _ = O.energy_and_grad_adjoint(ho, psi0, ops, th)
+    tol = 2 * (n + 1) * 4.4e-16 * d * L * (2 * d + 2 * 0.3 * d + 0.25 * d * d + 0.1 * d)
+    E, g = ad.energy_grad(ops, th)
+    assert abs(E - Eo) <= tol and abs(ad.energy_grad(ops, th, grad=False)[0] - Eo) <= tol
+    assert n == 0 or np.abs(g - go).max() <= 2 * d * d * tol * 2
+    s = ad.step()  # scores the state that the launches leave
+    assert abs(s["E_init"] - O.energy_of(ho, psi0, [], [])) <= tol
+    ad.close()
