@@ -203,13 +203,12 @@ int fock_adjoint_sweep(const fock_ham_t *ham, const fock_op_t *ops, const double
  * otherwise create on their first use: the gate eigendata of cutoff d (device
  * memory and a synchronous upload, Sec. II.B), the tile-order tables of the
  * stencil schedules 1-3 for open and ring chains, and this thread's pinned
- * staging buffers at their base size (64 kB each) with its pinned results
- * buffer for real-state gradient evaluations (32 kB).  Afterwards fock_apply_H,
- * fock_apply_gate2 and fock_energy_grad_adjoint on (L, d) from this thread
+ * staging buffer at its base size (64 kB) with its pinned results buffer
+ * (104 kB).  Afterwards fock_apply_H, fock_apply_gate2, fock_score,
+ * fock_pool_grads and fock_energy_grad_adjoint on (L, d) from this thread
  * allocate nothing and add no synchronisation of their own beyond their
- * documented result fetch, for circuits of up to ~2,700 gates.  (Pool scoring
- * outside the slab kernels stages its pair tables through the pinned buffer,
- * which grows on its first such call.)  Idempotent; FOCK_ERR_UNSUPPORTED /
+ * documented result fetch, for circuits of up to ~2,700 gates.  Idempotent;
+ * FOCK_ERR_UNSUPPORTED /
  * FOCK_ERR_SIZE as fock_workspace_bytes; the tables are kept until the process
  * ends. */
 int fock_prepare(int L, int d);

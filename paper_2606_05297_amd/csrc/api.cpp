@@ -129,9 +129,8 @@ static thread_local Pinned tl_in;
 
 // Results written by a kernel straight into host memory: fine-grained
 // (coherent) pinned memory, so the stream synchronisation that follows the
-// kernel is all the host waits for.  One per thread, sized for the longest
-// circuit (energy, norm and 4096 gradients).
-constexpr size_t kHostResults = 2 + 4096;
+// kernel is all the host waits for.  One per thread, of kHostResults doubles (the
+// longest circuit's, or the network's gradient), so that it never moves.
 struct HostResults {
   double *p = nullptr;
   size_t cap = 0;
@@ -140,7 +139,7 @@ struct HostResults {
     if (p) FOCK_HIP(hipHostFree(p));
     p = nullptr;
     const size_t c = std::max<size_t>(count, kHostResults);
-    FOCK_HIP(hipHostMalloc((void **)&p, sizeof(double) * c, hipHostMallocCoherent | hipHostMallocMapped));
+    FOCK_HIP(hipHostMalloc((void **)&p, sizeof(double) * c, kHostResultFlags));
     cap = c;
     return FOCK_OK;
   }
@@ -346,7 +345,7 @@ static int check_energy_rows(const Ctx &c, int G) {
 // its own after them costs 4 us on the device and as much before and after: 30
 // gates with gradients at L = 6, d = 8 take 266 us, 280 with the copy and the
 // energy's reduction apart.
-static int host_results(int count, double **res) {
+int host_results(int count, double **res) {
   const int rc = tl_res.reserve((size_t)count);
   *res = tl_res.p;
   return rc;

@@ -5,6 +5,7 @@
 #include <vector>
 
 #include "mlp_internal.h"
+#include "pipeline.h"
 
 using namespace fock;
 using namespace fock::mlp;
@@ -15,10 +16,7 @@ struct fock_mlp {
   float *params = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr, *partial = nullptr;
   uint16_t *wb = nullptr;
   Count *cnt = nullptr;
-  double *lossp = nullptr;
-  // host-visible, written by the update kernel: loss, gradient
-  double *loss = nullptr;
-  float *host_grad = nullptr;
+  double *lossp = nullptr, *loss = nullptr;
   int step = 0;
 };
 
@@ -37,17 +35,22 @@ int check_batch(const fock_mlp *n, int B) {
 }
 
 // Forward and backward of one batch, then the sums over workgroups: loss,
-// gradient (grad: device or host-visible) and, with ad.on, the Adam update.
-int train(fock_mlp *n, const float *X, const float *T, const int *nv, int B, const AdamArgs &ad, float *grad,
-          hipStream_t s) {
+// gradient (each device or host-visible) and, with ad.on, the Adam update.
+int train(fock_mlp *n, const float *X, const float *T, const int *nv, int B, const AdamArgs &ad, double *loss,
+          float *grad, hipStream_t s) {
   {
     ProfScope ps(FOCK_K_MLP_TRAIN, s, 149504.0 * B);
     const int rc = launch_mlp(true, weights_of(n), X, T, nv, n->cnt, B, nullptr, n->partial, n->lossp, s);
     if (rc) return rc;
   }
   return launch_mlp_update(n->partial, mlp_workgroups(B), grad, n->params, n->m, n->v, ad, n->wb, n->lossp, n->cnt,
-                           n->loss, s);
+                           loss, s);
 }
+
+// Where a call's loss and gradient go that the caller asks for: this thread's
+// results buffer, which the kernels write (the call waits before it returns).
+constexpr int kHostLossGrad = 1 + (NPAR + 1) / 2;  // doubles
+static_assert(kHostLossGrad <= (int)kHostResults, "the buffer never moves");
 
 int finish(hipStream_t s) {
   FOCK_HIP(hipStreamSynchronize(s));
@@ -68,10 +71,10 @@ int fock_mlp_create(int max_batch, fock_mlp_t **out) {
   n->max_batch = max_batch;
   n->max_wg = mlp_partials(max_batch);
   const size_t sp = al256(sizeof(float) * NPAR);
-  const size_t sizes[] = {sp, sp, sp, sp, al256(sizeof(float) * NPAR * (size_t)n->max_wg),
-                          al256(sizeof(uint16_t) * WB_TOTAL), al256(sizeof(Count)),
-                          al256(sizeof(double) * n->max_wg)};
-  size_t total = 0;
+  const size_t sizes[] = {sp, sp, sp, sp, al256(sizeof(uint16_t) * WB_TOTAL), al256(sizeof(Count)),
+                          al256(sizeof(double)), al256(sizeof(double) * n->max_wg),
+                          al256(sizeof(float) * NPAR * (size_t)n->max_wg)};
+  size_t total = 0, zero = 0;
   for (size_t x : sizes) total += x;
   if (hipMalloc(&n->dev, total) != hipSuccess) {
     delete n;
@@ -82,18 +85,14 @@ int fock_mlp_create(int max_batch, fock_mlp_t **out) {
   n->m = (float *)p, p += sizes[1];
   n->v = (float *)p, p += sizes[2];
   n->grad = (float *)p, p += sizes[3];
-  n->partial = (float *)p, p += sizes[4];
-  n->wb = (uint16_t *)p, p += sizes[5];
-  n->cnt = (Count *)p, p += sizes[6];
-  n->lossp = (double *)p;
-  if (hipHostMalloc(&n->loss, 256 + sizeof(float) * NPAR, hipHostMallocDefault) != hipSuccess) {
-    (void)hipFree(n->dev);
-    delete n;
-    return set_error(FOCK_ERR_HIP, "allocation of the network's result buffer failed");
-  }
-  n->host_grad = (float *)((char *)n->loss + 256);
-  if (hipMemset(n->dev, 0, total) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
-    (void)hipHostFree(n->loss);
+  n->wb = (uint16_t *)p, p += sizes[4];
+  n->cnt = (Count *)p, p += sizes[5];
+  n->loss = (double *)p, p += sizes[6];
+  zero = (size_t)(p - (char *)n->dev);
+  // partials: written by each call before they are read
+  n->lossp = (double *)p, p += sizes[7];
+  n->partial = (float *)p;
+  if (hipMemset(n->dev, 0, zero) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
     (void)hipFree(n->dev);
     delete n;
     return set_error(FOCK_ERR_HIP, "clearing the network buffers failed");
@@ -144,11 +143,14 @@ int fock_mlp_loss_grad(fock_mlp_t *n, const float *X, const float *T, const int 
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
   AdamArgs off{};
-  rc = train(n, X, T, nvalid, B, off, grad ? n->host_grad : n->grad, s);
-  if (rc || (!grad && !loss)) return rc;
+  double *host = nullptr;
+  if ((grad || loss) && (rc = host_results(kHostLossGrad, &host))) return rc;
+  float *const host_grad = (float *)(host + 1);
+  rc = train(n, X, T, nvalid, B, off, host ? host : n->loss, grad ? host_grad : n->grad, s);
+  if (rc || !host) return rc;
   if ((rc = finish(s))) return rc;
-  if (grad) memcpy(grad, n->host_grad, sizeof(float) * NPAR);
-  if (loss) *loss = *n->loss;
+  if (grad) memcpy(grad, host_grad, sizeof(float) * NPAR);
+  if (loss) *loss = *host;
   return FOCK_OK;
 }
 
@@ -159,6 +161,8 @@ int fock_mlp_adam_step(fock_mlp_t *n, const float *X, const float *T, const int 
   int rc = check_batch(n, B);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
+  double *host = nullptr;
+  if (loss && (rc = host_results(1, &host))) return rc;
   n->step += 1;
   AdamArgs ad;
   ad.on = 1;
@@ -168,10 +172,10 @@ int fock_mlp_adam_step(fock_mlp_t *n, const float *X, const float *T, const int 
   ad.eps = 1e-8f;
   ad.bc1 = (float)(1.0 - std::pow(0.9, n->step));
   ad.bc2 = (float)(1.0 - std::pow(0.999, n->step));
-  rc = train(n, X, T, nvalid, B, ad, n->grad, s);
+  rc = train(n, X, T, nvalid, B, ad, loss ? host : n->loss, n->grad, s);
   if (rc || !loss) return rc;
   if ((rc = finish(s))) return rc;
-  *loss = *n->loss;
+  *loss = *host;
   return FOCK_OK;
 }
 
@@ -179,7 +183,6 @@ int fock_mlp_destroy(fock_mlp_t *n) {
   if (!n) return FOCK_OK;
   (void)hipDeviceSynchronize();
   if (n->dev) (void)hipFree(n->dev);
-  if (n->loss) (void)hipHostFree(n->loss);
   delete n;
   return FOCK_OK;
 }

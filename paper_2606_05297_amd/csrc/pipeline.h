@@ -36,6 +36,14 @@ struct Ctx {
 
 int gate_fusion_mode();  // FOCK_FUSE_*
 
+// Results that kernels write into host memory: fine-grained, so that they are there
+// once the stream is done.
+constexpr unsigned kHostResultFlags = hipHostMallocCoherent | hipHostMallocMapped;
+// The calling thread's buffer for count of them, at most kHostResults; a call that
+// hands it to a kernel waits for the stream before it returns.
+constexpr size_t kHostResults = 13312;
+int host_results(int count, double **res);
+
 int check_geometry(int L, int d, uint32_t *namp);
 // check_ham takes full d^L states only; check_ham_layout also the parity-halved
 // layout (namp = d^L / 2 then) and, with allow_real, FOCK_LAYOUT_REAL.
