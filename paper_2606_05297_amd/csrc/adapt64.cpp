@@ -43,8 +43,6 @@ struct fock_adapt64 {
   std::vector<double> sums;    // results of the gate-by-gate evaluation
   std::map<int, double2 *> A;  // dense generator per type
   int maxblk = 0;
-  // small states (small64_ok): generator links (behind res); pinned angles, results and gates
-  double *links = nullptr, *host = nullptr;
   int iter = 0;
   bool done = false;
   fock_adapt_report_t warm{};  // warm-up optimisation done at creation (iter 0)
@@ -128,22 +126,27 @@ int fetch(fock_adapt64 *st, int n, double *host) {
   return FOCK_OK;
 }
 
-// Pinned buffer of the one-launch evaluation: angles, then results, then gates.
-constexpr size_t kHost64 = sizeof(double) * (2 * kGates64 + 2) + sizeof(int) * kGates64;
+// The one-launch evaluation's part of this thread's results buffer: angles, then
+// results, then gates.
+constexpr int kHost64 = 2 * kGates64 + 2 + kGates64 / 2;  // doubles
+static_assert(kHost64 <= (int)kHostResults, "the buffer never moves");
 
 // E, <psi|psi> and the gate sums of a small state (f64_small.hip) into out.
 int eval_small(fock_adapt64 *st, const std::vector<double> &th, bool grad, const double **out) {
   const int n = (int)th.size();
-  double *res = st->host + kGates64;
+  double *theta = nullptr;
+  const double2 *links = nullptr;
+  int rc = host_results(kHost64, &theta);
+  if (rc || (rc = small64_links(st->d, &links))) return rc;
+  double *res = theta + kGates64;
   int *gates = (int *)(res + 2 + kGates64);
   for (int k = 0; k < n; ++k) {
     const fock_op_t &op = st->gops[k];
-    st->host[k] = th[k];
+    theta[k] = th[k];
     gates[k] = op.type | gate_modes(op) << 8;
   }
-  Small64 it{st->psi0, st->phi, st->lam, st->host, (const double2 *)st->links, gates, res, n, grad ? 1 : 0, 0, 0};
-  const int rc = launch64_small(it, st->h, st->T, st->s);
-  if (rc) return rc;
+  Small64 it{st->psi0, st->phi, st->lam, theta, links, gates, res, n, grad ? 1 : 0, 0, 0};
+  if ((rc = launch64_small(it, st->h, st->T, st->s))) return rc;
   FOCK_HIP(hipStreamSynchronize(st->s));
   *out = res;
   return FOCK_OK;
@@ -269,7 +272,6 @@ void release(fock_adapt64 *st) {
   for (void *p : {(void *)st->psi0, (void *)st->phi, (void *)st->lam, (void *)st->utab, (void *)st->partial,
                   (void *)st->res, (void *)st->th_dev, (void *)st->recs})
     if (p) (void)hipFree(p);
-  if (st->host) (void)hipHostFree(st->host);
   for (auto &kv : st->A) (void)hipFree(kv.second);
   if (st->s) (void)hipStreamDestroy(st->s);
 }
@@ -335,9 +337,7 @@ int adapt64_create(const fock_ham_t *ham, const fock_op_t *pool, int P, const vo
     const uint32_t fpw = (uint32_t)std::max(1, kBlock / M), nf = namp / (uint32_t)M;
     st->maxblk = std::max(st->maxblk, (int)((nf + fpw - 1) / fpw));
   }
-  const int rows = (std::max(2 + st->cap, P) + 3) & ~1;  // even: the links behind them are read in pairs
-  std::vector<double> links;
-  if (small64_ok(st->d, st->namp, 0)) small64_links(st->d, links);
+  const int rows = std::max(2 + st->cap, P) + 2;
   auto fail = [&](int code) {
     release(st);
     delete st;
@@ -350,7 +350,7 @@ int adapt64_create(const fock_ham_t *ham, const fock_op_t *pool, int P, const vo
       hipMalloc(&st->lam, bs) != hipSuccess ||
       hipMalloc(&st->utab, sizeof(double2) * (size_t)st->cap * st->Mmax * st->Mmax) != hipSuccess ||
       hipMalloc(&st->partial, sizeof(double) * (size_t)rows * st->maxblk) != hipSuccess ||
-      hipMalloc(&st->res, sizeof(double) * (rows + links.size())) != hipSuccess ||
+      hipMalloc(&st->res, sizeof(double) * rows) != hipSuccess ||
       hipMalloc(&st->th_dev, sizeof(double) * st->cap) != hipSuccess ||
       hipMalloc(&st->recs, sizeof(GateRec) * st->cap) != hipSuccess)
     return fail(set_error(FOCK_ERR_HIP, "device allocation failed"));
@@ -360,12 +360,6 @@ int adapt64_create(const fock_ham_t *ham, const fock_op_t *pool, int P, const vo
   if (hipMemcpyAsync(st->psi0, psi0, bs, hipMemcpyDeviceToDevice, st->s) != hipSuccess)
     return fail(set_error(FOCK_ERR_HIP, "copy of psi0 failed"));
   if ((rc = get_tables(ham->d, &st->T))) return fail(rc);
-  if (!links.empty()) {
-    st->links = st->res + rows;
-    if (hipMemcpyAsync(st->links, links.data(), sizeof(double) * links.size(), hipMemcpyHostToDevice, st->s) != hipSuccess ||
-        hipHostMalloc(&st->host, kHost64, hipHostMallocDefault) != hipSuccess)
-      return fail(set_error(FOCK_ERR_HIP, "set-up of the small-state evaluation failed"));
-  }
   st->warm.iter = 0;
   st->warm.k_sel = -1;
   double E0 = 0.0, n2 = 0.0;

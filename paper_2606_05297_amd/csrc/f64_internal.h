@@ -1,8 +1,6 @@
 // FP64-state path: parameters and launchers (f64_kernels.hip, f64_small.hip).
 #pragma once
 
-#include <vector>
-
 #include "device_common.h"
 
 namespace fock {
@@ -37,7 +35,7 @@ int launch64_build(const double *theta, const GateRec *recs, int n, const EigTab
 // the n gates, then (<phi|H phi>, <phi|phi>) into res[0..1] and, with grad,
 // Re<lam_k|A_k phi_k> into res[2 + k]; without grad the states go to phi and
 // lam.  theta, gates (type | gate_modes << 8) and res are
-// host-visible; links: the rows of small64_links on the device.
+// host-visible; links: small64_links.
 struct Small64 {
   const double2 *psi0;
   double2 *phi, *lam;
@@ -54,8 +52,9 @@ struct Small64 {
 bool small64_ok(int d, uint32_t namp, int n);
 // Those that are faster in it than gate by gate.
 bool small64_used(const H64 &h, int n, bool grad);
-// The diagonal and the links between levels of every generator at cutoff d.
-void small64_links(int d, std::vector<double> &out);
+// The diagonal and the links between levels of every generator at cutoff d <= 8, on
+// the current device: made on first use and kept, like the gate eigendata (13 kB).
+int small64_links(int d, const double2 **out);
 int launch64_small(const Small64 &it, const H64 &h, const EigTables &T, hipStream_t s);
 // Circuits of at most so many gates.
 constexpr int kGates64 = 256;

@@ -34,7 +34,10 @@
 #include "f64_internal.h"
 
 #include <algorithm>
+#include <map>
+#include <mutex>
 #include <type_traits>
+#include <vector>
 
 #include "tile_gate.h"
 
@@ -529,8 +532,8 @@ bool small64_used(const H64 &h, int n, bool grad) {
 
 // (diagonal, link to the next level) of every generator's groups, in the order
 // of link_row; zero where a link would leave its block.
-void small64_links(int d, std::vector<double> &out) {
-  out.assign((size_t)2 * links64(d), 0.0);
+static std::vector<double> build_links(int d) {
+  std::vector<double> out((size_t)2 * links64(d), 0.0);
   std::vector<double> A;
   auto put = [&](int row, int type, int M, int p, int up) {
     const int im = imaginary(type) ? 1 : 0;
@@ -551,6 +554,28 @@ void small64_links(int d, std::vector<double> &out) {
     for (int p = 0; p < d; ++p)
       put(link_row(type, d) + p, type, d, p, (type == FOCK_SR || type == FOCK_SI) && p + 2 < d ? p + 2 : -1);
   }
+  return out;
+}
+
+int small64_links(int d, const double2 **out) {
+  static std::mutex mu;
+  static std::map<std::pair<int, int>, const double2 *> made;
+  int dev = 0;
+  FOCK_HIP(hipGetDevice(&dev));
+  std::lock_guard<std::mutex> lk(mu);
+  const double2 *&p = made[{dev, d}];
+  if (!p) {
+    const std::vector<double> h = build_links(d);
+    void *b = nullptr;
+    FOCK_HIP(hipMalloc(&b, sizeof(double) * h.size()));
+    if (hipMemcpy(b, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice) != hipSuccess) {
+      (void)hipFree(b);
+      return set_error(FOCK_ERR_HIP, "upload of the generator links failed");
+    }
+    p = (const double2 *)b;
+  }
+  *out = p;
+  return FOCK_OK;
 }
 
 int launch64_small(const Small64 &item, const H64 &h, const EigTables &T, hipStream_t s) {

@@ -69,3 +69,36 @@ def test_networks_and_circuits():
             assert np.array_equal(j(), want)
     for got, want in zip(together(jobs), alone):
         assert all(np.array_equal(g, want) for g in got)
+
+
+def run64(L, d, seed, max_iters=20):
+    h = lib.ham(L, d, False, 1.0, 0.5, 0.1, 0.3, 0.0)
+    pool = W.pool(L, "all", False, ("HR", "PI", "CK")) + W.site_ops(L, ("SR", "KERR"))
+    ops, th = W.random_circuit(pool, 18, seed=seed)
+    x = torch.from_numpy(W.random_state(L, d, seed=seed, dtype=np.complex128)).cuda()
+    ad = lib.Adapt64(h, pool, x, max_iters=max_iters)
+
+    def run():
+        E, g = ad.energy_grad(ops, th)
+        return np.concatenate([[E, ad.energy_grad(ops, th, grad=False)[0]], g])
+    return run
+
+
+def test_complex128_and_others():
+    print("[case] threads: complex128", flush=True)
+    jobs = [run64(3, 4, 1), run64(3, 5, 2), run64(4, 6, 3), run64(3, 4, 4), network(4, 300), circuit(4, 4, 5)]
+    alone = [j() for j in jobs]
+    for j, want in zip(jobs, alone):
+        assert np.array_equal(j(), want)
+    for got, want in zip(together(jobs), alone):
+        assert all(np.array_equal(g, want) for g in got)
+
+
+def test_handles_made_on_one_thread_and_used_on_another():
+    print("[case] threads: handles", flush=True)
+    jobs = together([lambda: run64(3, 8, 1), lambda: run64(3, 7, 2), lambda: run64(3, 8, 3)])
+    runs = [r for js in jobs for r in js[:2]]
+    first = [r() for r in runs]
+    for r, w in zip(runs, first):
+        assert np.array_equal(r(), w)
+    assert np.array_equal(first[0], first[1]) and np.array_equal(first[2], first[3])
