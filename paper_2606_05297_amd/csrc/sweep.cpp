@@ -77,7 +77,8 @@ struct fock_sweep {
   std::vector<DGroup> groups;
   fock_adapt_opts_t opt;
   hipStream_t s = nullptr;  // private non-blocking stream (graph capture needs one)
-  // side streams of an evaluation round (forked from s and joined to it)
+  // side streams of an evaluation round (forked from s and joined to it), as many as
+  // a round has needed
   hipStream_t side[kSideStreams] = {};
   hipEvent_t fork = nullptr, join[kSideStreams] = {};
   void *dbuf = nullptr;
@@ -143,6 +144,7 @@ struct Lists {
   std::vector<GroupLists> g;                // [group]
   std::vector<DevList<SmallItem>> small;    // points evaluated by one workgroup each, per launch
   DevList<HamArgs> hams;                    // [point]
+  int nside = 0;                            // side streams of a round
 };
 
 // Whether a point's circuit is evaluated whole by one workgroup (the rule of
@@ -324,6 +326,39 @@ int upload_recs(fock_sweep *sw) {
   return FOCK_OK;
 }
 
+// Side streams of a round: chains run side by side only where that saves more than
+// the fork and the join cost (about 40 us a round), by the chains' times in us from
+// the kernels' measured ones.  A sweep of four short chains takes 34 ms with side
+// streams and 39 without, of two short ones 17.9 - 19.2 and 16.9 - 17.2.
+int side_streams(const Lists &Ls, bool grad) {
+  int chains = 0;
+  double total = 0.0, longest = 0.0;
+  auto chain_of = [&](double us) {
+    ++chains;
+    total += us;
+    longest = std::max(longest, us);
+  };
+  for (const GroupLists &GL : Ls.g)
+    if (!GL.h.v.empty()) chain_of(25.0 + (grad ? 24.0 : 10.0) * (double)GL.layers.size());
+  for (const DevList<SmallItem> &l : Ls.small) {
+    double us = 0.0;
+    for (const SmallItem &it : l.v) us = std::max(us, 10.0 + it.n * (1.2 + 8.5e-4 * it.N));
+    chain_of(us);
+  }
+  return total - longest > 40.0 ? std::min(chains - 1, kSideStreams) : 0;  // the first chain stays on s
+}
+
+// The streams and events of n side streams, made on first use: a sweep whose rounds
+// are one chain needs none (they take 90 us to make and 60 to destroy).
+int make_side_streams(fock_sweep *sw, int n) {
+  if (n > 0 && !sw->fork) FOCK_HIP(hipEventCreateWithFlags(&sw->fork, hipEventDisableTiming));
+  for (int b = 0; b < n; ++b) {
+    if (!sw->join[b]) FOCK_HIP(hipEventCreateWithFlags(&sw->join[b], hipEventDisableTiming));
+    if (!sw->side[b]) FOCK_HIP(hipStreamCreateWithFlags(&sw->side[b], hipStreamNonBlocking));
+  }
+  return FOCK_OK;
+}
+
 // Enqueue one evaluation round (forward, H psi, optional reverse sweep,
 // reductions) of the points in the current lists.  The points of each cutoff
 // and each launch of small points are chains of their own; they run side by
@@ -340,25 +375,7 @@ int enqueue_eval(fock_sweep *sw, const Lists &Ls, bool grad, bool upload) {
       if (rc) return rc;
     }
   }
-  // Side by side only where that saves more than the fork and the join cost (about
-  // 40 us a round): the chains' times, in us, from the kernels' measured ones.  A
-  // sweep of four short chains takes 34 ms with side streams and 39 without, of two
-  // short ones 17.9 - 19.2 and 16.9 - 17.2.
-  int chains = 0;
-  double total = 0.0, longest = 0.0;
-  auto chain_of = [&](double us) {
-    ++chains;
-    total += us;
-    longest = std::max(longest, us);
-  };
-  for (const GroupLists &GL : Ls.g)
-    if (!GL.h.v.empty()) chain_of(25.0 + (grad ? 24.0 : 10.0) * (double)GL.layers.size());
-  for (const DevList<SmallItem> &l : Ls.small) {
-    double us = 0.0;
-    for (const SmallItem &it : l.v) us = std::max(us, 10.0 + it.n * (1.2 + 8.5e-4 * it.N));
-    chain_of(us);
-  }
-  const int nside = total - longest > 40.0 ? std::min(chains - 1, kSideStreams) : 0;  // the first chain stays on s
+  const int nside = Ls.nside;
   if (nside > 0) FOCK_HIP(hipEventRecord(sw->fork, s));
   for (int b = 0; b < nside; ++b) FOCK_HIP(hipStreamWaitEvent(sw->side[b], sw->fork, 0));
   int chain = 0;
@@ -418,7 +435,7 @@ int enqueue_eval(fock_sweep *sw, const Lists &Ls, bool grad, bool upload) {
   return FOCK_OK;
 }
 
-// Lay out all item lists in one device blob.
+// Lay out all item lists in one device blob, and choose the round's streams.
 int stage_lists(fock_sweep *sw, Lists &Ls, bool grad) {
   std::vector<char> blob;
   auto put = [&](auto &l) { l.off = push_items(blob, l.v); };
@@ -439,7 +456,9 @@ int stage_lists(fock_sweep *sw, Lists &Ls, bool grad) {
   }
   for (auto &l : Ls.small) put(l);
   put(Ls.hams);
-  return upload_blob(sw, blob);
+  Ls.nside = side_streams(Ls, grad);
+  const int rc = make_side_streams(sw, Ls.nside);
+  return rc ? rc : upload_blob(sw, blob);
 }
 
 void pack_angles(fock_sweep *sw) {
@@ -757,12 +776,7 @@ int fock_sweep_create(const fock_sweep_point_t *pts, int npts, const fock_adapt_
   if (hipStreamSynchronize((hipStream_t)stream) != hipSuccess) return set_error(FOCK_ERR_HIP, "caller stream error");
   fock_sweep *sw = new fock_sweep();
   sw->opt = *opts;
-  bool ok = hipStreamCreateWithFlags(&sw->s, hipStreamNonBlocking) == hipSuccess &&
-            hipEventCreateWithFlags(&sw->fork, hipEventDisableTiming) == hipSuccess;
-  for (int b = 0; b < kSideStreams && ok; ++b)
-    ok = hipStreamCreateWithFlags(&sw->side[b], hipStreamNonBlocking) == hipSuccess &&
-         hipEventCreateWithFlags(&sw->join[b], hipEventDisableTiming) == hipSuccess;
-  if (!ok) {
+  if (hipStreamCreateWithFlags(&sw->s, hipStreamNonBlocking) != hipSuccess) {
     fock_sweep_destroy(sw);
     return set_error(FOCK_ERR_HIP, "stream creation failed");
   }
