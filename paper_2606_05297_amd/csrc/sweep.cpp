@@ -359,25 +359,10 @@ int make_side_streams(fock_sweep *sw, int n) {
   return FOCK_OK;
 }
 
-// Enqueue one evaluation round (forward, H psi, optional reverse sweep,
-// reductions) of the points in the current lists.  The points of each cutoff
-// and each launch of small points are chains of their own; they run side by
-// side on streams forked from s and joined to it.
-int enqueue_eval(fock_sweep *sw, const Lists &Ls, bool grad, bool upload) {
+// The chains of a round, on s and nside side streams in turn.
+int enqueue_chains(fock_sweep *sw, const Lists &Ls, bool grad, int nside) {
   hipStream_t s = sw->s;
   char *base = (char *)sw->items_d;
-  if (upload) {
-    // angles and active flags, adjacent here and there
-    FOCK_HIP(hipMemcpyAsync(sw->up_d, pin_up(sw), al256(sizeof(double) * sw->n_up) + sizeof(int) * sw->pts.size(),
-                            hipMemcpyHostToDevice, s));
-    for (auto &G : sw->groups) {
-      int rc = launch_gate_build(G.theta, G.recs, G.ngates, G.T, G.utab, G.rtab, s);
-      if (rc) return rc;
-    }
-  }
-  const int nside = Ls.nside;
-  if (nside > 0) FOCK_HIP(hipEventRecord(sw->fork, s));
-  for (int b = 0; b < nside; ++b) FOCK_HIP(hipStreamWaitEvent(sw->side[b], sw->fork, 0));
   int chain = 0;
   auto next_stream = [&]() {
     const int c = chain++ % (nside + 1);
@@ -430,9 +415,46 @@ int enqueue_eval(fock_sweep *sw, const Lists &Ls, bool grad, bool upload) {
                                G.T, sw->active_d, next_stream());
     if (rc) return rc;
   }
-  for (int b = 0; b < nside; ++b) FOCK_HIP(hipEventRecord(sw->join[b], sw->side[b]));
-  for (int b = 0; b < nside; ++b) FOCK_HIP(hipStreamWaitEvent(s, sw->join[b], 0));
   return FOCK_OK;
+}
+
+// Enqueue one evaluation round (forward, H psi, optional reverse sweep,
+// reductions) of the points in the current lists.  The points of each cutoff
+// and each launch of small points are chains of their own; they run side by
+// side on streams forked from s and joined to it.
+int enqueue_eval(fock_sweep *sw, const Lists &Ls, bool grad, bool upload) {
+  hipStream_t s = sw->s;
+  if (upload) {
+    // angles and active flags, adjacent here and there
+    FOCK_HIP(hipMemcpyAsync(sw->up_d, pin_up(sw), al256(sizeof(double) * sw->n_up) + sizeof(int) * sw->pts.size(),
+                            hipMemcpyHostToDevice, s));
+    for (auto &G : sw->groups) {
+      int rc = launch_gate_build(G.theta, G.recs, G.ngates, G.T, G.utab, G.rtab, s);
+      if (rc) return rc;
+    }
+  }
+  const int nside = Ls.nside;
+  int forked = 0;
+  // Whatever has been forked is joined, also after an error: under capture a stream
+  // left behind would stay in it.
+  auto join = [&]() -> int {
+    hipError_t e = hipSuccess;
+    for (int b = 0; b < forked; ++b) {
+      hipError_t r = hipEventRecord(sw->join[b], sw->side[b]);
+      if (r == hipSuccess) r = hipStreamWaitEvent(s, sw->join[b], 0);
+      if (e == hipSuccess) e = r;
+    }
+    return e == hipSuccess ? FOCK_OK : set_error(FOCK_ERR_HIP, "joining a side stream: %s", hipGetErrorString(e));
+  };
+  if (nside > 0) FOCK_HIP(hipEventRecord(sw->fork, s));
+  for (; forked < nside; ++forked)
+    if (hipStreamWaitEvent(sw->side[forked], sw->fork, 0) != hipSuccess) {
+      (void)join();
+      return set_error(FOCK_ERR_HIP, "forking a side stream");
+    }
+  const int rc = enqueue_chains(sw, Ls, grad, nside);
+  const int jrc = join();
+  return rc ? rc : jrc;
 }
 
 // Lay out all item lists in one device blob, and choose the round's streams.
