@@ -428,8 +428,11 @@ int enqueue_eval(fock_sweep *sw, const Lists &Ls, bool grad, bool upload) {
     // angles and active flags, adjacent here and there
     FOCK_HIP(hipMemcpyAsync(sw->up_d, pin_up(sw), al256(sizeof(double) * sw->n_up) + sizeof(int) * sw->pts.size(),
                             hipMemcpyHostToDevice, s));
-    for (auto &G : sw->groups) {
-      int rc = launch_gate_build(G.theta, G.recs, G.ngates, G.T, G.utab, G.rtab, s);
+    for (size_t gi = 0; gi < sw->groups.size(); ++gi) {
+      const DGroup &G = sw->groups[gi];
+      bool runs = false;  // the tables of fused runs
+      for (const GroupLists::Layer &Ly : Ls.g[gi].layers) runs = runs || !Ly.runs.empty();
+      int rc = launch_gate_build(G.theta, G.recs, G.ngates, G.T, G.utab, runs ? G.rtab : nullptr, s);
       if (rc) return rc;
     }
   }
@@ -552,7 +555,6 @@ int bfgs_phase(fock_sweep *sw, const std::vector<char> &sel, const std::vector<d
     const int brc = build_lists(sw, sel, true, &Ls);
     if (brc) return brc;
   }
-  std::vector<size_t> offs;
   int rc = stage_lists(sw, Ls, true);
   if (rc) return rc;
   rc = upload_recs(sw);
@@ -1177,7 +1179,6 @@ int fock_sweep_autotune(fock_sweep_t *sw, const char *cache_path, int *best_grid
     const int brc = build_lists(sw, sel, false, &Ls);
     if (brc) return brc;
   }
-  std::vector<size_t> offs;
   int rc = upload_recs(sw);
   if (rc) return rc;
   rc = stage_lists(sw, Ls, false);
