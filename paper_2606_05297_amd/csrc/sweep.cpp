@@ -882,7 +882,7 @@ int fock_sweep_create(const fock_sweep_point_t *pts, int npts, const fock_adapt_
   }
   const size_t pin_bytes =
       al256(sizeof(double) * sw->n_up) + al256(sizeof(int) * npts) + al256(sizeof(double) * sw->n_res);
-  if (!rc && hipHostMalloc(&sw->pin, pin_bytes, hipHostMallocDefault) != hipSuccess)
+  if (!rc && hipHostMalloc(&sw->pin, pin_bytes, kHostResultFlags) != hipSuccess)
     rc = set_error(FOCK_ERR_HIP, "pinned allocation failed");
   if (!rc) memset(sw->pin, 0, pin_bytes);
   for (int p = 0; p < npts && !rc; ++p) {

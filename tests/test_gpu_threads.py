@@ -102,3 +102,30 @@ def test_handles_made_on_one_thread_and_used_on_another():
     for r, w in zip(runs, first):
         assert np.array_equal(r(), w)
     assert np.array_equal(first[0], first[1]) and np.array_equal(first[2], first[3])
+
+
+def sweep_run(seed):
+    entries = []
+    for L, d in ((4, 4), (3, 8), (4, 6)):
+        x = torch.zeros(d ** L, dtype=torch.complex64, device="cuda")
+        x[W.fock_index(L, d, [1] * L)] = 1
+        warm = W.warmup_ops(L, False)
+        entries.append(dict(ham=lib.ham(L, d, False, 1.0, 1.0 + seed), pool=W.pool(L, "nn", False, W.BH_TYPES), psi0=x,
+                            warm_ops=warm, warm_theta0=W.warmup_theta0(len(warm), seed)))
+    torch.cuda.synchronize()
+
+    def run():
+        sw = lib.Sweep(entries, max_iters=3)
+        r = sw.warm_reports() + sw.step()[0]
+        sw.close()
+        return np.array([[v["E"], v["k_sel"], v["bfgs_evals"]] for v in r])
+    return run
+
+
+def test_sweeps_at_once():
+    """Rounds that write into the sweep's own host memory, from chains on side streams."""
+    print("[case] threads: sweeps", flush=True)
+    jobs = [sweep_run(1), sweep_run(2), circuit(4, 4, 6)]
+    alone = [j() for j in jobs]
+    for got, want in zip(together(jobs), alone):
+        assert all(np.array_equal(g, want) for g in got)
