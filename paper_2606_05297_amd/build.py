@@ -86,7 +86,8 @@ _MFMA_RE = re.compile(r"v_mfma_\w+\s+([av])\[(\d+):(\d+)\],[^\n]*,\s*([av])\[(\d
 def check_mfma_operands(src: str) -> int:
     """Compile `src` to gfx950 device assembly and reject any matrix instruction
     whose destination registers partially overlap its accumulator input (the
-    two must be identical or disjoint; a partial overlap gives wrong sums).
+    two must be identical or disjoint; a partial overlap gives wrong sums), and
+    static LDS where the kernels rule it out (LDS_FROM_ZERO).
     Returns the number of MFMA instructions inspected."""
     asm = os.path.join(BUILD, os.path.splitext(src)[0] + ".s")
     cmd = [HIPCC, *COMMON, "--cuda-device-only", "-S", "-x", "hip", os.path.join(CSRC, src), "-o", asm]
@@ -94,9 +95,14 @@ def check_mfma_operands(src: str) -> int:
     if r.returncode != 0:
         raise RuntimeError(f"assembly generation failed: {' '.join(cmd)}\n{r.stderr}")
     with open(asm) as fh:
-        n, bad = mfma_overlaps(fh.read())
+        text = fh.read()
+    n, bad = mfma_overlaps(text)
     if bad:
         raise RuntimeError(f"{src}: matrix instruction with partially overlapping dst/srcC: {bad[0]}")
+    if src in LDS_FROM_ZERO:
+        for kernel, size in static_lds(text).items():
+            if size:
+                raise RuntimeError(f"{src}: {kernel} has {size} bytes of static LDS, its dynamic LDS has to start at 0")
     return n
 
 
@@ -110,6 +116,18 @@ def mfma_overlaps(text: str):
         if dk == ck and (d0, d1) != (c0, c1) and not (d1 < c0 or c1 < d0):
             bad.append(m.group(0).strip())
     return n, bad
+
+
+# Sources whose kernels take the start of their dynamic LDS for address 0
+# (fibre_gate.h combines LDS addresses by exclusive or): no static LDS before it.
+LDS_FROM_ZERO = ["tile_runs.hip"]
+
+_LDS_RE = re.compile(r"\.amdhsa_kernel\s+(\S+).*?\.amdhsa_group_segment_fixed_size\s+(\d+)", re.S)
+
+
+def static_lds(text: str) -> dict:
+    """Bytes of static LDS of every kernel in device assembly text."""
+    return {m.group(1): int(m.group(2)) for m in _LDS_RE.finditer(text)}
 
 
 def build(jobs: int = 8, verbose: bool = True) -> str:
