@@ -225,6 +225,7 @@ int make_ctx(const fock_ham_t &ham, uint32_t namp, int P, int n, void *ws, size_
 static FuseTables tables_of(Ctx &c) { return {(const float2 *)(c.ws + c.L.utab), (const float *)(c.ws + c.L.rtab)}; }
 
 int stage_gates(Ctx &c, const fock_op_t *ops, const double *theta, int n, const int *nblk, bool runs) {
+  if (n > c.L.nmax) return set_error(FOCK_ERR_SIZE, "circuit of %d gates exceeds the workspace's %d", n, c.L.nmax);
   float *const rtab = runs ? (float *)(c.ws + c.L.rtab) : nullptr;  // the tables of fused runs
   const int stride = gate_stride(c.g.d);
   if (n <= kArgGates) {  // angles and records ride in the build kernel's arguments
@@ -379,7 +380,6 @@ static bool fused_runs(const Ctx &c) {
 static bool reverse_fused(const Ctx &c) { return c.fuse != FOCK_FUSE_FORWARD; }
 
 static int stage_circuit(Ctx &c, const fock_op_t *ops, const double *theta, int n, std::vector<GateGroup> *groups) {
-  if (n > c.L.nmax) return set_error(FOCK_ERR_SIZE, "circuit of %d gates exceeds the workspace's %d", n, c.L.nmax);
   if (c.g.half)
     for (int k = 0; k < n; ++k)
       if (!half_layout_op_ok(ops[k], c.g.L))
@@ -732,7 +732,6 @@ SmallItem small_item(const HamArgs &h, uint32_t namp, int n, bool grad) {
 // <H>, <1> and, with grad, the raw gate sums.
 static int enqueue_small(Ctx &c, const fock_op_t *ops, const double *theta, int n, const void *psi0, float2 *phi,
                          float2 *lam, bool grad, double *res) {
-  if (n > c.L.nmax) return set_error(FOCK_ERR_SIZE, "circuit of %d gates exceeds the workspace's %d", n, c.L.nmax);
   int rc = n > 0 ? stage_gates(c, ops, theta, n, nullptr) : FOCK_OK;
   if (rc) return rc;
   SmallItem it = small_item(c.h, c.g.n_amp, n, grad);
