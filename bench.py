@@ -292,7 +292,8 @@ def main():
             g_sum = l_sum = 0
             for r in reps:
                 n_s = r["n_params"]
-                runs = lib.real_fusion_plan(hf, ops_final[:n_s])
+                order = lib.real_fusion_order(hf, ops_final[:n_s])  # as the evaluations run them
+                runs = lib.real_fusion_plan(hf, [ops_final[k] for k in order])
                 ends = [k0 for k0, _ in runs[1:]] + [n_s]
                 for (k0, a), k1 in zip(runs, ends):
                     if a >= 0:

@@ -574,14 +574,20 @@ int fock_set_real_fusion(int mode);
 int fock_get_real_fusion(void);
 
 /* The runs of ops[0..n) on real states, in the given order, under the current
- * fusion mode (host only: no device work).  run_k0[r] is the first
- * gate of run r (runs are consecutive and cover the circuit in order), run_a[r]
+ * fusion mode (host only: no device work); see fock_real_fusion_order for those
+ * of an evaluation.  run_k0[r] is the first gate of run r (runs are consecutive and cover the circuit in order), run_a[r]
  * the lowest of its three tile modes, or -1 for a gate taken by the per-gate
  * kernels; *nruns receives the count.  ham->layout selects the geometry (full
  * or parity-halved; FOCK_LAYOUT_REAL optional).  run_k0 and run_a hold n
  * entries (caller owned).  Errors: FOCK_ERR_ARG (layout, pairs, NULL arrays),
  * FOCK_ERR_UNSUPPORTED (a gate other than HR or PR). */
 int fock_real_fusion_plan(const fock_ham_t *ham, const fock_op_t *ops, int n, int *run_k0, int *run_a, int *nruns);
+
+/* The order in which an evaluation on real states runs ops[0..n): its k-th gate is
+ * ops[at[k]] (host only).  fock_real_fusion_plan of the gates in this order gives
+ * the runs that the evaluation launches.  at holds n entries; arguments and errors
+ * as there. */
+int fock_real_fusion_order(const fock_ham_t *ham, const fock_op_t *ops, int n, int *at);
 
 /* ------------------------------------------------------------------ FP64 states */
 

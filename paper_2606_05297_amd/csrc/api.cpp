@@ -578,35 +578,23 @@ struct RealCircuit {
 static RealCircuit real_order(const Geometry &g, const fock_op_t *ops, const double *theta, int n) {
   const int top = real_fuse_supported(g) ? real_fuse_top(g) : -1;
   auto fusable = [&](int k) { return ops[k].i >= 0 && ops[k].j == ops[k].i + 1 && ops[k].j <= top; };
+  std::vector<unsigned> modes(n);
+  for (int k = 0; k < n; ++k) modes[k] = (1u << ops[k].i) | (1u << ops[k].j);
   RealCircuit c;
-  c.at.reserve(n);
-  c.ops.reserve(n);
-  c.theta.reserve(n);
   std::vector<char> done(n, 0);
-  auto take = [&](int k) {
-    done[k] = 1;
-    c.at.push_back(k);
-    c.ops.push_back(ops[k]);
-    c.theta.push_back(theta[k]);
-  };
   for (int a = 0; a < n; ++a) {
     if (done[a]) continue;
-    take(a);
-    if (!fusable(a)) continue;
-    int lo = ops[a].i, hi = lo, size = 1;
-    unsigned behind = 0u;
-    for (int b = a + 1; b < n && size < kRFuseMax; ++b) {
-      if (done[b]) continue;
-      const unsigned m = (1u << ops[b].i) | (1u << ops[b].j);
-      const int nlo = std::min(lo, ops[b].i), nhi = std::max(hi, ops[b].i);
-      if (!(m & behind) && fusable(b) && nhi - nlo <= 1) {
-        lo = nlo;
-        hi = nhi;
-        ++size;
-        take(b);
-      } else {
-        behind |= m;
-      }
+    int lo = ops[a].i, hi = lo;
+    for (int k : take_run(a, modes, (1u << g.L) - 1, fusable(a) ? kRFuseMax : 1, done, [&](int b) {
+           const int nlo = std::min(lo, ops[b].i), nhi = std::max(hi, ops[b].i);
+           if (!fusable(b) || nhi - nlo > 1) return false;
+           lo = nlo;
+           hi = nhi;
+           return true;
+         })) {
+      c.at.push_back(k);
+      c.ops.push_back(ops[k]);
+      c.theta.push_back(theta ? theta[k] : 0.0);
     }
   }
   return c;
@@ -1342,27 +1330,46 @@ int fock_energy_grad_adjoint(const fock_ham_t *ham, const fock_op_t *ops, const 
                      dEdtheta);
 }
 
-int fock_real_fusion_plan(const fock_ham_t *ham, const fock_op_t *ops, int n, int *run_k0, int *run_a,
-                          int *nruns) {
+// Geometry of a circuit on real states, or an error.
+static int real_circuit_geometry(const fock_ham_t *ham, const fock_op_t *ops, int n, Geometry *g) {
   uint32_t namp = 0;
   int rc = check_ham_layout(ham, &namp, true);
   if (rc) return rc;
   if (n < 0 || n > 4096) return set_error(FOCK_ERR_ARG, "n=%d out of range", n);
-  if (n > 0 && (!ops || !run_k0 || !run_a)) return set_error(FOCK_ERR_ARG, "ops/run_k0/run_a is NULL");
-  if (!nruns) return set_error(FOCK_ERR_ARG, "nruns is NULL");
+  if (n > 0 && !ops) return set_error(FOCK_ERR_ARG, "ops is NULL");
   for (int k = 0; k < n; ++k) {
     if ((rc = check_op(ops[k], ham->L))) return rc;
     if (ops[k].type != FOCK_HR && ops[k].type != FOCK_PR)
       return set_error(FOCK_ERR_UNSUPPORTED, "real states take HR and PR gates only (gate %d)", k);
   }
-  Geometry g{ham->L, ham->d, namp};
-  g.half = (ham->layout & 3) != FOCK_LAYOUT_FULL ? 1 : 0;
+  *g = Geometry{ham->L, ham->d, namp};
+  g->half = (ham->layout & 3) != FOCK_LAYOUT_FULL ? 1 : 0;
+  return FOCK_OK;
+}
+
+int fock_real_fusion_plan(const fock_ham_t *ham, const fock_op_t *ops, int n, int *run_k0, int *run_a,
+                          int *nruns) {
+  Geometry g;
+  const int rc = real_circuit_geometry(ham, ops, n, &g);
+  if (rc) return rc;
+  if (n > 0 && (!run_k0 || !run_a)) return set_error(FOCK_ERR_ARG, "run_k0/run_a is NULL");
+  if (!nruns) return set_error(FOCK_ERR_ARG, "nruns is NULL");
   const std::vector<RealRun> runs = plan_real_runs(g, ops, n);
   for (size_t r = 0; r < runs.size(); ++r) {
     run_k0[r] = runs[r].k0;
     run_a[r] = runs[r].a;
   }
   *nruns = (int)runs.size();
+  return FOCK_OK;
+}
+
+int fock_real_fusion_order(const fock_ham_t *ham, const fock_op_t *ops, int n, int *at) {
+  Geometry g;
+  const int rc = real_circuit_geometry(ham, ops, n, &g);
+  if (rc) return rc;
+  if (n > 0 && !at) return set_error(FOCK_ERR_ARG, "at is NULL");
+  const RealCircuit c = real_order(g, ops, nullptr, n);
+  std::copy(c.at.begin(), c.at.end(), at);
   return FOCK_OK;
 }
 

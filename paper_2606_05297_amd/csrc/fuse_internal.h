@@ -70,6 +70,26 @@ inline size_t fuse_lds(int d, int T, int ng, bool rev) {
 }
 
 bool fuse_supported(int d);
+// The items that run together with item a: a, and later ones that `joins` takes (asked
+// in order) and whose modes meet no item left behind: those commute with all of them
+// and may move up.  all: every mode; cap: items at most.  Marks them done.
+template <class Joins>
+std::vector<int> take_run(int a, const std::vector<unsigned> &modes, unsigned all, size_t cap, std::vector<char> &done,
+                          Joins joins) {
+  std::vector<int> take{a};
+  done[a] = 1;
+  unsigned behind = 0u;
+  for (int b = a + 1; b < (int)modes.size() && take.size() < cap && (~behind & all); ++b) {
+    if (done[b]) continue;
+    if (!(modes[b] & behind) && joins(b)) {
+      take.push_back(b);
+      done[b] = 1;
+    } else {
+      behind |= modes[b];
+    }
+  }
+  return take;
+}
 // Passes of ops[0..n) in the order they run; fuse: with fused runs.
 std::vector<GateGroup> plan_gate_groups(const Geometry &g, const fock_op_t *ops, int n, bool fuse);
 int fuse_modes(const Geometry &g);

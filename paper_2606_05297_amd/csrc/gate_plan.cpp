@@ -15,7 +15,6 @@ namespace {
 // A gate, or a run of single-mode phase gates, to be placed as a whole.
 struct Item {
   int k0, k1;
-  unsigned modes;
   bool fusable;
 };
 
@@ -86,11 +85,14 @@ std::vector<GateGroup> plan_gate_groups(const Geometry &g, const fock_op_t *ops,
   const int Lf = g.half ? g.L - 1 : g.L, smax = fuse_modes(g);
   const bool on = fuse && fuse_supported(g.d) && smax >= 3;
   std::vector<Item> items;
+  std::vector<unsigned> modes;
   for (int k = 0; k < n;) {
-    Item it{k, std::max(diag_run_end(ops, n, k), k + 1), 0u, false};
-    for (int q = it.k0; q < it.k1; ++q) it.modes |= mode_mask(ops[q]);
-    it.fusable = on && it.k1 == it.k0 + 1 && !is_squeeze(ops[k].type) && !(it.modes >> Lf);
+    Item it{k, std::max(diag_run_end(ops, n, k), k + 1), false};
+    unsigned m = 0u;
+    for (int q = it.k0; q < it.k1; ++q) m |= mode_mask(ops[q]);
+    it.fusable = on && it.k1 == it.k0 + 1 && !is_squeeze(ops[k].type) && !(m >> Lf);
     items.push_back(it);
+    modes.push_back(m);
     k = it.k1;
   }
   std::vector<GateGroup> out;
@@ -98,29 +100,19 @@ std::vector<GateGroup> plan_gate_groups(const Geometry &g, const fock_op_t *ops,
   for (size_t a = 0; a < items.size(); ++a) {
     if (done[a]) continue;
     GateGroup gr;
-    std::vector<size_t> take{a};
-    unsigned mask = 1u | items[a].modes;  // mode 0 always, so that rows stay contiguous
-    if (items[a].fusable && __builtin_popcount(mask) <= smax) {
-      // Later gates join while the union of modes fits the tile; one whose modes
-      // meet no gate left behind commutes with all of them and may move up.
-      unsigned behind = 0u;
-      for (size_t b = a + 1; b < items.size() && take.size() < kMaxFuseGates && ~behind & ((1u << g.L) - 1); ++b) {
-        if (done[b]) continue;
-        const unsigned u = mask | items[b].modes;
-        if (items[b].fusable && !(items[b].modes & behind) && __builtin_popcount(u) <= smax) {
-          mask = u;
-          take.push_back(b);
-        } else {
-          behind |= items[b].modes;
-        }
-      }
-      if (take.size() > 1)  // the tile's other modes: the lowest
-        for (int r = 0; r < Lf && __builtin_popcount(mask) < smax; ++r) mask |= 1u << r;
-    }
-    for (size_t b : take) {
-      done[b] = 1;
+    unsigned mask = 1u | modes[a];  // mode 0 always, so that rows stay contiguous
+    const bool open = items[a].fusable && __builtin_popcount(mask) <= smax;
+    // later gates join while the union of modes fits the tile
+    const std::vector<int> take = take_run((int)a, modes, (1u << g.L) - 1, open ? kMaxFuseGates : 1, done, [&](int b) {
+      const unsigned u = mask | modes[b];
+      if (!items[b].fusable || __builtin_popcount(u) > smax) return false;
+      mask = u;
+      return true;
+    });
+    if (take.size() > 1)  // the tile's other modes: the lowest
+      for (int r = 0; r < Lf && __builtin_popcount(mask) < smax; ++r) mask |= 1u << r;
+    for (int b : take)
       for (int k = items[b].k0; k < items[b].k1; ++k) gr.k.push_back(k);
-    }
     gr.diag = take.size() == 1 && gr.k.size() > 1;
     if (take.size() > 1)
       for (int r = 0; r < Lf; ++r)

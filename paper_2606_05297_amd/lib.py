@@ -116,6 +116,7 @@ def load(path: str = LIB_PATH):
     L.fock_set_real_states.argtypes = [C.c_int]
     L.fock_set_real_fusion.argtypes = [C.c_int]
     L.fock_real_fusion_plan.argtypes = [C.POINTER(Ham), C.POINTER(Op), C.c_int, ip, ip, ip]
+    L.fock_real_fusion_order.argtypes = [C.POINTER(Ham), C.POINTER(Op), C.c_int, ip]
     L.adapt_real.argtypes = [vp, ip]
     L.fock_sector_pack.argtypes = [C.c_int, C.c_int, C.c_int, vp, vp, vp]
     L.fock_sector_unpack.argtypes = [C.c_int, C.c_int, C.c_int, vp, vp, vp]
@@ -343,6 +344,14 @@ def real_fusion_plan(h: Ham, ops):
     nr = C.c_int(0)
     _check(load().fock_real_fusion_plan(C.byref(h), ops_array(ops), n, k0, a, C.byref(nr)))
     return [(k0[r], a[r]) for r in range(nr.value)]
+
+
+def real_fusion_order(h: Ham, ops):
+    """The order in which an evaluation on real states runs ops: indices into
+    ops (fock_real_fusion_order; host only)."""
+    at = (C.c_int * max(len(ops), 1))()
+    _check(load().fock_real_fusion_order(C.byref(h), ops_array(ops), len(ops), at))
+    return list(at[:len(ops)])
 
 
 def set_sector_layout(mode: int):
