@@ -54,7 +54,8 @@ HBM_PEAK_GBS = 8000.0
 METRIC = "ADAPT steps/s, Kitaev-Kerr L=8 d=8, |ΔE|<1e-5 vs ED; apply-H GB/s vs peak"
 KERNEL_NAMES = {0: "apply_h", 1: "pool_grads", 2: "gate2", 3: "gate2_adjoint", 4: "diag_gate", 9: "score",
                 10: "gate2_real", 11: "gate2_adjoint_real", 12: "real_convert", 13: "apply_h_real",
-                14: "gate2_real_fused", 15: "gate2_adjoint_real_fused"}
+                14: "gate2_real_fused", 15: "gate2_adjoint_real_fused", 16: "small_eval", 17: "gate2_fused",
+                18: "gate2_adjoint_fused"}
 
 
 def traffic_for(kid: int):

@@ -686,7 +686,9 @@ enum { FOCK_K_APPLY_H = 0, FOCK_K_POOL = 1, FOCK_K_GATE = 2, FOCK_K_ADJ = 3, FOC
        FOCK_K_CONVERT = 12 /* real <-> complex64 state conversion around H psi */,
        FOCK_K_APPLY_H_REAL = 13 /* two-pass H psi on real states */,
        FOCK_K_RFUSE = 14, FOCK_K_RFUSE_ADJ = 15 /* fused runs of real gates / reverse steps */,
-       FOCK_K_NUM = 16 };
+       FOCK_K_SMALL = 16 /* whole evaluation of a small state; bytes: psi0 read, without gradient states written */,
+       FOCK_K_FUSE = 17, FOCK_K_FUSE_ADJ = 18 /* fused runs on complex64 states / reverse steps */,
+       FOCK_K_NUM = 19 };
 
 /* Enable/disable event timing of launches (off by default). */
 int fock_prof_enable(int on);

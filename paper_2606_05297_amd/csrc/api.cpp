@@ -455,7 +455,7 @@ static int reverse_sweep(Ctx &c, const fock_op_t *ops, int n, const std::vector<
       continue;
     }
     if (gr.s > 0 && reverse_fused(c)) {
-      ProfScope ps(FOCK_K_ADJ, c.s, 32.0 * c.g.n_amp);
+      ProfScope ps(FOCK_K_FUSE_ADJ, c.s, 32.0 * c.g.n_amp);
       rc = launch_fuse_adj(make_fuse_args(c.g, c.T, gr, ops), phi, lam, tables_of(c), part, c.L.rs, c.s);
       if (rc) return rc;
       continue;
@@ -506,7 +506,7 @@ static int forward_circuit(Ctx &c, const fock_op_t *ops, int n, const std::vecto
     } else if (gr.s == 0) {
       rc = forward_gate(c, ops[gr.k.front()], gr.k.front(), false, src, phi);
     } else {
-      ProfScope ps(FOCK_K_GATE, c.s, 16.0 * c.g.n_amp);
+      ProfScope ps(FOCK_K_FUSE, c.s, 16.0 * c.g.n_amp);
       rc = launch_fuse_fwd(make_fuse_args(c.g, c.T, gr, ops), src, phi, tables_of(c), c.s);
     }
     if (rc) return rc;
@@ -729,7 +729,7 @@ static int enqueue_small(Ctx &c, const fock_op_t *ops, const double *theta, int 
   it.U = (const float2 *)(c.ws + c.L.utab);
   it.recs = (const GateRec *)(c.ws + c.L.recs);
   it.res = res;
-  ProfScope ps(grad ? FOCK_K_ADJ : FOCK_K_GATE, c.s, ((grad ? 48.0 : 16.0) * n + 16.0) * c.g.n_amp);
+  ProfScope ps(FOCK_K_SMALL, c.s, (grad ? 8.0 : 24.0) * c.g.n_amp);
   return launch_small_eval(it, nullptr, 0, small_lds_bytes(it), small_waves(it), c.T, nullptr, c.s);
 }
 

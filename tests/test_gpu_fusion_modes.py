@@ -15,7 +15,7 @@ from paper_2606_05297_amd import lib
 
 pytestmark = pytest.mark.gpu
 
-GATE, ADJ, DIAG = 2, 3, 4
+APPLY_H, GATE, ADJ, SMALL, FUSE, FUSE_ADJ = 0, 2, 3, 16, 17, 18
 TWO = ("HR", "HI", "DH", "PR", "PI", "CK")
 
 
@@ -27,8 +27,8 @@ def off():
     lib.set_gate_fusion(prev)
 
 
-def launches(fn, families=(GATE, ADJ)):
-    """Launches of forward gates and reverse steps that fn() enqueues."""
+def launches(fn, families=(GATE, ADJ, FUSE, FUSE_ADJ, SMALL, APPLY_H)):
+    """Launches of these kernel families that fn() enqueues."""
     lib.prof_reset()
     lib.prof_enable(True)
     try:
@@ -56,13 +56,33 @@ def test_launches_of_each_mode(L, d):
         lib.set_gate_fusion(prev)
     print("[case] launches", L, d, got, flush=True)
     n = len(ops)
-    assert got[lib.FUSE_OFF] == [n, n]
+    assert got[lib.FUSE_OFF] == [n, n, 0, 0, 0, 1]
     if d ** L == 256:  # too few tiles for fused runs: one launch, or gate by gate
-        assert got[lib.FUSE_FORWARD] == got[lib.FUSE_ALL] == [n, n] and got[lib.FUSE_AUTO] == [0, 1]
+        assert got[lib.FUSE_FORWARD] == got[lib.FUSE_ALL] == got[lib.FUSE_OFF]
+        assert got[lib.FUSE_AUTO] == [0, 0, 0, 0, 1, 0]
         return
-    assert got[lib.FUSE_FORWARD][0] < n and got[lib.FUSE_FORWARD][1] == n
-    assert got[lib.FUSE_ALL][0] < n and got[lib.FUSE_ALL][1] < n
+    single, adj, runs, rruns, small, _ = got[lib.FUSE_ALL]
+    assert 0 < runs == rruns and single == adj and single + runs < n and small == 0
+    assert got[lib.FUSE_FORWARD] == [single, n, runs, 0, 0, 1]
     assert got[lib.FUSE_AUTO] == got[lib.FUSE_ALL]
+
+
+def test_bytes_of_a_whole_evaluation():
+    """psi0 read once; without a gradient the two states written."""
+    L, d = 4, 4
+    h = lib.ham(L, d, False, 1.0, 0.5)
+    x = torch.from_numpy(W.random_state(L, d, seed=2)).cuda()
+    a, b = torch.empty_like(x), torch.empty_like(x)
+    ws = lib.workspace(h, 0, 3)
+    for grad, per in ((True, 8), (False, 24)):
+        lib.prof_reset()
+        lib.prof_enable(True)
+        try:
+            lib.energy_grad_adjoint(h, [("HR", 0, 1)] * 3, [0.1, 0.2, 0.3], x, a, b, ws, grad=grad)
+            assert lib.prof_query(SMALL)["bytes"] == per * d ** L
+        finally:
+            lib.prof_enable(False)
+            lib.prof_reset()
 
 
 def two(L, n):
@@ -103,10 +123,9 @@ def test_small_states_leave_passes_that_are_faster(k):
     def run():
         return lib.energy_grad_adjoint(h, ops, th, x, a, b, ws)
 
-    APPLY_H = 0
-    got = launches(run, (GATE, ADJ, APPLY_H))
+    got = launches(run)
     print("[case] plan", L, d, len(ops), got, flush=True)
-    assert (got == [0, 1, 0]) == one and (got[2] == 1) == (not one)
+    assert got[4:] == ([1, 0] if one else [0, 1])
     E, _, g = run()
     prev = lib.get_gate_fusion()
     lib.set_gate_fusion(lib.FUSE_OFF)
