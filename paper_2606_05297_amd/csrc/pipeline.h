@@ -37,8 +37,8 @@ struct Ctx {
 int gate_fusion_mode();  // FOCK_FUSE_*
 
 // Results that kernels write into host memory: fine-grained, so that they are there
-// once the stream is done.
-constexpr unsigned kHostResultFlags = hipHostMallocCoherent | hipHostMallocMapped;
+// once the stream is done, and for every device, since a thread may change its own.
+constexpr unsigned kHostResultFlags = hipHostMallocCoherent | hipHostMallocMapped | hipHostMallocPortable;
 // The calling thread's buffer for count of them, at most kHostResults; a call that
 // hands it to a kernel waits for the stream before it returns.
 constexpr size_t kHostResults = 13312;
