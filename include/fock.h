@@ -383,7 +383,8 @@ typedef struct fock_sweep fock_sweep_t;
  * run in lockstep: every phase of all points is one batched launch per d,
  * and each energy + adjoint-gradient round of the BFGS re-optimisations is a
  * replay of one captured HIP graph.  Results per point are identical to
- * adapt_step on that point alone (same kernels, same reduction order).
+ * adapt_step on that point alone on complex64 states (same passes, same reduction
+ * order), in the gate fusion modes FOCK_FUSE_AUTO and FOCK_FUSE_OFF.
  * opts: iteration caps, tolerances and BFGS settings shared by all points
  * (its warm-up fields are ignored; each point brings its own).  The sweep owns
  * its device buffers and a private stream; `stream` is synchronised once at
@@ -595,10 +596,13 @@ int fock_real_fusion_order(const fock_ham_t *ham, const fock_op_t *ops, int n, i
  * differences far below the complex64 state's ~1e-7 relative rounding (the
  * paper runs to |E - E0| ~ 1e-10, Sec. V).  Same loop as adapt_step: pool
  * scoring, tie band, append at theta = 0, BFGS with the L-inf tolerance and
- * optional Hessian recycling (no noise-floor stop).  Plain kernels (one thread
- * per amplitude for H psi; one workgroup per group of fibres with a dense
- * local gate matrix of d^2 x d^2 or d x d), meant for lattices of up to ~1e6
- * amplitudes.  psi0: device, d^L complex128 (copied); opts: as adapt_create
+ * optional Hessian recycling (no noise-floor stop).  States of d <= 8 that fit
+ * one workgroup's LDS twice (up to about 4,100 amplitudes; at most 256 gates) are
+ * evaluated in one launch; larger ones by plain kernels (one thread per amplitude
+ * for H psi; one workgroup per group of fibres with a dense local gate matrix of
+ * d^2 x d^2 or d x d), meant for lattices of up to ~1e6 amplitudes.  An
+ * optimisation that starts on a saddle (a two-parameter pool on a real psi0)
+ * leaves it by rounding, on either path.  psi0: device, d^L complex128 (copied); opts: as adapt_create
  * (a warm-up layer of one-parameter ops leads the ansatz, is BFGS-optimised
  * here with tolerance max(warm_gtol, gtol_floor_rel max(1,|E|)) and re-optimised
  * with every step, Appendix C; with warm_fixed its angles stay at warm_theta0

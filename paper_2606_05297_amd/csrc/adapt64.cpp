@@ -209,7 +209,7 @@ int eval_launches(fock_adapt64 *st, const std::vector<double> &th, bool grad, co
 
 // E (Rayleigh quotient), <psi|psi>, and the gate gradients when g != nullptr,
 // for the gates st->gops at angles th.  Leaves phi = psi and lam = H psi when
-// no gradient is asked for.
+// no gradient is asked for, up to a global phase common to both.
 int eval_gates(fock_adapt64 *st, const std::vector<double> &th, double *E, double *n2, std::vector<double> *g) {
   const int n = (int)st->gops.size();
   if (n > st->cap) return set_error(FOCK_ERR_SIZE, "more gates (%d) than the run's capacity (%d)", n, st->cap);

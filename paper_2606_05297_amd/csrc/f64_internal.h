@@ -34,7 +34,8 @@ int launch64_build(const double *theta, const GateRec *recs, int n, const EigTab
 // One evaluation of a small state by one workgroup (f64_small.hip): psi0 through
 // the n gates, then (<phi|H phi>, <phi|phi>) into res[0..1] and, with grad,
 // Re<lam_k|A_k phi_k> into res[2 + k]; without grad the states go to phi and
-// lam.  theta, gates (type | gate_modes << 8) and res are
+// lam, both times the global phase 0.8 + 0.6 i (f64_small.hip: why), which no
+// energy, gradient or score depends on.  theta, gates (type | gate_modes << 8) and res are
 // host-visible; links: small64_links.
 struct Small64 {
   const double2 *psi0;

@@ -171,7 +171,8 @@ __global__ __launch_bounds__(kThreads64) void k64_small(Small64 it, H64 h, EigTa
   // The states carry a global phase.  E, gradients and scores do not depend on
   // it, but a real psi0 would stay real to the last bit under HR, PR and SR here,
   // and an optimisation that starts on a saddle of real states (the phases of
-  // two-parameter gates at 0) would never leave it: rounding makes it do so.
+  // two-parameter gates at 0) would never leave it.  Rounding makes it do so, as
+  // in the launches of larger states, whose complex tables round off the real axis.
   for (int a = tid; a < N; a += kThreads64) phi[at64<D>(a)] = mul(make_double2(0.8, 0.6), it.psi0[a]);
   for (int k = tid; k < n; k += kThreads64) {
     const int g = it.gates[k], type = g & 0xff, i = (g >> 8) & 0xff, j = (g >> 16) & 0xff;

@@ -2,9 +2,10 @@
 // (fock_energy_grad_adjoint, the ADAPT, HVA and sweep drivers): one workgroup
 // keeps phi and lam in LDS from psi0 to the last gradient.
 //
-// These states (up to about 9,500 amplitudes, 150 KB for both) are far too
-// small to fill the chip, and gate by gate a circuit of n gates is 2n + 5
-// launches of 2-6 us each, most of it launch gap and memory latency.  Here a
+// These states (LDS takes both of up to about 9,500 amplitudes; the plan gives it
+// those of up to 4,096, small_planned) are far too small to fill the chip, and gate
+// by gate a circuit of n gates is 2n + 5 launches of 2-6 us each, most of it launch
+// gap and memory latency.  Here a
 // gate is one pass over LDS (the matrix-core tile code of tile_gate.h) and one
 // barrier; a reverse step is the same on two states plus one wave reduction.
 // The gate tables come into LDS in bulk, as many gates at a time as fit beside
@@ -15,7 +16,8 @@
 // Bound by instruction issue and LDS latency of the one CU.  Per gate forward /
 // reverse: 0.48 / 0.78 us at 64-256 amplitudes (d = 4), 1.1 / 2.1 at 1,296
 // (d = 6), 1.5 / 2.6 at 4,096 (d = 8), 2.6 / 5.5 at 7,776 (d = 6), against
-// 1.8-6 / 2.6-8 us and a launch gap each for the per-gate kernels.  With 8
+// 1.8-6 / 2.6-8 us and a launch gap each for the per-gate kernels.  A squeezer is
+// dense work of one thread a fibre: 3 us forward and 8 in reverse at d = 8.  With 8
 // instead of 16 waves from 1,296 amplitudes on it ran 10-35 % slower; with the
 // next gate's operands held in registers, 20-60 % slower (spills).
 #include "small_eval.h"

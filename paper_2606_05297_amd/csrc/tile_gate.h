@@ -16,12 +16,11 @@
 // v_mfma_f32_16x16x4_f32.  The reduction index is permuted so that lane l
 // supplies and receives the same two slots 2 (l / 16) and 2 (l / 16) + 1 of
 // fibre l % 16: it reads its two members, and writes them back in place, with
-// no exchange between lanes.  The matrix operand is two table entries per
-// lane, the same for every fibre, so it is loaded from global memory one gate
-// ahead and needs no LDS.  With the block tables broadcast from LDS instead, a
-// gate on vector ALUs reads b^2 table entries a block beside its 2 b members
-// (LDS-bound), and packed FP32, the other way to the full FP32 rate, is off in
-// this build.
+// no exchange between lanes.  The matrix operand is two table entries per lane,
+// the same for every fibre, so a wavefront reads it once a gate.  On vector ALUs,
+// with the block tables broadcast from LDS, a gate reads b^2 table entries a block
+// beside its 2 b members (LDS-bound), and packed FP32, the other way to the full
+// FP32 rate, is off in this build.
 #pragma once
 
 #include "gate_kernels.h"
@@ -151,8 +150,8 @@ __device__ __forceinline__ TileLane tile_lane(int D, int nwaves) {
 }
 
 // A lane's matrix operand for the four reduction steps: row (re or im) times
-// (re, im) of its two slots.  Loaded as table entries (TileRaw, so that a load
-// can be in flight while another gate runs) and finished by tile_mat.
+// (re, im) of its two slots.  Read as table entries (TileRaw) and finished by
+// tile_mat.
 struct TileRaw {
   unsigned e00, e01, e10, e11;
 };
