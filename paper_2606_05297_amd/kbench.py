@@ -21,7 +21,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 NAMES = {0: "apply_h", 1: "pool_grads", 2: "gate2", 3: "gate2_adjoint", 4: "diag_gate", 6: "mlp_forward",
-         7: "mlp_train_step", 8: "gate2_dense_mfma", 9: "score"}
+         7: "mlp_train_step", 8: "gate2_dense_mfma", 9: "score", 17: "gate2_fused", 18: "gate2_adjoint_fused"}
 
 
 def main():
@@ -129,14 +129,17 @@ def main():
         print(f"[kbench] dense done", file=sys.stderr, flush=True)
     if "adjoint" in want:
         ops, th = W.random_circuit(cfg["pool"], 8, seed=3)
+        planned = lib.get_gate_fusion()
+        lib.set_gate_fusion(lib.FUSE_OFF)  # the per-gate kernels
         for k in range(max(1, args.iters // 4)):
             lib.energy_grad_adjoint(h, ops, th, states[k % 3], outs[(k + 1) % 3], outs[(k + 2) % 3], ws)
+        lib.set_gate_fusion(planned)
         print(f"[kbench] adjoint done", file=sys.stderr, flush=True)
     if "m4" in want:
         # one energy + adjoint-gradient evaluation of a 30-gate circuit (gates drawn
         # from the pool with default_rng(3), angles U[-0.5, 0.5]) on the complex64
-        # tensor, against the plain method's central-difference gradient (2n energy
-        # evaluations); then a 30-gate HR / PR circuit on real parity-halved states,
+        # tensor, gate by gate and in the library's plan, against the plain method's
+        # central-difference gradient (2n energy evaluations, gate by gate); then a 30-gate HR / PR circuit on real parity-halved states,
         # gate by gate and with fused runs.  Wall time per call (results on the host).
         nm4, reps = 30, max(3, args.iters // 4)
         rng = np.random.default_rng(3)
@@ -154,9 +157,13 @@ def main():
             torch.cuda.synchronize()
             return (time.perf_counter() - t0) / reps
 
+        planned = lib.get_gate_fusion()
+        t_plan = per_call(lambda: lib.energy_grad_adjoint(h, ops, th, states[0], outs[1], outs[2], ws30))
+        lib.set_gate_fusion(lib.FUSE_OFF)
         t_adj = per_call(lambda: lib.energy_grad_adjoint(h, ops, th, states[0], outs[1], outs[2], ws30))
         t_en = per_call(lambda: lib.energy_grad_adjoint(h, ops, th, states[0], outs[1], outs[2], ws30, grad=False))
-        m4 = {"n": nm4, "complex_full": {
+        lib.set_gate_fusion(planned)
+        m4 = {"n": nm4, "complex_full_planned": {"adjoint_ms": 1e3 * t_plan}, "complex_full": {
             "adjoint_ms": 1e3 * t_adj, "algorithmic_GB": (48 * nm4 + 16) * n / 1e9,
             "GBs": (48 * nm4 + 16) * n / t_adj / 1e9, "energy_ms": 1e3 * t_en,
             "fd_gradient_ms": 1e3 * 2 * nm4 * t_en, "adjoint_speedup_vs_fd": 2 * nm4 * t_en / t_adj}}
@@ -174,7 +181,8 @@ def main():
             for mode, name in ((lib.RFUSE_OFF, "real_halved_gate_by_gate"), (lib.RFUSE_ON, "real_halved_fused")):
                 lib.set_real_fusion(mode)
                 t = per_call(lambda: lib.energy_grad_adjoint(hr, ops_r, th, x0, a, b, wsr))
-                m4[name] = {"adjoint_ms": 1e3 * t, "runs": len(lib.real_fusion_plan(hr, ops_r)),
+                moved = [ops_r[k] for k in lib.real_fusion_order(hr, ops_r)]  # as the evaluation runs them
+                m4[name] = {"adjoint_ms": 1e3 * t, "runs": len(lib.real_fusion_plan(hr, moved)),
                             "algorithmic_GB": (24 * nm4 + 8) * (n // 2) / 1e9}
             lib.set_real_fusion(lib.RFUSE_ON)
         res["m4"] = m4
